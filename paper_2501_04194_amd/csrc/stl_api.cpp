@@ -361,6 +361,7 @@ static stl_status run(const stl_plan* plan, const stl_batch* bt, const float* pa
     ka.arena_floats = (int64_t)g.arena_floats;
     ka.counter = (int*)wsb;
     ka.persistent = g.persistent;
+    ka.nt = g.nt;
     // dense node traces are [n_nodes][B*T]; a ragged batch's N_total (offsets[B])
     // is read by the kernel itself
     if (nodes && !bt->offsets) ka.n_total = bt->B * bt->T;
@@ -432,8 +433,7 @@ static stl_status run(const stl_plan* plan, const stl_batch* bt, const float* pa
         if (saved == 1 && g.fused) ka.saved = traces;
         if (saved == 2 && g.fused) ka.saved_in = traces;
         // a forward that does not take the fused path leaves nothing to reuse
-        if (saved == 1 && !g.fused && launch_fill_int(flags, bt->B, 0, st) != hipSuccess)
-            return fail(STL_E_HIP, "launch failed: %s", hipGetErrorString(hipGetLastError()));
+        if (saved == 1 && !g.fused) ka.saved_none = flags;
         // (matrix-core layout: geometry marked unusable, so that a matrix-core
         // backward hands every trajectory to the generic executor)
         if (saved == 1 && mx_applies(plan->dev, bt, nullptr, false) &&
@@ -454,10 +454,11 @@ static stl_status run(const stl_plan* plan, const stl_batch* bt, const float* pa
         kf.persistent = 1;
         e = launch_exec(bwd, dp, b, kf, g.grid, g.nt, g.lds_bytes, st);
     } else {
+        if (bwd && dp.n_masks == 0) ka.gp_zero = gparams;
         e = launch_exec(bwd, dp, b, ka, g.grid, g.nt, g.lds_bytes, st);
     }
     if (e != hipSuccess) return fail(STL_E_HIP, "kernel launch failed: %s", hipGetErrorString(e));
-    if (bwd && gparams) {
+    if (bwd && gparams && !ka.gp_zero) {
         e = launch_reduce_params(ka.mask_part, bt->B, dp, gparams, st);
         if (e != hipSuccess) return fail(STL_E_HIP, "launch failed: %s", hipGetErrorString(e));
     }

@@ -51,7 +51,7 @@ struct Builder {
     std::vector<Instr> ins;
     std::vector<std::vector<int>> kids;   // instruction children (instruction indices)
     std::vector<float> coef;
-    std::vector<int> pred_ins;
+    int n_pred = 0;
     std::vector<int> mask_params;
     int max_until_b = 0;
     bool has_until = false;
@@ -85,7 +85,7 @@ stl_status emit(Builder& B, int id, int depth, int* out)
     if (depth > 256) return fail(STL_E_FORMULA, "formula too deep (cycle?) at node %d", id);
     const stl_node& n = B.nodes[id];
     Instr I = blank();
-    I.node = (int16_t)id;
+    I.node = id;
     std::vector<int> ch;
     auto child = [&](int k) { return B.child_idx[n.child_off + k]; };
     // children first
@@ -126,7 +126,7 @@ stl_status emit(Builder& B, int id, int depth, int* out)
         const stl_pred& p = B.preds[n.pred];
         if (p.kind != n.op) return fail(STL_E_FORMULA, "node %d: predicate kind does not match the node op", id);
         I.kind = n.op == STL_PRED_LINEAR ? K_LIN : K_NORM;
-        I.coef = (int16_t)B.coef.size();
+        I.coef = (int32_t)B.coef.size();
         if (n.op == STL_PRED_LINEAR) {
             B.coef.push_back(p.c);
             for (int d = 0; d < B.D; ++d) B.coef.push_back(p.w[d]);
@@ -139,7 +139,7 @@ stl_status emit(Builder& B, int id, int depth, int* out)
             for (int i = 0; i < p.m * B.D; ++i) B.coef.push_back(p.A[i]);
         }
         if ((int)B.coef.size() > MAX_COEF) return fail(STL_E_UNSUPPORTED, "too many predicate coefficients");
-        if ((int)B.pred_ins.size() >= MAX_PRED) return fail(STL_E_UNSUPPORTED, "more than %d predicates", MAX_PRED);
+        if (B.n_pred >= MAX_PRED) return fail(STL_E_UNSUPPORTED, "more than %d predicates", MAX_PRED);
         break;
     }
     case STL_NOT:
@@ -187,7 +187,7 @@ stl_status emit(Builder& B, int id, int depth, int* out)
             if (n.b < 0) I.flags |= F_UNB;
             if (n.pad < 0 || n.pad > 2) return fail(STL_E_ARG, "node %d: bad pad policy", id);
             I.pad = (int8_t)n.pad;
-            I.coef = (int16_t)B.coef.size();
+            I.coef = (int32_t)B.coef.size();
             B.coef.push_back(n.pad_value);
         }
         break;
@@ -220,7 +220,7 @@ stl_status emit(Builder& B, int id, int depth, int* out)
         return fail(STL_E_FORMULA, "node %d: unknown op %d", id, n.op);
     }
     int k = B.new_instr(I, kid_ins);
-    if (n.op == STL_PRED_LINEAR || n.op == STL_PRED_NORM) B.pred_ins.push_back(k);
+    if (n.op == STL_PRED_LINEAR || n.op == STL_PRED_NORM) ++B.n_pred;
     *out = k;
     return STL_OK;
 }
@@ -233,6 +233,15 @@ int expected_children(int op, int* lo, int* hi)
     case STL_UNTIL: *lo = *hi = 2; return 1;
     case STL_AND: case STL_OR: *lo = 1; *hi = STL_MAX_CHILDREN; return 1;
     default: return 0;
+    }
+}
+
+// the predicates' entries (their instructions come first) from the slot maps
+void pred_refs(DevPlan& dp)
+{
+    for (int i = 0; i < dp.n_pred; ++i) {
+        const Instr& I = dp.ins[i];
+        dp.pred[i] = PredRef{I.coef, I.kind, I.f_out, I.b_out, I.g_out};
     }
 }
 
@@ -309,6 +318,22 @@ extern "C" stl_status stl_compile(const stl_node* nodes, int32_t n_nodes, const 
         return fail(STL_E_UNSUPPORTED, "predicate and pad coefficients need %d floats (max %d)", (int)B.coef.size(),
                     MAX_COEF);
 
+    // the predicates first (in their order), then the other instructions
+    {
+        std::vector<int> at(n);
+        int np = 0, no = B.n_pred;
+        for (int k = 0; k < n; ++k) at[k] = B.ins[k].kind == K_LIN || B.ins[k].kind == K_NORM ? np++ : no++;
+        std::vector<Instr> ins(n);
+        std::vector<std::vector<int>> kids(n);
+        for (int k = 0; k < n; ++k) {
+            ins[at[k]] = B.ins[k];
+            for (int c : B.kids[k]) kids[at[k]].push_back(at[c]);
+        }
+        B.ins.swap(ins);
+        B.kids.swap(kids);
+        rootk = at[rootk];
+    }
+
     // consumers
     std::vector<int> parent(n, -1);
     for (int k = 0; k < n; ++k)
@@ -318,11 +343,13 @@ extern "C" stl_status stl_compile(const stl_node* nodes, int32_t n_nodes, const 
     SlotAlloc fa;
     std::vector<int> fslot(n);
     {
-        // intervals: def = k, last = parent step (root: n)
-        for (int k = 0; k < n; ++k) {
-            int last = parent[k] < 0 ? n : parent[k];
-            fslot[k] = fa.get(k, last);
-        }
+        // intervals: def = k (predicates: 0, they are evaluated together
+        // before the first step), last = parent step (root: n)
+        auto pred = [&](int k) { return B.ins[k].kind == K_LIN || B.ins[k].kind == K_NORM; };
+        for (int k = 0; k < n; ++k)
+            if (pred(k)) fslot[k] = fa.get(0, parent[k] < 0 ? n : parent[k]);
+        for (int k = 0; k < n; ++k)
+            if (!pred(k)) fslot[k] = fa.get(k, parent[k] < 0 ? n : parent[k]);
     }
     // backward map: values get their own slots (kept through the adjoint sweep);
     // adjoints are allocated over the reverse sweep.  Step numbering for the
@@ -366,7 +393,7 @@ extern "C" stl_status stl_compile(const stl_node* nodes, int32_t n_nodes, const 
         if (I.kind != K_UNTIL) continue;
         I.coef = -1;
         if (I.flags & F_SMOOTH) {
-            I.coef = (int16_t)nbwd;
+            I.coef = nbwd;
             nbwd += 2;
         }
     }
@@ -380,13 +407,13 @@ extern "C" stl_status stl_compile(const stl_node* nodes, int32_t n_nodes, const 
     dp.D = D;
     dp.n_masks = (int)B.mask_params.size();
     dp.n_params = n_params;
-    dp.n_pred = (int)B.pred_ins.size();
+    dp.n_pred = B.n_pred;
     dp.root = rootk;
     dp.rho_max = rho_max;
     dp.rho_pad = rho_pad;
-    for (int i = 0; i < dp.n_pred; ++i) dp.pred_ins[i] = (int16_t)B.pred_ins[i];
-    for (int i = 0; i < dp.n_masks; ++i) dp.mask_param[i] = (int8_t)B.mask_params[i];
+    for (int i = 0; i < dp.n_masks; ++i) dp.mask_param[i] = B.mask_params[i];
     for (int k = 0; k < n; ++k) dp.ins[k] = B.ins[k];
+    pred_refs(dp);
     for (size_t i = 0; i < B.coef.size(); ++i) dp.coef[i] = B.coef[i];
     // fused fast path: root = smooth n-ary over <= 4 smooth-mask nodes on linear
     // predicates, or a single such mask node
@@ -431,6 +458,7 @@ extern "C" stl_status stl_compile(const stl_node* nodes, int32_t n_nodes, const 
         I.f_in1 = I.b_in1;
         for (int j = 0; j < MAX_NCH; ++j) I.f_ch[j] = I.b_ch[j];
     }
+    pred_refs(tp);
     p->n_nodes = n_nodes;
     p->n_params = n_params;
     p->D = D;

@@ -52,7 +52,7 @@ DEV SP sp_zero() { return SP{0.f, SP_NEG}; }
 DEV SP sp_leaf(float z)  // 2^z
 {
     float c = ceilf(fminf(fmaxf(z, -1e9f), 1e9f));
-    return SP{exp2f(z - c), (int)c};
+    return SP{__builtin_amdgcn_exp2f(z - c), (int)c};      // z - c in (-1, 0]: no denormal
 }
 
 DEV SP sp_add(SP a, SP b)
@@ -112,9 +112,6 @@ struct OpVI {
 struct OpD {
     __device__ __forceinline__ double operator()(double a, double b) const { return a + b; }
 };
-struct OpF {
-    __device__ __forceinline__ float operator()(float a, float b) const { return a + b; }
-};
 
 // ------------------------------------------------------------------ scans
 
@@ -126,123 +123,6 @@ struct Shared {
     int scan_pos, scan_min;      // flag-scan fix-up: next row index of this work-group, first set flag
 };
 
-// storage index maps for scanned arrays: identity, or one pad element after
-// every 8 (conflict-free LDS access when each lane owns 8 consecutive elements)
-struct IdxId {
-    __device__ __forceinline__ int operator()(int p) const { return p; }
-};
-struct IdxPad {
-    __device__ __forceinline__ int operator()(int p) const { return p + (p >> 3); }
-};
-
-// In-place inclusive scan of x[0..n) within segments.  Forward scans have
-// segment heads at positions with (p + off) % K == 0; reverse scans at
-// (p + off) % K == K-1 and at n-1.  K <= 0 means one segment.  Each thread
-// scans a contiguous chunk sequentially; chunk aggregates are combined with a
-// segmented Hillis-Steele pass; the carry is then applied to each chunk's
-// head part.  Must be called by every thread of the work-group.
-template <class T, class Op, class SH, class IX = IdxId>
-DEV void seg_scan(T* x, int n, int K, bool rev, T ident, Op op, SH& sh, int off = 0, IX ix = IX())
-{
-    const int tid = threadIdx.x, nt = blockDim.x;
-    T* shv = reinterpret_cast<T*>(sh.scan);
-    const int C = (n + nt - 1) / nt;
-    const int c0 = min(n, tid * C), c1 = min(n, c0 + C);
-    T acc = ident;
-    int head = 0;
-    if (c0 < c1) {
-        if (!rev) {
-            int rem = K > 0 ? (c0 + off) % K : c0;
-            for (int p = c0; p < c1; ++p) {
-                bool h = K > 0 ? (rem == 0) : (p == 0);
-                T v = x[ix(p)];
-                acc = h ? v : op(acc, v);
-                head |= h;
-                x[ix(p)] = acc;
-                if (K > 0 && ++rem == K) rem = 0;
-            }
-        } else {
-            int rem = K > 0 ? (c1 - 1 + off) % K : 0;
-            for (int p = c1 - 1; p >= c0; --p) {
-                bool h = (p == n - 1) || (K > 0 && rem == K - 1);
-                T v = x[ix(p)];
-                acc = h ? v : op(v, acc);
-                head |= h;
-                x[ix(p)] = acc;
-                if (K > 0) rem = rem == 0 ? K - 1 : rem - 1;
-            }
-        }
-    }
-    shv[tid] = acc;
-    sh.flag[tid] = head;
-    __syncthreads();
-    for (int d = 1; d < nt; d <<= 1) {
-        T a = shv[tid];
-        int f = sh.flag[tid];
-        int src = rev ? tid + d : tid - d;
-        if (!f && (rev ? src < nt : src >= 0)) {
-            T b = shv[src];
-            a = rev ? op(a, b) : op(b, a);
-            f = sh.flag[src];
-        }
-        __syncthreads();
-        shv[tid] = a;
-        sh.flag[tid] = f;
-        __syncthreads();
-    }
-    const int nb = rev ? tid + 1 : tid - 1;
-    if (c0 < c1 && nb >= 0 && nb < nt) {
-        T carry = shv[nb];
-        if (!rev) {
-            int rem = K > 0 ? (c0 + off) % K : c0;
-            for (int p = c0; p < c1; ++p) {
-                bool h = K > 0 ? (rem == 0) : (p == 0);
-                if (h) break;
-                x[ix(p)] = op(carry, x[ix(p)]);
-                if (K > 0 && ++rem == K) rem = 0;
-            }
-        } else {
-            int rem = K > 0 ? (c1 - 1 + off) % K : 0;
-            for (int p = c1 - 1; p >= c0; --p) {
-                bool h = (p == n - 1) || (K > 0 && rem == K - 1);
-                if (h) break;
-                x[ix(p)] = op(x[ix(p)], carry);
-                if (K > 0) rem = rem == 0 ? K - 1 : rem - 1;
-            }
-        }
-    }
-    __syncthreads();
-}
-
-// deterministic work-group sum of one float per thread
-DEV float wg_sum(float v, Shared& sh)
-{
-    const int tid = threadIdx.x, nt = blockDim.x;
-    float* f = reinterpret_cast<float*>(sh.scan);
-    f[tid] = v;
-    __syncthreads();
-    for (int s = nt >> 1; s > 0; s >>= 1) {
-        if (tid < s) f[tid] += f[tid + s];
-        __syncthreads();
-    }
-    float r = f[0];
-    __syncthreads();
-    return r;
-}
-
-DEV int lower_bound_i(const int* a, int n, int key)
-{
-    int lo = 0, hi = n;
-    while (lo < hi) {
-        int mid = (lo + hi) >> 1;
-        if (a[mid] < key) lo = mid + 1; else hi = mid;
-    }
-    return lo;
-}
-
-// ------------------------------------------------------------------ context
-
-
 struct Env {
     const DevPlan* P;
     const float* x;    // this trajectory, [L, D]
@@ -251,7 +131,213 @@ struct Env {
     float* arena;      // slots
     float* scr;        // op scratch (SCR_FLOATS(Lc) floats)
     Shared* sh;
+    int nt;            // work-group size (blockDim.x is a 16-bit field of the argument segment in host
+                       // memory: a vector load of 1 to 2 us wherever the compiler reads it again)
 };
+
+// value of another lane by a DPP move (0x110 + k: row_shr:k within rows of 16
+// lanes, 0x142: lane 15 of the row below, 0x143: lane 31, 0x138: wave_shr:1;
+// lanes without a source read 0), for types of 8 bytes
+template <int CTRL, class T>
+DEV T dpp8(T v)
+{
+    static_assert(sizeof(T) == 8, "two words");
+    int w[2];
+    __builtin_memcpy(w, &v, 8);
+    w[0] = __builtin_amdgcn_update_dpp(0, w[0], CTRL, 0xF, 0xF, true);
+    w[1] = __builtin_amdgcn_update_dpp(0, w[1], CTRL, 0xF, 0xF, true);
+    __builtin_memcpy(&v, w, 8);
+    return v;
+}
+
+// n / K for 0 <= n <= 2^24, inv = 1 / K: the float quotient is below 2^21 for
+// K >= 8, so it is off by at most one
+DEV int div_k(int n, int K, float inv)
+{
+    if (K < 8) return n / K;
+    int q = (int)((float)n * inv);
+    const int r = n - q * K;
+    return r < 0 ? q - 1 : (r >= K ? q + 1 : q);
+}
+
+// Segmented inclusive scan of leaf(p), p in [0, n), into x, in two parts with
+// a work-group barrier between them (the caller's, so that scans which do not
+// depend on each other share it) and one after.  REV scans from n-1 down.
+// head(p) starts a segment (asked in scan order).  A short serial chain per
+// thread, then DPP steps inside the wave, then the totals of the waves before
+// through LDS: the scans are bound by latency (a few elements per thread), and
+// a Hillis-Steele pass over the work-group cost two barriers and two LDS trips
+// per step (a 100-sample hard formula: forward 17.1 us, backward 37.7 us).
+// Every thread must call both parts.
+struct ScanPos {
+    int c0, c1;        // this thread's elements
+    int free;          // how many of them, in scan order, precede its first segment head
+    bool wave_carry;   // no segment head in the lanes before
+};
+
+template <bool REV, class T, class Op>
+DEV T scan_join(T before, T v, Op op)
+{
+    return REV ? op(v, before) : op(before, v);
+}
+
+// elements per thread: odd, so that the lanes' 8-byte accesses fall on distinct banks
+DEV int scan_chunk(int n, int nt) { return (n + nt - 1) / nt | 1; }
+
+template <bool REV, class T, class Op, class Leaf, class Head>
+DEV T scan_local(T* x, int n, T ident, Op op, Leaf leaf, Head head, const Env& e, int which, ScanPos& s)
+{
+    const int C = scan_chunk(n, e.nt), lane = threadIdx.x & 63;
+    const int ct = REV ? (int)e.nt - 1 - (int)threadIdx.x : (int)threadIdx.x;
+    s.c0 = min(n, ct * C);
+    s.c1 = min(n, s.c0 + C);
+    const int m = s.c1 - s.c0;
+    s.free = m;
+    T acc = ident;
+    for (int i = 0; i < m; ++i) {
+        const int p = REV ? s.c1 - 1 - i : s.c0 + i;
+        const bool h = head(p);
+        const T v = leaf(p);
+        acc = (h || i == 0) ? v : scan_join<REV>(acc, v, op);
+        if (h) s.free = min(s.free, i);
+        x[p] = acc;
+    }
+    // wave: combine with the lane k below while no head lies in between
+    const unsigned long long hm = __ballot(s.free < m);
+    const unsigned long long upto = hm & (~0ull >> (63 - lane));
+    const int d = upto ? lane - (63 - __builtin_clzll(upto)) : lane;
+#define STLMI_SCAN_STEP(CTRL, COND)                    \
+    {                                                  \
+        const T b = dpp8<CTRL>(acc);                   \
+        if (COND) acc = scan_join<REV>(b, acc, op);    \
+    }
+    STLMI_SCAN_STEP(0x111, (lane & 15) >= 1 && d >= 1)
+    STLMI_SCAN_STEP(0x112, (lane & 15) >= 2 && d >= 2)
+    STLMI_SCAN_STEP(0x114, (lane & 15) >= 4 && d >= 4)
+    STLMI_SCAN_STEP(0x118, (lane & 15) >= 8 && d >= 8)
+    STLMI_SCAN_STEP(0x142, (lane & 16) && d >= (lane & 15) + 1)
+    STLMI_SCAN_STEP(0x143, lane >= 32 && d >= lane - 31)
+#undef STLMI_SCAN_STEP
+    s.wave_carry = (hm & ((1ull << lane) - 1)) == 0;
+    if (lane == 63) {
+        reinterpret_cast<T*>(e.sh->scan)[which * 8 + (threadIdx.x >> 6)] = acc;
+        e.sh->flag[which * 8 + (threadIdx.x >> 6)] = hm != 0;
+    }
+    const T ex = dpp8<0x138>(acc);
+    return lane == 0 ? ident : ex;
+}
+
+template <bool REV, class T, class Op>
+DEV void scan_carry(T* x, T carry, Op op, const Env& e, int which, const ScanPos& s)
+{
+    const int w = threadIdx.x >> 6, lane = threadIdx.x & 63;
+    if (e.nt > 64) {
+        // lane q % 8 scans the totals of waves 0 .. q (wave w needs those of 0 .. w-1)
+        const int q = lane & 7;
+        T c = reinterpret_cast<const T*>(e.sh->scan)[which * 8 + q];
+        const unsigned hm = (unsigned)__ballot(e.sh->flag[which * 8 + q] != 0) & 0xffu & ((2u << q) - 1u);
+        const int d = hm ? q - (31 - __builtin_clz(hm)) : q;
+#define STLMI_CARRY_STEP(CTRL, K)                        \
+    {                                                  \
+        const T b = dpp8<CTRL>(c);                     \
+        if (q >= K && d >= K) c = scan_join<REV>(b, c, op); \
+    }
+        STLMI_CARRY_STEP(0x111, 1)
+        STLMI_CARRY_STEP(0x112, 2)
+        STLMI_CARRY_STEP(0x114, 4)
+#undef STLMI_CARRY_STEP
+        int cw[2];
+        __builtin_memcpy(cw, &c, 8);
+        const int src = __builtin_amdgcn_readfirstlane(max(w - 1, 0));
+        cw[0] = __builtin_amdgcn_readlane(cw[0], src);
+        cw[1] = __builtin_amdgcn_readlane(cw[1], src);
+        __builtin_memcpy(&c, cw, 8);
+        if (s.wave_carry && w > 0) carry = lane == 0 ? c : scan_join<REV>(c, carry, op);
+    }
+    if (threadIdx.x == 0) return;        // nothing comes before
+    for (int i = 0; i < s.free; ++i) {
+        const int p = REV ? s.c1 - 1 - i : s.c0 + i;
+        x[p] = scan_join<REV>(carry, x[p], op);
+    }
+}
+
+// segment heads of the van Herk blocks: p % K == 0 upwards, p % K == K-1 (and
+// the last position) downwards; K <= 0: one segment
+struct BlockHead {
+    int K, n, rem;
+    float inv;
+    __device__ __forceinline__ BlockHead(int K_, int n_) : K(K_), n(n_), rem(-1), inv(K_ > 0 ? 1.f / (float)K_ : 0.f) {}
+};
+struct HeadUp : BlockHead {
+    using BlockHead::BlockHead;
+    __device__ __forceinline__ bool operator()(int p)
+    {
+        if (K <= 0) return p == 0;
+        rem = rem < 0 ? p - div_k(p, K, inv) * K : (rem + 1 == K ? 0 : rem + 1);
+        return rem == 0;
+    }
+};
+struct HeadDown : BlockHead {
+    using BlockHead::BlockHead;
+    __device__ __forceinline__ bool operator()(int p)
+    {
+        if (K > 0) rem = rem < 0 ? p - div_k(p, K, inv) * K : (rem == 0 ? K - 1 : rem - 1);
+        return p == n - 1 || (K > 0 && rem == K - 1);
+    }
+};
+
+// block prefixes and suffixes of the same leaves (K <= 0: suffixes of the
+// whole range only)
+template <class T, class Op, class Leaf>
+DEV void scan_blocks(T* pre, T* suf, int n, int K, T ident, Op op, Leaf leaf, const Env& e)
+{
+    ScanPos sp, ss;
+    T cp = ident;
+    const T cs = scan_local<true>(suf, n, ident, op, leaf, HeadDown(K, n), e, 0, ss);
+    if (K > 0) cp = scan_local<false>(pre, n, ident, op, leaf, HeadUp(K, n), e, 1, sp);
+    __syncthreads();
+    scan_carry<true>(suf, cs, op, e, 0, ss);
+    if (K > 0) scan_carry<false>(pre, cp, op, e, 1, sp);
+    __syncthreads();
+}
+
+// one scan of the whole work-group
+template <bool REV, class T, class Op, class Leaf, class Head>
+DEV void scan_one(T* x, int n, T ident, Op op, Leaf leaf, Head head, const Env& e)
+{
+    ScanPos s;
+    const T c = scan_local<REV>(x, n, ident, op, leaf, head, e, 0, s);
+    __syncthreads();
+    scan_carry<REV>(x, c, op, e, 0, s);
+    __syncthreads();
+}
+
+// does the window of K positions at t (ending at e2, clipped to n-1) lie in one block?
+DEV bool one_block(int t, int e2, int K, float inv, bool& at_start)
+{
+    const int q = div_k(t, K, inv) * K;
+    at_start = q == t;
+    return e2 < q + K;
+}
+
+// deterministic work-group sum of one value per thread (a fixed shuffle tree,
+// then the waves in order)
+template <class T>
+DEV T wg_sum(T v, const Env& e)
+{
+#pragma unroll
+    for (int d = 32; d > 0; d >>= 1) v += __shfl_xor(v, d);
+    T* tot = reinterpret_cast<T*>(e.sh->scan);
+    if ((threadIdx.x & 63) == 0) tot[threadIdx.x >> 6] = v;
+    __syncthreads();
+    T r = tot[0];
+    for (int w = 1; w < e.nt >> 6; ++w) r += tot[w];
+    __syncthreads();
+    return r;
+}
+
+// ------------------------------------------------------------------ context
+
 
 // scratch layout (floats): everything an operator needs, in units of Lc
 #define SCR_UNITS 16
@@ -263,154 +349,281 @@ DEV float pbeta(const Env& e, const Instr& I) { return I.beta >= 0 ? e.params[I.
 
 // ------------------------------------------------------------------ pointwise ops
 
-DEV void op_pred_fwd(const Env& e, const Instr& I, float* out)
+// a plan entry read as 32-bit words (scalar loads; single bytes of the
+// argument segment would be vector loads)
+template <class T>
+DEV T load_words(const T* p)
 {
-    const float* cf = e.P->coef + I.coef;
-    const int D = e.D;
-    if (I.kind == K_LIN) {
-        const float c = cf[0];
-        for (int t = threadIdx.x; t < e.L; t += blockDim.x) {
-            const float* xr = e.x + (size_t)t * D;
-            float s = 0.f;
-            for (int d = 0; d < D; ++d) s = fmaf(cf[1 + d], xr[d], s);
-            out[t] = s - c;
-        }
+    int w[sizeof(T) / 4];
+#pragma unroll
+    for (int i = 0; i < (int)(sizeof(T) / 4); ++i) w[i] = ((const int*)p)[i];
+    T v;
+    __builtin_memcpy(&v, w, sizeof(T));
+    return v;
+}
+
+// The predicates are evaluated for the whole formula at once: a row of x is
+// read once (per predicate it cost 0.5 to 1 us of latency in a short
+// trajectory) and feeds every predicate.
+constexpr int PRED_TB = 4;    // rows per thread and pass
+
+template <int D>
+DEV void load_row(const float* p, bool vec, float (&r)[D])
+{
+    if (vec && D == 4) {
+        const float4 v = *(const float4*)p;
+        r[0] = v.x; r[1 % D] = v.y; r[2 % D] = v.z; r[3 % D] = v.w;
+    } else if (vec && D == 2) {
+        const float2 v = *(const float2*)p;
+        r[0] = v.x; r[1 % D] = v.y;
     } else {
-        const int m = (int)cf[0];
-        const float r = cf[1], sg = cf[2];
-        for (int t = threadIdx.x; t < e.L; t += blockDim.x) {
-            const float* xr = e.x + (size_t)t * D;
-            float q = 0.f;
-            for (int i = 0; i < m; ++i) {
-                float z = -cf[3 + i];
-                for (int d = 0; d < D; ++d) z = fmaf(cf[7 + i * D + d], xr[d], z);
-                q = fmaf(z, z, q);
-            }
-            out[t] = sg * (sqrtf(q) - r);
+#pragma unroll
+        for (int d = 0; d < D; ++d) r[d] = p[d];
+    }
+}
+
+template <int D>
+DEV void store_row(float* p, bool vec, const float (&r)[D])
+{
+    if (vec && D == 4) *(float4*)p = float4{r[0], r[1 % D], r[2 % D], r[3 % D]};
+    else if (vec && D == 2) *(float2*)p = float2{r[0], r[1 % D]};
+    else {
+#pragma unroll
+        for (int d = 0; d < D; ++d) p[d] = r[d];
+    }
+}
+
+// rows of 2 or 4 floats are moved whole where they are aligned
+template <int D>
+DEV bool vec_rows(const float* p) { return (D == 2 || D == 4) && ((uintptr_t)p & (4 * D - 1)) == 0; }
+
+// A x - p of a norm predicate (rows i < m, others 0) and its squared length
+template <class Row>
+DEV float norm_rows(const float* cf, int m, int D, Row x, float (&z)[4])
+{
+    float q = 0.f;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+        z[i] = 0.f;
+        if (i < m) {
+            z[i] = -cf[3 + i];
+            for (int d = 0; d < D; ++d) z[i] = fmaf(cf[7 + i * D + d], x[d], z[i]);
+            q = fmaf(z[i], z[i], q);
+        }
+    }
+    return q;
+}
+
+template <class Row>
+DEV float pred_value(int kind, const float* cf, int D, Row x)
+{
+    if (kind == K_LIN) {
+        float s = 0.f;
+        for (int d = 0; d < D; ++d) s = fmaf(cf[1 + d], x[d], s);
+        return s - cf[0];
+    }
+    float z[4];
+    return cf[2] * (sqrtf(norm_rows(cf, (int)cf[0], D, x, z)) - cf[1]);
+}
+
+template <int D>
+DEV void preds_fwd(const Env& e, bool bwdmap)
+{
+    const DevPlan& P = *e.P;
+    const int nt = e.nt;
+    const bool vec = vec_rows<D>(e.x);
+    for (int t0 = threadIdx.x; t0 < e.L; t0 += PRED_TB * nt) {
+        float x[PRED_TB][D];
+#pragma unroll
+        for (int j = 0; j < PRED_TB; ++j)
+            if (t0 + j * nt < e.L) load_row<D>(e.x + (size_t)(t0 + j * nt) * D, vec, x[j]);
+#pragma unroll 2
+        for (int p = 0; p < P.n_pred; ++p) {
+            const PredRef I = load_words(&P.pred[p]);
+            float* out = slot(e, bwdmap ? I.b_out : I.f_out);
+#pragma unroll
+            for (int j = 0; j < PRED_TB; ++j)
+                if (t0 + j * nt < e.L) out[t0 + j * nt] = pred_value(I.kind, P.coef + I.coef, D, x[j]);
         }
     }
 }
 
+DEV void op_preds(const Env& e, bool bwdmap)
+{
+    switch (e.D) {
+    case 1: preds_fwd<1>(e, bwdmap); return;
+    case 2: preds_fwd<2>(e, bwdmap); return;
+    case 3: preds_fwd<3>(e, bwdmap); return;
+    case 4: preds_fwd<4>(e, bwdmap); return;
+    }
+    const DevPlan& P = *e.P;
+    for (int p = 0; p < P.n_pred; ++p) {
+        const PredRef I = load_words(&P.pred[p]);
+        float* out = slot(e, bwdmap ? I.b_out : I.f_out);
+        for (int t = threadIdx.x; t < e.L; t += e.nt)
+            out[t] = pred_value(I.kind, P.coef + I.coef, e.D, e.x + (size_t)t * e.D);
+    }
+}
+
 // d/dx of all predicates: dx[t, d] = sum_p dmu_p/dx_d * g_p[t]
-DEV void op_dx(const Env& e, float* dx)
+template <class Row, class Acc>
+DEV void pred_dx(const Env& e, int D, int t, Row x, Acc& acc)
 {
     const DevPlan& P = *e.P;
-    const int D = e.D;
-    for (int t = threadIdx.x; t < e.L; t += blockDim.x) {
-        const float* xr = e.x + (size_t)t * D;
-        float acc[MAX_D];
-        for (int d = 0; d < D; ++d) acc[d] = 0.f;
-        for (int p = 0; p < P.n_pred; ++p) {
-            const Instr& I = P.ins[P.pred_ins[p]];
-            const float g = slot(e, I.g_out)[t];
-            const float* cf = P.coef + I.coef;
-            if (I.kind == K_LIN) {
-                for (int d = 0; d < D; ++d) acc[d] = fmaf(cf[1 + d], g, acc[d]);
-            } else {
-                const int m = (int)cf[0];
-                const float sg = cf[2];
-                float z[4];
-                float q = 0.f;
-                for (int i = 0; i < m; ++i) {
-                    z[i] = -cf[3 + i];
-                    for (int d = 0; d < D; ++d) z[i] = fmaf(cf[7 + i * D + d], xr[d], z[i]);
-                    q = fmaf(z[i], z[i], q);
-                }
-                if (q > 0.f) {
-                    const float k = sg * g / sqrtf(q);
-                    for (int d = 0; d < D; ++d) {
-                        float s = 0.f;
-                        for (int i = 0; i < m; ++i) s = fmaf(cf[7 + i * D + d], z[i], s);
-                        acc[d] = fmaf(k, s, acc[d]);
-                    }
-                }
+    for (int p = 0; p < P.n_pred; ++p) {
+        const PredRef I = load_words(&P.pred[p]);
+        const float g = slot(e, I.g_out)[t];
+        const float* cf = P.coef + I.coef;
+        if (I.kind == K_LIN) {
+            for (int d = 0; d < D; ++d) acc[d] = fmaf(cf[1 + d], g, acc[d]);
+            continue;
+        }
+        const int m = (int)cf[0];
+        float z[4];
+        const float q = norm_rows(cf, m, D, x, z);
+        if (q > 0.f) {
+            const float k = cf[2] * g / sqrtf(q);
+            for (int d = 0; d < D; ++d) {
+                float v = 0.f;
+#pragma unroll
+                for (int i = 0; i < 4; ++i)
+                    if (i < m) v = fmaf(cf[7 + i * D + d], z[i], v);
+                acc[d] = fmaf(k, v, acc[d]);
             }
         }
-        for (int d = 0; d < D; ++d) dx[(size_t)t * D + d] = acc[d];
+    }
+}
+
+template <int D>
+DEV void preds_dx(const Env& e, float* dx)
+{
+    const bool vx = vec_rows<D>(e.x), vd = vec_rows<D>(dx);
+    for (int t = threadIdx.x; t < e.L; t += e.nt) {
+        float x[D], acc[D];
+        load_row<D>(e.x + (size_t)t * D, vx, x);
+#pragma unroll
+        for (int d = 0; d < D; ++d) acc[d] = 0.f;
+        pred_dx(e, D, t, x, acc);
+        store_row<D>(dx + (size_t)t * D, vd, acc);
+    }
+}
+
+DEV void op_dx(const Env& e, float* dx)
+{
+    switch (e.D) {
+    case 1: preds_dx<1>(e, dx); return;
+    case 2: preds_dx<2>(e, dx); return;
+    case 3: preds_dx<3>(e, dx); return;
+    case 4: preds_dx<4>(e, dx); return;
+    }
+    for (int t = threadIdx.x; t < e.L; t += e.nt) {
+        float acc[MAX_D];
+#pragma unroll
+        for (int d = 0; d < MAX_D; ++d) acc[d] = 0.f;
+        pred_dx(e, e.D, t, e.x + (size_t)t * e.D, acc);
+        for (int d = 0; d < e.D; ++d) dx[(size_t)t * e.D + d] = acc[d];
+    }
+}
+
+template <int N>
+DEV void nary_fwd(const Env& e, const Instr& I, const int8_t* ch, float* out)
+{
+    const float sg = (I.flags & F_MIN) ? -1.f : 1.f;
+    const bool smooth = I.flags & F_SMOOTH, soft = I.flags & F_SOFT;
+    const float bl = smooth ? pbeta(e, I) * LOG2E : 1.f;
+    const float* c[N];
+#pragma unroll
+    for (int k = 0; k < N; ++k) c[k] = slot(e, ch[k]);
+    for (int t = threadIdx.x; t < e.L; t += e.nt) {
+        float v[N], m = -INFINITY;
+#pragma unroll
+        for (int k = 0; k < N; ++k) v[k] = sg * c[k][t];
+        if (!smooth) {
+            m = v[0];
+#pragma unroll
+            for (int k = 1; k < N; ++k)
+                if (v[k] > m) m = v[k];
+            out[t] = sg * m;
+            continue;
+        }
+#pragma unroll
+        for (int k = 0; k < N; ++k) m = fmaxf(m, v[k]);
+        float s0 = 0.f, s1 = 0.f;
+#pragma unroll
+        for (int k = 0; k < N; ++k) {
+            const float q = exp2f((v[k] - m) * bl);
+            s0 += q;
+            s1 = fmaf(q, v[k], s1);
+        }
+        // softmax-weighted mean of the oriented values, or logsumexp (Sec. III-C)
+        out[t] = sg * (soft ? s1 / s0 : m + log2f(s0) / bl);
     }
 }
 
 DEV void op_nary_fwd(const Env& e, const Instr& I, const int8_t* ch, float* out)
 {
+    switch (I.nch) {
+    case 1: nary_fwd<1>(e, I, ch, out); break;
+    case 2: nary_fwd<2>(e, I, ch, out); break;
+    case 3: nary_fwd<3>(e, I, ch, out); break;
+    default: nary_fwd<4>(e, I, ch, out); break;
+    }
+}
+
+template <int N>
+DEV void nary_bwd(const Env& e, const Instr& I)
+{
     const float sg = (I.flags & F_MIN) ? -1.f : 1.f;
-    const int n = I.nch;
-    const float* c[MAX_NCH];
-    for (int k = 0; k < MAX_NCH; ++k) c[k] = slot(e, ch[k < n ? k : 0]);
-    if (!(I.flags & F_SMOOTH)) {
-        for (int t = threadIdx.x; t < e.L; t += blockDim.x) {
-            float best = sg * c[0][t];
-            for (int k = 1; k < n; ++k) {
-                float v = sg * c[k][t];
-                if (v > best) best = v;
-            }
-            out[t] = sg * best;
-        }
-    } else if (I.flags & F_SOFT) {
-        // softmax-weighted mean of the oriented values (Sec. III-C)
-        const float bl = pbeta(e, I) * LOG2E;
-        for (int t = threadIdx.x; t < e.L; t += blockDim.x) {
-            float v[MAX_NCH];
-            float m = -INFINITY;
-            for (int k = 0; k < n; ++k) { v[k] = sg * c[k][t]; m = fmaxf(m, v[k]); }
-            float s0 = 0.f, s1 = 0.f;
-            for (int k = 0; k < n; ++k) {
-                const float q = exp2f((v[k] - m) * bl);
-                s0 += q;
-                s1 = fmaf(q, v[k], s1);
-            }
-            out[t] = sg * (s1 / s0);
-        }
-    } else {
-        const float bl = pbeta(e, I) * LOG2E;
-        for (int t = threadIdx.x; t < e.L; t += blockDim.x) {
-            float v[MAX_NCH];
-            float m = -INFINITY;
-            for (int k = 0; k < n; ++k) { v[k] = sg * c[k][t]; m = fmaxf(m, v[k]); }
-            float s = 0.f;
-            for (int k = 0; k < n; ++k) s += exp2f((v[k] - m) * bl);
-            out[t] = sg * (m + log2f(s) / bl);
+    const bool smooth = I.flags & F_SMOOTH, soft = I.flags & F_SOFT;
+    const float bl = smooth ? pbeta(e, I) * LOG2E : 1.f;
+    const float* g = slot(e, I.g_out);
+    const float* out = slot(e, I.b_out);
+    const float* c[N];
+    float* gc[N];
+#pragma unroll
+    for (int k = 0; k < N; ++k) {
+        c[k] = slot(e, I.b_ch[k]);
+        gc[k] = slot(e, I.g_ch[k]);
+    }
+    for (int t = threadIdx.x; t < e.L; t += e.nt) {
+        const float gt = g[t];
+        float v[N];
+#pragma unroll
+        for (int k = 0; k < N; ++k) v[k] = sg * c[k][t];
+        if (!smooth) {
+            int kb = 0;
+            float best = v[0];
+#pragma unroll
+            for (int k = 1; k < N; ++k)
+                if (v[k] > best) { best = v[k]; kb = k; }
+#pragma unroll
+            for (int k = 0; k < N; ++k) gc[k][t] = (k == kb) ? gt : 0.f;
+        } else if (soft) {
+            // d r / d v_k = p_k (1 + beta (v_k - r)), r = sg out
+            const float r = sg * out[t], beta = bl / LOG2E;
+            float m = -INFINITY, s0 = 0.f;
+#pragma unroll
+            for (int k = 0; k < N; ++k) m = fmaxf(m, v[k]);
+#pragma unroll
+            for (int k = 0; k < N; ++k) s0 += exp2f((v[k] - m) * bl);
+#pragma unroll
+            for (int k = 0; k < N; ++k)
+                gc[k][t] = gt * (exp2f((v[k] - m) * bl) / s0) * (1.f + beta * (v[k] - r));
+        } else {
+            const float o = sg * out[t];
+#pragma unroll
+            for (int k = 0; k < N; ++k) gc[k][t] = gt * exp2f((v[k] - o) * bl);
         }
     }
 }
 
 DEV void op_nary_bwd(const Env& e, const Instr& I)
 {
-    const float sg = (I.flags & F_MIN) ? -1.f : 1.f;
-    const int n = I.nch;
-    const float* g = slot(e, I.g_out);
-    const float* out = slot(e, I.b_out);
-    const float* c[MAX_NCH];
-    float* gc[MAX_NCH];
-    for (int k = 0; k < MAX_NCH; ++k) {
-        c[k] = slot(e, I.b_ch[k < n ? k : 0]);
-        gc[k] = slot(e, I.g_ch[k < n ? k : 0]);
-    }
-    const bool smooth = I.flags & F_SMOOTH;
-    const float bl = pbeta(e, I) * LOG2E;
-    for (int t = threadIdx.x; t < e.L; t += blockDim.x) {
-        const float gt = g[t];
-        if (!smooth) {
-            int kb = 0;
-            float best = sg * c[0][t];
-            for (int k = 1; k < n; ++k) {
-                float v = sg * c[k][t];
-                if (v > best) { best = v; kb = k; }
-            }
-            for (int k = 0; k < n; ++k) gc[k][t] = (k == kb) ? gt : 0.f;
-        } else if (I.flags & F_SOFT) {
-            // d r / d v_k = p_k (1 + beta (v_k - r)), r = sg out
-            const float r = sg * out[t], beta = bl / LOG2E;
-            float v[MAX_NCH];
-            float m = -INFINITY;
-            for (int k = 0; k < n; ++k) { v[k] = sg * c[k][t]; m = fmaxf(m, v[k]); }
-            float s0 = 0.f;
-            for (int k = 0; k < n; ++k) s0 += exp2f((v[k] - m) * bl);
-            for (int k = 0; k < n; ++k)
-                gc[k][t] = gt * (exp2f((v[k] - m) * bl) / s0) * (1.f + beta * (v[k] - r));
-        } else {
-            const float o = sg * out[t];
-            for (int k = 0; k < n; ++k) gc[k][t] = gt * exp2f((sg * c[k][t] - o) * bl);
-        }
+    switch (I.nch) {
+    case 1: nary_bwd<1>(e, I); break;
+    case 2: nary_bwd<2>(e, I); break;
+    case 3: nary_bwd<3>(e, I); break;
+    default: nary_bwd<4>(e, I); break;
     }
 }
 
@@ -426,24 +639,18 @@ DEV void win_hard(const Env& e, const float* u, float* out, int* jstar, float sg
     const bool unb = khi < 0;
     const int n = L - klo;
     const int K = unb ? n : khi - klo + 1;
-    if (n > 0) {
-        for (int i = threadIdx.x; i < n; i += blockDim.x) {
-            VI v{sg * u[klo + i], klo + i};
-            Suf[i] = v;
-            if (!unb) Pre[i] = v;
-        }
-        __syncthreads();
-        const VI id{-INFINITY, 0x7fffffff};
-        seg_scan(Suf, n, unb ? 0 : K, true, id, OpVI(), *e.sh);
-        if (!unb) seg_scan(Pre, n, K, false, id, OpVI(), *e.sh);
-    }
+    const float inv = 1.f / (float)K;
+    if (n > 0)
+        scan_blocks(Pre, Suf, n, unb ? 0 : K, VI{-INFINITY, 0x7fffffff}, OpVI(),
+                    [&](int i) { return VI{sg * u[klo + i], klo + i}; }, e);
     const float rho_pad = e.P->rho_pad;
-    for (int t = threadIdx.x; t < L; t += blockDim.x) {
+    for (int t = threadIdx.x; t < L; t += e.nt) {
         VI r{-INFINITY, L};
         bool any = false;
         if (t < n) {
-            int e2 = min(t + K - 1, n - 1);
-            r = (unb || t / K == e2 / K) ? Suf[t] : vi_best(Suf[t], Pre[e2]);
+            const int e2 = min(t + K - 1, n - 1);
+            bool st;
+            r = (unb || one_block(t, e2, K, inv, st)) ? Suf[t] : vi_best(Suf[t], Pre[e2]);
             any = true;
         }
         if (!unb && pad != PAD_NEUTRAL && t + khi > L - 1) {
@@ -463,19 +670,17 @@ DEV void win_hard(const Env& e, const float* u, float* out, int* jstar, float sg
 
 // adjoint of a hard window: gu[j] = sum of g[t] over the t whose selected
 // index is j.  The selected index is non-decreasing in t, so each j owns a
-// contiguous run of t, found by binary search; the run sum comes from an
-// fp64 prefix sum of g (exact to fp32 rounding, deterministic).
+// contiguous run of t: an fp64 segmented sum of g leaves the run's total (exact
+// to fp32 rounding, deterministic) at the run's last t.
 DEV void win_hard_adj(const Env& e, const float* g, float* gu, const int* jstar, double* P)
 {
     const int L = e.L;
-    for (int t = threadIdx.x; t < L; t += blockDim.x) P[t + 1] = jstar[t] < L ? (double)g[t] : 0.0;
-    if (threadIdx.x == 0) P[0] = 0.0;
-    __syncthreads();
-    seg_scan(P + 1, L, 0, false, 0.0, OpD(), *e.sh);
-    for (int j = threadIdx.x; j < L; j += blockDim.x) {
-        int lo = lower_bound_i(jstar, L, j);
-        int hi = lower_bound_i(jstar, L, j + 1);
-        gu[j] = (float)(P[hi] - P[lo]);
+    for (int j = threadIdx.x; j < L; j += e.nt) gu[j] = 0.f;
+    scan_one<false>(P, L, 0.0, OpD(), [&](int t) { return (double)g[t]; },
+                    [&](int t) { return t == 0 || jstar[t] != jstar[t - 1]; }, e);
+    for (int t = threadIdx.x; t < L; t += e.nt) {
+        const int j = jstar[t];
+        if (j < L && (t == L - 1 || jstar[t + 1] != j)) gu[j] = (float)P[t];
     }
     __syncthreads();
 }
@@ -493,21 +698,16 @@ DEV void win_smooth_sum(const Env& e, const float* u, SP* acc, float sgz, int kl
     const bool unb = khi < 0;
     const int n = L - klo;
     const int K = unb ? n : khi - klo + 1;
-    if (n > 0) {
-        for (int i = threadIdx.x; i < n; i += blockDim.x) {
-            SP v = sp_leaf(sgz * u[klo + i]);
-            Suf[i] = v;
-            if (!unb) Pre[i] = v;
-        }
-        __syncthreads();
-        seg_scan(Suf, n, unb ? 0 : K, true, sp_zero(), OpSP(), *e.sh);
-        if (!unb) seg_scan(Pre, n, K, false, sp_zero(), OpSP(), *e.sh);
-    }
-    for (int t = threadIdx.x; t < L; t += blockDim.x) {
+    const float inv = 1.f / (float)K;
+    if (n > 0)
+        scan_blocks(Pre, Suf, n, unb ? 0 : K, sp_zero(), OpSP(), [&](int i) { return sp_leaf(sgz * u[klo + i]); },
+                    e);
+    for (int t = threadIdx.x; t < L; t += e.nt) {
         SP a = sp_zero();
         if (t < n) {
-            int e2 = min(t + K - 1, n - 1);
-            a = (unb || t / K == e2 / K) ? Suf[t] : sp_add(Suf[t], Pre[e2]);
+            const int e2 = min(t + K - 1, n - 1);
+            bool st;
+            a = (unb || one_block(t, e2, K, inv, st)) ? Suf[t] : sp_add(Suf[t], Pre[e2]);
         }
         if (!unb && pad != PAD_NEUTRAL && t + khi > L - 1) {
             int np = min(K, t + khi - (L - 1));
@@ -520,9 +720,6 @@ DEV void win_smooth_sum(const Env& e, const float* u, SP* acc, float sgz, int kl
     __syncthreads();
 }
 
-// Transposed window sum for adjoints: for each position j,
-// out[j] = sum over t in [j-khi, j-klo] (clipped to [0, nt_valid)) of h[t].
-// h (scaled pairs) is consumed (overwritten by the scans).
 // Window sums of u_j 2^{sgz u_j} (signed scaled pairs) over [t+klo, t+khi]
 // (khi < 0: to the end), NEUTRAL pad: the numerator of the softmax-weighted
 // mean whose denominator win_smooth_sum gives.
@@ -532,22 +729,21 @@ DEV void win_smooth_sum_w(const Env& e, const float* u, SP* acc, float sgz, int 
     const bool unb = khi < 0;
     const int n = L - klo;
     const int K = unb ? n : khi - klo + 1;
-    if (n > 0) {
-        for (int i = threadIdx.x; i < n; i += blockDim.x) {
-            SP v = sp_leaf(sgz * u[klo + i]);
-            v.s *= u[klo + i];
-            Suf[i] = v;
-            if (!unb) Pre[i] = v;
-        }
-        __syncthreads();
-        seg_scan(Suf, n, unb ? 0 : K, true, sp_zero(), OpSP(), *e.sh);
-        if (!unb) seg_scan(Pre, n, K, false, sp_zero(), OpSP(), *e.sh);
-    }
-    for (int t = threadIdx.x; t < L; t += blockDim.x) {
+    const float inv = 1.f / (float)K;
+    if (n > 0)
+        scan_blocks(Pre, Suf, n, unb ? 0 : K, sp_zero(), OpSP(),
+                    [&](int i) {
+                        SP v = sp_leaf(sgz * u[klo + i]);
+                        v.s *= u[klo + i];
+                        return v;
+                    },
+                    e);
+    for (int t = threadIdx.x; t < L; t += e.nt) {
         SP a = sp_zero();
         if (t < n) {
-            int e2 = min(t + K - 1, n - 1);
-            a = (unb || t / K == e2 / K) ? Suf[t] : sp_add(Suf[t], Pre[e2]);
+            const int e2 = min(t + K - 1, n - 1);
+            bool st;
+            a = (unb || one_block(t, e2, K, inv, st)) ? Suf[t] : sp_add(Suf[t], Pre[e2]);
         }
         acc[t] = a;
     }
@@ -560,23 +756,26 @@ DEV float sp_ratio(SP num, SP den)
     return ldexpf(num.s / den.s, clampe((long long)num.r - den.r));
 }
 
-DEV void win_smooth_adj_sum(const Env& e, SP* h, SP* hPre, SP* res, int klo, int khi, int n_valid)
+// Transposed window sum for adjoints: for each position j, res[j] = sum over
+// t in [j-khi, j-klo] (clipped to [0, n_valid)) of h(t).
+template <class Leaf>
+DEV void win_smooth_adj_sum(const Env& e, Leaf h, SP* hSuf, SP* hPre, SP* res, int klo, int khi, int n_valid)
 {
     const int L = e.L;
     const bool unb = khi < 0;
     const int K = unb ? L : khi - klo + 1;
-    for (int t = threadIdx.x; t < L; t += blockDim.x) hPre[t] = h[t];
-    __syncthreads();
-    seg_scan(hPre, L, unb ? 0 : K, false, sp_zero(), OpSP(), *e.sh);
-    if (!unb) seg_scan(h, L, K, true, sp_zero(), OpSP(), *e.sh);
-    for (int j = threadIdx.x; j < L; j += blockDim.x) {
+    const float inv = 1.f / (float)K;
+    if (unb) scan_one<false>(hPre, L, sp_zero(), OpSP(), h, HeadUp(0, L), e);
+    else scan_blocks(hPre, hSuf, L, K, sp_zero(), OpSP(), h, e);
+    for (int j = threadIdx.x; j < L; j += e.nt) {
         SP a = sp_zero();
-        int en = min(j - klo, n_valid - 1);
-        int st = unb ? 0 : max(0, j - khi);
+        const int en = min(j - klo, n_valid - 1);
+        const int st = unb ? 0 : max(0, j - khi);
         if (st <= en) {
+            bool at_start;
             if (unb) a = hPre[en];
-            else if (st / K == en / K) a = (st % K == 0) ? hPre[en] : h[st];
-            else a = sp_add(h[st], hPre[en]);
+            else if (one_block(st, en, K, inv, at_start)) a = at_start ? hPre[en] : hSuf[st];
+            else a = sp_add(hSuf[st], hPre[en]);
         }
         res[j] = a;
     }
@@ -697,7 +896,7 @@ DEV int wave_imax(int v)
 // Weights for k in [0, L) (stored when w != NULL), the support {w > 0} and
 // the core.  Without stored weights only the support's window is searched.
 template <class SH>
-DEV MaskInfo mask_info(const float* params, const Instr& I, int L, SH& sh, float* w, float* dwa, float* dwb)
+DEV MaskInfo mask_info(const float* params, const Instr& I, int L, SH& sh, int nt, float* w, float* dwa, float* dwb)
 {
     const MaskP mp = mask_params(params + I.mask, I.flags & F_MASK_UNB);
     int* si = sh.ints;
@@ -706,7 +905,7 @@ DEV MaskInfo mask_info(const float* params, const Instr& I, int L, SH& sh, float
     int lo = L, hi = -1;
     int k0 = 0, k1 = L - 1;
     if (!w && !dwa) mask_window(mp, L, k0, k1);
-    for (int k = k0 + (int)threadIdx.x; k <= k1; k += blockDim.x) {
+    for (int k = k0 + (int)threadIdx.x; k <= k1; k += nt) {
         float da, db;
         const float wk = mask_wk(mp, k, dwa ? &da : nullptr, &db);
         if (w) w[k] = wk;
@@ -731,22 +930,7 @@ DEV float mask_padv(const Instr& I) { return __int_as_float(I.a); }
 
 DEV MaskInfo mask_weights(const Env& e, const Instr& I, float* w, float* dwa, float* dwb)
 {
-    return mask_info(e.params, I, e.L, *e.sh, w, dwa, dwb);
-}
-
-// deterministic work-group sum of one double per thread
-DEV double wg_sum_d(double v, Shared& sh)
-{
-    const int tid = threadIdx.x, nt = blockDim.x;
-    sh.scan[tid] = v;
-    __syncthreads();
-    for (int s = nt >> 1; s > 0; s >>= 1) {
-        if (tid < s) sh.scan[tid] += sh.scan[tid + s];
-        __syncthreads();
-    }
-    const double r = sh.scan[0];
-    __syncthreads();
-    return r;
+    return mask_info(e.params, I, e.L, *e.sh, e.nt, w, dwa, dwb);
 }
 
 // Offsets past the signal end, for the LAST / CONST pads of a bounded smooth
@@ -777,7 +961,7 @@ DEV MaskTail mask_tail(const Env& e, const Instr& I, bool grads)
     __syncthreads();
     int lo = INT_MAX, hi = -1;
     double s = 0.0, sa = 0.0, sb = 0.0;
-    for (int k = L + (int)threadIdx.x; k <= kend; k += blockDim.x) {
+    for (int k = L + (int)threadIdx.x; k <= kend; k += e.nt) {
         float da = 0.f, db = 0.f;
         const float wk = mask_wk(mp, k, grads ? &da : nullptr, &db);
         if (wk > 0.f) {
@@ -794,9 +978,9 @@ DEV MaskTail mask_tail(const Env& e, const Instr& I, bool grads)
     MaskTail mt;
     mt.lo = si[5];
     mt.hi = si[6];
-    mt.s = wg_sum_d(s, *e.sh);
-    mt.sa = grads ? wg_sum_d(sa, *e.sh) : 0.0;
-    mt.sb = grads ? wg_sum_d(sb, *e.sh) : 0.0;
+    mt.s = wg_sum(s, e);
+    mt.sa = grads ? wg_sum(sa, e) : 0.0;
+    mt.sb = grads ? wg_sum(sb, e) : 0.0;
     return mt;
 }
 
@@ -805,9 +989,10 @@ DEV MaskTail mask_tail(const Env& e, const Instr& I, bool grads)
 // end for the output at t, plus the tail beyond the table.  fp64 sums: one
 // contiguous chunk per thread, an exclusive suffix scan over the lanes and
 // the totals of the later waves.
-DEV void tail_weights(const float* v, float* out, int L, double tail, Shared& sh)
+DEV void tail_weights(const float* v, float* out, int L, double tail, const Env& e)
 {
-    const int nt = blockDim.x, tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
+    Shared& sh = *e.sh;
+    const int nt = e.nt, tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
     const int nw = (nt + 63) >> 6;
     const int ch = (L + nt - 1) / nt;
     const int k0 = min(L, tid * ch), k1 = min(L, k0 + ch);
@@ -846,7 +1031,7 @@ DEV void until_hard(const Env& e, int a, int b, const float* phi, const float* p
 {
     const int L = e.L;
     const float rho_pad = e.P->rho_pad;
-    for (int t = threadIdx.x; t < L; t += blockDim.x) {
+    for (int t = threadIdx.x; t < L; t += e.nt) {
         const int imax = b < 0 ? L - 1 - t : min(b, L - 1 - t);
         if (a > imax) {
             if (out) out[t] = -rho_pad;
@@ -871,7 +1056,7 @@ DEV void until_hard(const Env& e, int a, int b, const float* phi, const float* p
     }
     if (!g) return;
     __syncthreads();
-    for (int j = threadIdx.x; j < L; j += blockDim.x) {
+    for (int j = threadIdx.x; j < L; j += e.nt) {
         float sp = 0.f, sq = 0.f;
         for (int t = b < 0 ? 0 : max(0, j - b); t <= j; ++t) {
             const int c = code[t];
@@ -927,11 +1112,11 @@ DEV void until_hard_unb(const Env& e, int a, const float* phi, const float* psi,
     int* jA = (int*)S(e, 5);
     ClampMap* cm = (ClampMap*)S(e, 6);      // units 6, 7
     if (a > 0) win_hard(e, phi, mA, jA, -1.f, 0, a - 1, PAD_NEUTRAL, 0.f, (VI*)S(e, 0), (VI*)S(e, 2));
-    for (int s = threadIdx.x; s < L; s += blockDim.x) cm[s] = ClampMap{phi[s] <= psi[s] ? phi[s] : psi[s], phi[s]};
-    __syncthreads();
-    seg_scan(cm, L, 0, true, ClampMap{-INFINITY, INFINITY}, OpClamp(), *e.sh);     // cm[s].lo = U(s)
+    scan_one<true>(cm, L, ClampMap{-INFINITY, INFINITY}, OpClamp(),
+                   [&](int s) { return ClampMap{phi[s] <= psi[s] ? phi[s] : psi[s], phi[s]}; }, HeadDown(0, L),
+                   e);                                                         // cm[s].lo = U(s)
     if (!g) {
-        for (int t = threadIdx.x; t < L; t += blockDim.x) {
+        for (int t = threadIdx.x; t < L; t += e.nt) {
             float v = -rho_pad;
             if (t + a <= L - 1) {
                 const float u = cm[t + a].lo;
@@ -945,7 +1130,7 @@ DEV void until_hard_unb(const Env& e, int a, const float* phi, const float* psi,
     int* code = (int*)S(e, 8);
     Affine* fa = (Affine*)S(e, 9);          // units 9, 10
     float* gw = S(e, 11);                   // adjoint sent to the window argmin of m_a
-    for (int s = threadIdx.x; s < L; s += blockDim.x) {
+    for (int s = threadIdx.x; s < L; s += e.nt) {
         const float un = s + 1 < L ? cm[s + 1].lo : -INFINITY;
         int c = UH_PHI;
         if (!(phi[s] <= psi[s])) {
@@ -963,14 +1148,14 @@ DEV void until_hard_unb(const Env& e, int a, const float* phi, const float* psi,
         gw[s] = win ? gt : 0.f;
     }
     __syncthreads();
-    for (int s = threadIdx.x; s < L; s += blockDim.x) {
-        const int t = s - a;
-        const float h = (t >= 0 && !(a > 0 && mA[t] <= cm[s].lo)) ? g[t] : 0.f;
-        fa[s] = Affine{h, s > 0 && code[s - 1] == UH_PASS ? 1 : 0};
-    }
-    __syncthreads();
-    seg_scan(fa, L, 0, false, Affine{0.f, 1}, OpAffine(), *e.sh);                 // fa[s].h = F(s)
-    for (int s = threadIdx.x; s < L; s += blockDim.x) {
+    scan_one<false>(fa, L, Affine{0.f, 1}, OpAffine(),
+                    [&](int s) {
+                        const int t = s - a;
+                        const float h = (t >= 0 && !(a > 0 && mA[t] <= cm[s].lo)) ? g[t] : 0.f;
+                        return Affine{h, s > 0 && code[s - 1] == UH_PASS ? 1 : 0};
+                    },
+                    HeadUp(0, L), e);                                         // fa[s].h = F(s)
+    for (int s = threadIdx.x; s < L; s += e.nt) {
         if (code[s] == UH_PHI) gphi[s] += fa[s].h;
         else if (code[s] == UH_PSI) gpsi[s] += fa[s].h;
     }
@@ -978,7 +1163,7 @@ DEV void until_hard_unb(const Env& e, int a, const float* phi, const float* psi,
     if (a > 0) {
         float* gu = S(e, 15);
         win_hard_adj(e, gw, gu, jA, (double*)S(e, 12));                          // units 12..14
-        for (int j = threadIdx.x; j < L; j += blockDim.x) gphi[j] += gu[j];
+        for (int j = threadIdx.x; j < L; j += e.nt) gphi[j] += gu[j];
         __syncthreads();
     }
 }
@@ -994,7 +1179,7 @@ DEV void until_smooth_fwd(const Env& e, int a, int b, const float* w, const SP* 
 {
     const int L = e.L;
     const float rho_pad = e.P->rho_pad;
-    for (int t = threadIdx.x; t < L; t += blockDim.x) {
+    for (int t = threadIdx.x; t < L; t += e.nt) {
         const int imax = b < 0 ? L - 1 - t : min(b, L - 1 - t);
         if (a > imax) { out[t] = -rho_pad; continue; }
         SP P = sp_zero(), Z = sp_zero();
@@ -1020,8 +1205,8 @@ constexpr int UCK_UNIT = 7;   // scratch unit where its checkpoints start (units
 // checkpoint blocks backward, recomputing P inside each block.  The float
 // contributions go through the lane-shifted accumulators of lane_stage
 // (defined below), in the same fixed order as the fp64 adjoint.
-DEV void lane_stage_f(int i, int tb, int lane, int L, float& accp, float& accq, float& stp, float& stq,
-                      float* gphi, float* gpsi);
+DEV void lane_stage(int i, int tb, int lane, int L, float& accp, float& accq, float& stp, float& stq,
+                    float* gphi, float* gpsi);
 
 DEV void until_smooth_adj(const Env& e, int a, int b, const float* w, const float* dwa, const float* dwb,
                           const SP* Ephi, const SP* Epsi, const float* g, float* gphi, float* gpsi, SP* ck,
@@ -1029,7 +1214,7 @@ DEV void until_smooth_adj(const Env& e, int a, int b, const float* w, const floa
 {
     const int L = e.L;
     const int lane = threadIdx.x & 63;
-    for (int base = 0; base < L; base += blockDim.x) {
+    for (int base = 0; base < L; base += e.nt) {
         const int tb = base + (int)threadIdx.x - lane;
         const int t = tb + lane;
         const int imax = t >= L ? -1 : (b < 0 ? L - 1 - t : min(b, L - 1 - t));
@@ -1084,7 +1269,7 @@ DEV void until_smooth_adj(const Env& e, int a, int b, const float* w, const floa
                     const SP E = Ephi[t + i];
                     accp += ldexpf(gz * A.s * E.s, clampe((long long)A.r + E.r - Z.r));
                 }
-                if (i > 0) lane_stage_f(i, tb, lane, L, accp, accq, stp, stq, gphi, gpsi);
+                if (i > 0) lane_stage(i, tb, lane, L, accp, accq, stp, stq, gphi, gpsi);
             }
         }
         if (wblk > 0 && t < L) {
@@ -1131,10 +1316,11 @@ DEV double log2_minus(double z, int M)
 
 // Reference exponent M of the two leaf traces; false when the fp64 form
 // cannot hold them.
-DEV bool until_ref(const float* phi, const float* psi, int L, float bl, Shared& sh, int& M)
+DEV bool until_ref(const float* phi, const float* psi, int L, float bl, const Env& e, int& M)
 {
+    Shared& sh = *e.sh;
     int hi = INT_MIN, lo = INT_MAX, bad = 0;
-    for (int j = threadIdx.x; j < L; j += blockDim.x) {
+    for (int j = threadIdx.x; j < L; j += e.nt) {
         const float u1 = -bl * phi[j], u2 = -bl * psi[j];
         if (!(fabsf(u1) < 1e9f) || !(fabsf(u2) < 1e9f)) {
             bad = 1;                                 // also catches NaN
@@ -1160,29 +1346,20 @@ DEV bool until_ref(const float* phi, const float* psi, int L, float bl, Shared& 
 }
 
 // leaf terms of both inputs as doubles 2^{u - M} (Ep, Eq)
-DEV void until_terms(const float* phi, const float* psi, int L, float bl, int M, double* Ep, double* Eq)
+DEV void until_terms(const float* phi, const float* psi, int L, float bl, int M, double* Ep, double* Eq, int nt)
 {
-    for (int j = threadIdx.x; j < L; j += blockDim.x) {
+    for (int j = threadIdx.x; j < L; j += nt) {
         Ep[j] = uterm(-bl * phi[j], M);
         Eq[j] = uterm(-bl * psi[j], M);
     }
     __syncthreads();
 }
 
-typedef __attribute__((address_space(3))) double lds_double;
-typedef __attribute__((address_space(3))) float lds_float;
-
-// true when p points into the work-group's LDS (the arena placement is chosen per launch)
-DEV bool in_lds(const void* p)
-{
-    return __builtin_amdgcn_is_shared((const __attribute__((address_space(0))) void*)p);
-}
-
 // Z = sum_{i=a}^{imax} 1 / (P_i + q_i), P_i = sum_{k<=i} p_k, over the terms of
 // one output.  The terms are read eight at a time (independent loads ahead of
 // the dependent sums); the additions keep the plain sequential order.
-template <bool MW, class DP>
-DEV double until_z(DP ep, DP eq, int a, int imax, const float* w)
+template <bool MW>
+DEV double until_z(const double* ep, const double* eq, int a, int imax, const float* w)
 {
     double P = 0.0, Z = 0.0;
     int i = 0;
@@ -1218,13 +1395,13 @@ DEV double until_z(DP ep, DP eq, int a, int imax, const float* w)
 
 // Forward on the fp64 terms: the same sums as until_smooth_fwd, with
 // Y_i = 2^{-M} / (P_i + Q_i) in true units, so log2 Z_true = log2 Z - M.
-template <bool MW, class DP>
-DEV void until_fwd_d(const Env& e, int a, int b, const float* w, DP Ep, DP Eq, float* out, double* zs, float bl,
-                     int M)
+template <bool MW>
+DEV void until_fwd_d(const Env& e, int a, int b, const float* w, const double* Ep, const double* Eq, float* out,
+                     double* zs, float bl, int M)
 {
     const int L = e.L;
     const float rho_pad = e.P->rho_pad;
-    for (int t = threadIdx.x; t < L; t += blockDim.x) {
+    for (int t = threadIdx.x; t < L; t += e.nt) {
         const int imax = b < 0 ? L - 1 - t : min(b, L - 1 - t);
         if (a > imax) { out[t] = -rho_pad; continue; }
         const double Z = until_z<MW>(Ep + t, Eq + t, a, imax, w);
@@ -1245,9 +1422,8 @@ DEV float lane_shr1(float v)
 // s = i - 1; it is parked in lane s % 64 of the staging pair, and a full
 // stage (s a multiple of 64: positions tb + 64 + s + lane) is added to the
 // adjoint slots, followed by a barrier.  Then the accumulators move up a lane.
-template <class FP>
-DEV void lane_stage(int i, int tb, int lane, int L, float& accp, float& accq, float& stp, float& stq, FP gphi,
-                    FP gpsi)
+DEV void lane_stage(int i, int tb, int lane, int L, float& accp, float& accq, float& stp, float& stq, float* gphi,
+                    float* gpsi)
 {
     const int s_ = i - 1, j = s_ & 63;
     const float dp = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(accp), 63));
@@ -1270,12 +1446,6 @@ DEV void lane_stage(int i, int tb, int lane, int L, float& accp, float& accq, fl
     accq = lane_shr1(accq);
 }
 
-DEV void lane_stage_f(int i, int tb, int lane, int L, float& accp, float& accq, float& stp, float& stq,
-                      float* gphi, float* gpsi)
-{
-    lane_stage<float*>(i, tb, lane, L, accp, accq, stp, stq, gphi, gpsi);
-}
-
 // Adjoint on the fp64 terms (the derivatives are ratios of terms, so the
 // reference cancels).  Z_t comes from the forward recompute (zs); a forward
 // sweep of additions keeps P every UCK steps; the reverse sweep rebuilds each
@@ -1294,23 +1464,23 @@ DEV void lane_stage_f(int i, int tb, int lane, int L, float& accp, float& accq, 
 // With smooth mask weights (MW) each term carries w_i: Z = sum w_i Y_i, A
 // sums w_i Y_i^2, and d out / d w_i = Y_i / (beta Z) is summed against
 // d w/da, d w/db into pa, pb (per thread, before the division by beta).
-template <bool MW, class DP, class CP, class FP>
-DEV void until_adj_d(const Env& e, int a, int b, const float* w, const float* dwa, const float* dwb, DP Ep,
-                     DP Eq, const double* zs, const float* g, FP gphi, FP gpsi, CP ck, int ncks, float& pa,
-                     float& pb)
+template <bool MW>
+DEV void until_adj_d(const Env& e, int a, int b, const float* w, const float* dwa, const float* dwb,
+                     const double* Ep, const double* Eq, const double* zs, const float* g, float* gphi, float* gpsi,
+                     double* ck, int ncks, float& pa, float& pb)
 {
     const int L = e.L;
     const int lane = threadIdx.x & 63;
-    for (int base = 0; base < L; base += blockDim.x) {
+    for (int base = 0; base < L; base += e.nt) {
         const int tb = base + (int)threadIdx.x - lane;
         const int t = tb + lane;
         const int imax = t >= L ? -1 : (b < 0 ? L - 1 - t : min(b, L - 1 - t));
         const float gt = t < L ? g[t] : 0.f;
         const bool act = a <= imax && gt != 0.f;
         const int nblk = act ? imax / UCK + 1 : 0;
-        const DP ep = Ep + t;
-        const DP eq = Eq + t;
-        const CP myck = ck + (size_t)threadIdx.x * ncks;
+        const double* ep = Ep + t;
+        const double* eq = Eq + t;
+        double* myck = ck + (size_t)threadIdx.x * ncks;
         double Z = 1.0;
         if (act) {
             // Z comes from the forward recompute: only the block-start prefixes of P
@@ -1381,39 +1551,19 @@ DEV void until_adj_d(const Env& e, int a, int b, const float* w, const float* dw
     }
 }
 
-DEV void until_smooth_fwd_d(const Env& e, int a, int b, const float* w, double* Ep, double* Eq, float* out,
+DEV void until_smooth_fwd_d(const Env& e, int a, int b, const float* w, const double* Ep, const double* Eq, float* out,
                             double* zs, float bl, int M)
 {
-    if (w) {
-        if (in_lds(Ep))
-            until_fwd_d<true>(e, a, b, w, (const lds_double*)Ep, (const lds_double*)Eq, out, zs, bl, M);
-        else
-            until_fwd_d<true>(e, a, b, w, (const double*)Ep, (const double*)Eq, out, zs, bl, M);
-    } else if (in_lds(Ep)) {
-        until_fwd_d<false>(e, a, b, w, (const lds_double*)Ep, (const lds_double*)Eq, out, zs, bl, M);
-    } else {
-        until_fwd_d<false>(e, a, b, w, (const double*)Ep, (const double*)Eq, out, zs, bl, M);
-    }
+    if (w) until_fwd_d<true>(e, a, b, w, Ep, Eq, out, zs, bl, M);
+    else until_fwd_d<false>(e, a, b, w, Ep, Eq, out, zs, bl, M);
 }
 
 DEV void until_smooth_adj_d(const Env& e, int a, int b, const float* w, const float* dwa, const float* dwb,
-                            double* Ep, double* Eq, const double* zs, const float* g, float* gphi, float* gpsi,
-                            double* ck, int ncks, float& pa, float& pb)
+                            const double* Ep, const double* Eq, const double* zs, const float* g, float* gphi,
+                            float* gpsi, double* ck, int ncks, float& pa, float& pb)
 {
-    if (w) {
-        if (in_lds(Ep))
-            until_adj_d<true>(e, a, b, w, dwa, dwb, (const lds_double*)Ep, (const lds_double*)Eq, zs, g,
-                              (lds_float*)gphi, (lds_float*)gpsi, (lds_double*)ck, ncks, pa, pb);
-        else
-            until_adj_d<true>(e, a, b, w, dwa, dwb, (const double*)Ep, (const double*)Eq, zs, g, gphi, gpsi, ck,
-                              ncks, pa, pb);
-    } else if (in_lds(Ep)) {
-        until_adj_d<false>(e, a, b, w, dwa, dwb, (const lds_double*)Ep, (const lds_double*)Eq, zs, g,
-                           (lds_float*)gphi, (lds_float*)gpsi, (lds_double*)ck, ncks, pa, pb);
-    } else {
-        until_adj_d<false>(e, a, b, w, dwa, dwb, (const double*)Ep, (const double*)Eq, zs, g, gphi, gpsi, ck, ncks,
-                           pa, pb);
-    }
+    if (w) until_adj_d<true>(e, a, b, w, dwa, dwb, Ep, Eq, zs, g, gphi, gpsi, ck, ncks, pa, pb);
+    else until_adj_d<false>(e, a, b, w, dwa, dwb, Ep, Eq, zs, g, gphi, gpsi, ck, ncks, pa, pb);
 }
 
 // ------------------------------------------------------------------ instructions
@@ -1431,15 +1581,14 @@ DEV void exec_fwd(const Env& e, const Instr& I, bool bwdmap)
     const float sg = (I.flags & F_MIN) ? -1.f : 1.f;
     switch (I.kind) {
     case K_TRUE:
-        for (int t = threadIdx.x; t < L; t += blockDim.x) out[t] = e.P->rho_max;
+        for (int t = threadIdx.x; t < L; t += e.nt) out[t] = e.P->rho_max;
         break;
     case K_LIN:
     case K_NORM:
-        op_pred_fwd(e, I, out);
-        break;
+        break;          // op_preds, before the first instruction
     case K_NOT: {
         const float* u = slot(e, i0);
-        for (int t = threadIdx.x; t < L; t += blockDim.x) out[t] = -u[t];
+        for (int t = threadIdx.x; t < L; t += e.nt) out[t] = -u[t];
         break;
     }
     case K_NARY:
@@ -1460,7 +1609,7 @@ DEV void exec_fwd(const Env& e, const Instr& I, bool bwdmap)
             win_smooth_sum(e, u, den, sg * bl, I.a, khi, I.pad, padv, (SP*)S(e, 0), (SP*)S(e, 2));
             win_smooth_sum_w(e, u, num, sg * bl, I.a, khi, (SP*)S(e, 0), (SP*)S(e, 2));
             const float v = I.pad == PAD_LAST ? u[L - 1] : padv;
-            for (int t = threadIdx.x; t < L; t += blockDim.x) {
+            for (int t = threadIdx.x; t < L; t += e.nt) {
                 SP nm = num[t];
                 const bool padded = khi >= 0 && I.pad != PAD_NEUTRAL && t + khi > L - 1;
                 if (padded) {
@@ -1476,7 +1625,7 @@ DEV void exec_fwd(const Env& e, const Instr& I, bool bwdmap)
             SP* acc = (SP*)S(e, 4);
             win_smooth_sum(e, u, acc, sg * bl, I.a, khi, I.pad, padv, (SP*)S(e, 0), (SP*)S(e, 2));
             const bool unb = khi < 0;
-            for (int t = threadIdx.x; t < L; t += blockDim.x) {
+            for (int t = threadIdx.x; t < L; t += e.nt) {
                 const bool any = (t + I.a <= L - 1) || (!unb && I.pad != PAD_NEUTRAL && t + khi > L - 1);
                 out[t] = any ? sg * sp_log2(acc[t]) / bl : -sg * e.P->rho_pad;
             }
@@ -1497,7 +1646,7 @@ DEV void exec_fwd(const Env& e, const Instr& I, bool bwdmap)
         const float padv = mask_padv(I);
         if (!is_smooth(I)) {
             if (!anyk) {
-                for (int t = threadIdx.x; t < L; t += blockDim.x) out[t] = -sg * e.P->rho_pad;
+                for (int t = threadIdx.x; t < L; t += e.nt) out[t] = -sg * e.P->rho_pad;
             } else {
                 const int kh = ((I.flags & F_MASK_UNB) && khi == L - 1) ? -1 : khi;
                 win_hard(e, u, out, nullptr, sg, klo, kh, padm ? I.pad : PAD_NEUTRAL, padv, (VI*)S(e, 0),
@@ -1514,11 +1663,11 @@ DEV void exec_fwd(const Env& e, const Instr& I, bool bwdmap)
             const int kh = ((I.flags & F_MASK_UNB) && mi.chi == L - 1) ? -1 : mi.chi;
             win_smooth_sum(e, u, acc, sg * bl, mi.clo, kh, PAD_NEUTRAL, 0.f, (SP*)S(e, 0), (SP*)S(e, 2));
         }
-        for (int j = threadIdx.x; j < L; j += blockDim.x) E[j] = sp_leaf(sg * bl * u[j]);
-        if (padm) tail_weights(w, TW, L, mt.s, *e.sh);
+        for (int j = threadIdx.x; j < L; j += e.nt) E[j] = sp_leaf(sg * bl * u[j]);
+        if (padm) tail_weights(w, TW, L, mt.s, e);
         __syncthreads();
         const SP Ev = sp_leaf(sg * bl * (I.pad == PAD_LAST ? u[L - 1] : padv));
-        for (int t = threadIdx.x; t < L; t += blockDim.x) {
+        for (int t = threadIdx.x; t < L; t += e.nt) {
             // band terms are summed one by one (up to a few hundred of them):
             // accumulate with a double mantissa so the error does not grow with the count
             SPD a{0.0, SP_NEG};
@@ -1546,7 +1695,7 @@ DEV void exec_fwd(const Env& e, const Instr& I, bool bwdmap)
             float* wt = S(e, 4);
             const MaskInfo mi = mask_weights(e, I, wt, nullptr, nullptr);
             if (!mi.any) {
-                for (int t = threadIdx.x; t < L; t += blockDim.x) out[t] = -e.P->rho_pad;
+                for (int t = threadIdx.x; t < L; t += e.nt) out[t] = -e.P->rho_pad;
                 break;
             }
             ua = mi.klo;
@@ -1559,10 +1708,10 @@ DEV void exec_fwd(const Env& e, const Instr& I, bool bwdmap)
         } else {
             const float bl = pbeta(e, I) * LOG2E;
             int M;
-            if (until_ref(phi, psi, L, bl, *e.sh, M)) {
+            if (until_ref(phi, psi, L, bl, e, M)) {
                 double* Ep = (double*)S(e, 0);
                 double* Eq = (double*)S(e, 2);
-                until_terms(phi, psi, L, bl, M, Ep, Eq);
+                until_terms(phi, psi, L, bl, M, Ep, Eq, e.nt);
                 // the backward's recompute keeps Z in the instruction's slot pair for the adjoint
                 double* zs = bwdmap ? (double*)slot(e, I.coef) : nullptr;
                 until_smooth_fwd_d(e, ua, ub, w, Ep, Eq, out, zs, bl, M);
@@ -1570,7 +1719,7 @@ DEV void exec_fwd(const Env& e, const Instr& I, bool bwdmap)
             }
             SP* Ephi = (SP*)S(e, 0);
             SP* Epsi = (SP*)S(e, 2);
-            for (int j = threadIdx.x; j < L; j += blockDim.x) {
+            for (int j = threadIdx.x; j < L; j += e.nt) {
                 Ephi[j] = sp_leaf(-bl * phi[j]);
                 Epsi[j] = sp_leaf(-bl * psi[j]);
             }
@@ -1582,7 +1731,6 @@ DEV void exec_fwd(const Env& e, const Instr& I, bool bwdmap)
     default:
         break;
     }
-    __syncthreads();
 }
 
 // Adjoint of one instruction (backward slot map).  Children adjoints are
@@ -1599,7 +1747,7 @@ DEV void exec_adj(const Env& e, const Instr& I, float* mask_part)
         break;
     case K_NOT: {
         float* gu = slot(e, I.g_in0);
-        for (int t = threadIdx.x; t < L; t += blockDim.x) gu[t] = -g[t];
+        for (int t = threadIdx.x; t < L; t += e.nt) gu[t] = -g[t];
         break;
     }
     case K_NARY:
@@ -1626,32 +1774,33 @@ DEV void exec_adj(const Env& e, const Instr& I, float* mask_part)
             const int n = L - I.a;
             SP* den = (SP*)S(e, 6);
             win_smooth_sum(e, u, den, sg * bl, I.a, khi, I.pad, padv, (SP*)S(e, 0), (SP*)S(e, 2));
-            SP* h = (SP*)S(e, 0);
-            SP* h2 = (SP*)S(e, 8);
             float lastpad = 0.f;
             const SP zv = sp_leaf(sg * bl * u[L - 1]);
-            for (int t = threadIdx.x; t < L; t += blockDim.x) {
-                SP a = sp_zero(), b2 = sp_zero();
-                if (t < n) {
-                    const SP d = den[t];
-                    a = SP{g[t] / d.s, -d.r};
-                    b2 = SP{g[t] * out[t] / d.s, -d.r};
-                }
-                h[t] = a;
-                h2[t] = b2;
+            for (int t = threadIdx.x; t < L; t += e.nt) {
                 if (khi >= 0 && I.pad == PAD_LAST && t + khi > L - 1) {
                     const int np = min(khi - I.a + 1, t + khi - (L - 1));
                     const float pv = sp_ratio(zv, den[t]);
                     lastpad += g[t] * (float)np * pv * (1.f + kap * (u[L - 1] - out[t]));
                 }
             }
-            if (I.pad == PAD_LAST) lastpad = wg_sum(lastpad, *e.sh);
-            __syncthreads();
+            if (I.pad == PAD_LAST) lastpad = wg_sum(lastpad, e);
             SP* res = (SP*)S(e, 4);
             SP* res2 = (SP*)S(e, 10);
-            win_smooth_adj_sum(e, h, (SP*)S(e, 2), res, I.a, khi, n);
-            win_smooth_adj_sum(e, h2, (SP*)S(e, 2), res2, I.a, khi, n);
-            for (int j = threadIdx.x; j < L; j += blockDim.x) {
+            win_smooth_adj_sum(
+                e,
+                [&](int t) {
+                    const SP d = den[t];
+                    return t < n ? SP{g[t] / d.s, -d.r} : sp_zero();
+                },
+                (SP*)S(e, 0), (SP*)S(e, 2), res, I.a, khi, n);
+            win_smooth_adj_sum(
+                e,
+                [&](int t) {
+                    const SP d = den[t];
+                    return t < n ? SP{g[t] * out[t] / d.s, -d.r} : sp_zero();
+                },
+                (SP*)S(e, 0), (SP*)S(e, 2), res2, I.a, khi, n);
+            for (int j = threadIdx.x; j < L; j += e.nt) {
                 const SP r1 = res[j], r2 = res2[j];
                 const SP c = sp_add(SP{r1.s * (1.f + kap * u[j]), r1.r}, SP{-kap * r2.s, r2.r});
                 float vj = sp_times_exp2(c, sg * bl * u[j]);
@@ -1664,27 +1813,25 @@ DEV void exec_adj(const Env& e, const Instr& I, float* mask_part)
         const float* out = slot(e, I.b_out);
         const bool unb = khi < 0;
         const int n = L - I.a;
-        SP* h = (SP*)S(e, 0);
         float lastpad = 0.f;
-        for (int t = threadIdx.x; t < L; t += blockDim.x) {
-            const float O = sg * bl * out[t];
-            const bool real = t < n;
-            const bool padded = !unb && I.pad != PAD_NEUTRAL && t + khi > L - 1;
-            SP hv = sp_zero();
-            if (real || padded) {
-                SP q = sp_leaf(-O);
-                hv = SP{g[t] * q.s, q.r};
-            }
-            h[t] = real ? hv : sp_zero();
-            if (padded && I.pad == PAD_LAST) {
-                const int np = min(unb ? 0 : khi - I.a + 1, t + khi - (L - 1));
-                lastpad += (float)np * sp_times_exp2(hv, sg * bl * u[L - 1]);
-            }
+        if (!unb && I.pad == PAD_LAST) {
+            for (int t = threadIdx.x; t < L; t += e.nt)
+                if (t + khi > L - 1) {
+                    const int np = min(khi - I.a + 1, t + khi - (L - 1));
+                    const SP q = sp_leaf(-sg * bl * out[t]);
+                    lastpad += (float)np * sp_times_exp2(SP{g[t] * q.s, q.r}, sg * bl * u[L - 1]);
+                }
+            lastpad = wg_sum(lastpad, e);
         }
-        lastpad = wg_sum(lastpad, *e.sh);
         SP* res = (SP*)S(e, 4);
-        win_smooth_adj_sum(e, h, (SP*)S(e, 2), res, I.a, khi, n);
-        for (int j = threadIdx.x; j < L; j += blockDim.x) {
+        win_smooth_adj_sum(
+            e,
+            [&](int t) {
+                const SP q = sp_leaf(-sg * bl * out[t]);
+                return t < n ? SP{g[t] * q.s, q.r} : sp_zero();
+            },
+            (SP*)S(e, 0), (SP*)S(e, 2), res, I.a, khi, n);
+        for (int j = threadIdx.x; j < L; j += e.nt) {
             float v = sp_times_exp2(res[j], sg * bl * u[j]);
             if (j == L - 1) v += lastpad;
             gu[j] = v;
@@ -1706,7 +1853,7 @@ DEV void exec_adj(const Env& e, const Instr& I, float* mask_part)
         const bool anyk = mi.any || mt.hi >= 0;
         if (!is_smooth(I) || !anyk) {
             if (!anyk) {
-                for (int j = threadIdx.x; j < L; j += blockDim.x) gu[j] = 0.f;
+                for (int j = threadIdx.x; j < L; j += e.nt) gu[j] = 0.f;
             } else {
                 const int khi = ((I.flags & F_MASK_UNB) && khi_all == L - 1) ? -1 : khi_all;
                 int* js = (int*)S(e, 4);
@@ -1720,8 +1867,7 @@ DEV void exec_adj(const Env& e, const Instr& I, float* mask_part)
         const float bl = pbeta(e, I) * LOG2E;
         const float* out = slot(e, I.b_out);
         const bool core = mi.clo <= mi.chi;
-        SP* h = (SP*)S(e, 0);
-        SP* hb = (SP*)S(e, 9);      // band copy of h (the scans consume h)
+        SP* hb = (SP*)S(e, 9);      // adjoint terms
         SP* E = (SP*)S(e, 11);
         const int nvalid = mi.any ? L - mi.klo : 0;
         float pa = 0.f, pb = 0.f;
@@ -1733,12 +1879,12 @@ DEV void exec_adj(const Env& e, const Instr& I, float* mask_part)
             float* TW = S(e, 13);
             float* TWa = S(e, 14);
             float* TWb = S(e, 15);
-            tail_weights(w, TW, L, mt.s, *e.sh);
-            tail_weights(dwa, TWa, L, mt.sa, *e.sh);
-            tail_weights(dwb, TWb, L, mt.sb, *e.sh);
+            tail_weights(w, TW, L, mt.s, e);
+            tail_weights(dwa, TWa, L, mt.sa, e);
+            tail_weights(dwb, TWb, L, mt.sb, e);
             const float zv = sg * bl * (I.pad == PAD_LAST ? u[L - 1] : mask_padv(I));
             const float ib0 = sg / pbeta(e, I);
-            for (int t = threadIdx.x; t < L; t += blockDim.x) {
+            for (int t = threadIdx.x; t < L; t += e.nt) {
                 if (t + khi_all <= L - 1 || !(TW[t] > 0.f)) continue;
                 const float f = exp2f(zv - sg * bl * out[t] + log2f(TW[t]));
                 const float gf = g[t] * f;
@@ -1746,21 +1892,20 @@ DEV void exec_adj(const Env& e, const Instr& I, float* mask_part)
                 pb += ib0 * gf * (TWb[t] / TW[t]);
                 lastpad += gf;
             }
-            if (I.pad == PAD_LAST) lastpad = wg_sum(lastpad, *e.sh);
+            if (I.pad == PAD_LAST) lastpad = wg_sum(lastpad, e);
         }
-        for (int t = threadIdx.x; t < L; t += blockDim.x) {
+        for (int t = threadIdx.x; t < L; t += e.nt) {
             E[t] = sp_leaf(sg * bl * u[t]);
             SP hv = sp_zero();
             if (t < nvalid) {
                 SP q = sp_leaf(-sg * bl * out[t]);
                 hv = SP{g[t] * q.s, q.r};
             }
-            h[t] = hv;
             hb[t] = hv;
         }
         __syncthreads();
         // d/da, d/db: per t, sum over the support bands of dw_k 2^{z_{t+k} - O_t}
-        for (int t = threadIdx.x; t < nvalid; t += blockDim.x) {
+        for (int t = threadIdx.x; t < nvalid; t += e.nt) {
             SPD aa{0.0, SP_NEG}, ab{0.0, SP_NEG};
             const int b0 = mi.klo, b1 = core ? mi.clo - 1 : mi.khi;
             for (int k = b0; k <= b1 && t + k < L; ++k) {
@@ -1777,16 +1922,16 @@ DEV void exec_adj(const Env& e, const Instr& I, float* mask_part)
             pa += ib * sp_times_exp2(spd_to_sp(aa), -O);
             pb += ib * sp_times_exp2(spd_to_sp(ab), -O);
         }
-        pa = wg_sum(pa, *e.sh);
-        pb = wg_sum(pb, *e.sh);
+        pa = wg_sum(pa, e);
+        pb = wg_sum(pb, e);
         if (I.mslot >= 0 && threadIdx.x == 0) { mask_part[2 * I.mslot] = pa; mask_part[2 * I.mslot + 1] = pb; }
         // dx: core via the transposed van Herk sum, bands term by term
         SP* res = (SP*)S(e, 4);
         if (core) {
             const int khi = ((I.flags & F_MASK_UNB) && mi.chi == L - 1) ? -1 : mi.chi;
-            win_smooth_adj_sum(e, h, (SP*)S(e, 2), res, mi.clo, khi, nvalid);
+            win_smooth_adj_sum(e, [&](int t) { return hb[t]; }, (SP*)S(e, 0), (SP*)S(e, 2), res, mi.clo, khi, nvalid);
         }
-        for (int j = threadIdx.x; j < L; j += blockDim.x) {
+        for (int j = threadIdx.x; j < L; j += e.nt) {
             // signed adjoint terms: accumulate with a double mantissa
             SPD a{0.0, SP_NEG};
             if (core) a = spd_add(a, SP{res[j].s * mi.wc, res[j].r});
@@ -1806,7 +1951,7 @@ DEV void exec_adj(const Env& e, const Instr& I, float* mask_part)
         const float* psi = slot(e, I.b_in1);
         float* gphi = slot(e, I.g_in0);
         float* gpsi = slot(e, I.g_in1);
-        for (int t = threadIdx.x; t < L; t += blockDim.x) { gphi[t] = 0.f; gpsi[t] = 0.f; }
+        for (int t = threadIdx.x; t < L; t += e.nt) { gphi[t] = 0.f; gpsi[t] = 0.f; }
         __syncthreads();
         int ua = I.a, ub = I.b;
         const float *w = nullptr, *dwa = nullptr, *dwb = nullptr;
@@ -1833,17 +1978,17 @@ DEV void exec_adj(const Env& e, const Instr& I, float* mask_part)
             const float bl = pbeta(e, I) * LOG2E;
             const int bmax = ub < 0 ? L - 1 : min(ub, L - 1);
             int M;
-            if (until_ref(phi, psi, L, bl, *e.sh, M)) {
+            if (until_ref(phi, psi, L, bl, e, M)) {
                 double* Ep = (double*)S(e, 0);
                 double* Eq = (double*)S(e, 2);
-                until_terms(phi, psi, L, bl, M, Ep, Eq);
+                until_terms(phi, psi, L, bl, M, Ep, Eq, e.nt);
                 const double* zs = (const double*)slot(e, I.coef);
                 until_smooth_adj_d(e, ua, ub, w, dwa, dwb, Ep, Eq, zs, g, gphi, gpsi, (double*)S(e, UCK_UNIT),
                                    bmax / UCK + 1, pa, pb);
             } else {
                 SP* Ephi = (SP*)S(e, 0);
                 SP* Epsi = (SP*)S(e, 2);
-                for (int j = threadIdx.x; j < L; j += blockDim.x) {
+                for (int j = threadIdx.x; j < L; j += e.nt) {
                     Ephi[j] = sp_leaf(-bl * phi[j]);
                     Epsi[j] = sp_leaf(-bl * psi[j]);
                 }
@@ -1855,8 +2000,8 @@ DEV void exec_adj(const Env& e, const Instr& I, float* mask_part)
         if (I.mslot >= 0) {
             // d out / d w_i = Y_i / (beta Z); zero for the hard form
             const float ib = is_smooth(I) ? 1.f / pbeta(e, I) : 0.f;
-            const float sa = wg_sum(pa * ib, *e.sh);
-            const float sb = wg_sum(pb * ib, *e.sh);
+            const float sa = wg_sum(pa * ib, e);
+            const float sb = wg_sum(pb * ib, e);
             if (threadIdx.x == 0) { mask_part[2 * I.mslot] = sa; mask_part[2 * I.mslot + 1] = sb; }
         }
         // d phi / d psi are sums of scaled terms: convert the scaled psi/phi sums in place
@@ -1865,8 +2010,12 @@ DEV void exec_adj(const Env& e, const Instr& I, float* mask_part)
     default:
         break;
     }
-    __syncthreads();
 }
+
+// Instructions whose thread for timestep t reads only what that thread wrote
+// (every pointwise loop maps t to thread t mod blockDim) need no barrier
+// between them; the others read and write across threads.
+DEV bool crosses_threads(const Instr& I) { return I.kind == K_WIN || I.kind == K_MASK || I.kind == K_UNTIL; }
 
 // ------------------------------------------------------------------ kernels
 
@@ -1877,10 +2026,10 @@ DEV bool next_item(const KArgs& ka, Shared& sh, int64_t& item, bool first, int64
 {
     if (ka.scan) {
         // the rows blockIdx.x + i gridDim.x whose flag is set, in order of i
-        // (the flags of up to blockDim.x rows are read at once)
+        // (the flags of up to ka.nt rows are read at once)
         __syncthreads();
         const int64_t nrow = B > (int64_t)blockIdx.x ? (B - 1 - (int64_t)blockIdx.x) / gridDim.x + 1 : 0;
-        for (int64_t i0 = first ? 0 : (int64_t)sh.scan_pos; i0 < nrow; i0 += blockDim.x) {
+        for (int64_t i0 = first ? 0 : (int64_t)sh.scan_pos; i0 < nrow; i0 += ka.nt) {
             if (threadIdx.x == 0) sh.scan_min = INT_MAX;
             __syncthreads();
             const int64_t i = i0 + threadIdx.x;
@@ -1907,10 +2056,31 @@ DEV bool next_item(const KArgs& ka, Shared& sh, int64_t& item, bool first, int64
     return true;
 }
 
-template <bool BWD>
+// One word of every line of the plan that the program uses, requested at
+// once: the argument segment lies in host memory, and a line fetched when an
+// instruction is reached costs the program 0.5 to 1 us each time.
+DEV void plan_touch(const DevPlan* P)
+{
+    const int* w = (const int*)P;
+    constexpr int PR = offsetof(DevPlan, pred) / 4, I0 = offsetof(DevPlan, ins) / 4, C0 = offsetof(DevPlan, coef) / 4;
+    int a = 0;
+#pragma unroll
+    for (int i = 0; i < PR + 32; i += 16) a |= w[i];          // header, the first 16 predicates
+#pragma unroll
+    for (int i = 0; i < 176; i += 16) a |= w[I0 + i];         // the first 16 instructions
+#pragma unroll
+    for (int i = 0; i < 64; i += 16) a |= w[C0 + i];
+    const int n = P->n_ins * (int)sizeof(Instr) / 4;
+    for (int i = 176; i < n; i += 16) a |= w[I0 + i];
+    asm volatile("" ::"s"(a));
+}
+
+// GLOBAL: the slots lie in the workspace instead of LDS (two kernels, so that
+// every slot access of the LDS one is an LDS instruction, not a flat one).
+template <bool BWD, bool GLOBAL>
 __global__ void __launch_bounds__(MAX_NT) stl_exec_kernel(DevPlan plan, Batch bt, KArgs ka)
 {
-    extern __shared__ float smem[];
+    extern __shared__ __align__(16) float smem[];
     __shared__ Shared sh;
     // The plan is the first kernel argument, at offset 0 of the kernarg
     // segment: read it there.  (Taking the address of the by-value parameter
@@ -1918,11 +2088,15 @@ __global__ void __launch_bounds__(MAX_NT) stl_exec_kernel(DevPlan plan, Batch bt
     // does once the kernel body grows past some size.)
     const DevPlan* P = (const DevPlan*)__builtin_amdgcn_kernarg_segment_ptr();
     (void)plan;
-    float* arena = ka.garena ? ka.garena + (size_t)blockIdx.x * ka.arena_floats : smem;
+    if (!ka.scan) plan_touch(P);         // (a fix-up launch usually finds no flag set)
+    float* arena = GLOBAL ? ka.garena + (size_t)blockIdx.x * ka.arena_floats : smem;
     const int nslots = BWD ? P->n_slots_bwd : P->n_slots_fwd;
     const int Lc = bt.Lcap;
     int64_t item = 0;
     bool first = true;
+    // no mask bound to differentiate: the parameter gradients are 0
+    if (BWD && ka.gp_zero && blockIdx.x == 0)
+        for (int q = threadIdx.x; q < P->n_params; q += ka.nt) ka.gp_zero[q] = 0.f;
     // an empty fix-up list: nothing to do and no counter to clear
     if (ka.list_mode && *ka.list_count <= 0) return;
     while (next_item(ka, sh, item, first, bt.B)) {
@@ -1932,22 +2106,23 @@ __global__ void __launch_bounds__(MAX_NT) stl_exec_kernel(DevPlan plan, Batch bt
         const int64_t b = ka.list_mode ? (int64_t)ka.list[item] : (bt.order ? (int64_t)bt.order[item] : item);
         const int64_t off = bt.offsets ? bt.offsets[b] : b * bt.T;
         const int64_t len = bt.offsets ? bt.offsets[b + 1] - off : bt.T;
+        if (!BWD && ka.saved_none && threadIdx.x == 0) ka.saved_none[b] = 0;
         if (len <= 0) {
             // an empty trajectory adds nothing to d/da, d/db: its partials
             // are still read by the reduction
             if (BWD)
-                for (int q = threadIdx.x; q < ka.part_stride * P->n_masks * 2; q += blockDim.x)
+                for (int q = threadIdx.x; q < ka.part_stride * P->n_masks * 2; q += ka.nt)
                     ka.mask_part[b * ka.part_stride * P->n_masks * 2 + q] = 0.f;
             continue;
         }
         if (len > Lc) {
             // trajectory longer than the launch's capacity: report NaN
-            for (int64_t t = threadIdx.x; t < len; t += blockDim.x) {
+            for (int64_t t = threadIdx.x; t < len; t += ka.nt) {
                 if (!BWD) ka.root[off + t] = NAN;
                 else for (int d = 0; d < bt.D; ++d) ka.dx[(off + t) * bt.D + d] = NAN;
             }
             if (BWD)
-                for (int q = threadIdx.x; q < ka.part_stride * P->n_masks * 2; q += blockDim.x)
+                for (int q = threadIdx.x; q < ka.part_stride * P->n_masks * 2; q += ka.nt)
                     ka.mask_part[b * ka.part_stride * P->n_masks * 2 + q] = NAN;
             continue;
         }
@@ -1961,10 +2136,18 @@ __global__ void __launch_bounds__(MAX_NT) stl_exec_kernel(DevPlan plan, Batch bt
         e.arena = arena;
         e.scr = arena + (size_t)nslots * Lc;
         e.sh = &sh;
-        for (int k = 0; k < P->n_ins; ++k) exec_fwd(e, P->ins[k], BWD);
+        e.nt = ka.nt;
+        op_preds(e, BWD);
+        for (int k = P->n_pred; k < P->n_ins; ++k) {
+            const Instr I = load_words(&P->ins[k]);
+            const bool x = crosses_threads(I);
+            if (x) __syncthreads();
+            exec_fwd(e, I, BWD);
+            if (x) __syncthreads();
+        }
         if (!BWD) {
             const float* r = slot(e, P->ins[P->root].f_out);
-            for (int t = threadIdx.x; t < e.L; t += blockDim.x) ka.root[off + t] = r[t];
+            for (int t = threadIdx.x; t < e.L; t += ka.nt) ka.root[off + t] = r[t];
             if (ka.nodes) {
                 // every node trace (debug): rerun with all slots kept is not
                 // needed because the forward map keeps node outputs until
@@ -1977,21 +2160,26 @@ __global__ void __launch_bounds__(MAX_NT) stl_exec_kernel(DevPlan plan, Batch bt
                     const Instr& I = P->ins[k];
                     if (I.node < 0) continue;
                     const float* s = slot(e, I.f_out);
-                    for (int t = threadIdx.x; t < e.L; t += blockDim.x)
+                    for (int t = threadIdx.x; t < e.L; t += ka.nt)
                         ka.nodes[(int64_t)I.node * ntot + off + t] = s[t];
                 }
             }
             __syncthreads();
         } else {
             float* gr = slot(e, P->ins[P->root].g_out);
-            for (int t = threadIdx.x; t < e.L; t += blockDim.x) gr[t] = ka.G[off + t];
-            __syncthreads();
+            for (int t = threadIdx.x; t < e.L; t += ka.nt) gr[t] = ka.G[off + t];
             // one partial row per trajectory; with part_stride > 1 (rows per
             // chunk of the matrix-core path) the trajectory's other rows are cleared
             float* mp = ka.mask_part + b * ka.part_stride * P->n_masks * 2;
-            for (int q = threadIdx.x; q < (ka.part_stride - 1) * P->n_masks * 2; q += blockDim.x)
+            for (int q = threadIdx.x; q < (ka.part_stride - 1) * P->n_masks * 2; q += ka.nt)
                 mp[P->n_masks * 2 + q] = 0.f;
-            for (int k = P->n_ins - 1; k >= 0; --k) exec_adj(e, P->ins[k], mp);
+            for (int k = P->n_ins - 1; k >= P->n_pred; --k) {
+                const Instr I = load_words(&P->ins[k]);
+                const bool x = crosses_threads(I);
+                if (x) __syncthreads();
+                exec_adj(e, I, mp);
+                if (x) __syncthreads();
+            }
             op_dx(e, ka.dx + off * bt.D);
             __syncthreads();
         }
@@ -2081,19 +2269,22 @@ size_t scratch_floats(int Lc, int nt, int max_until_b)
 hipError_t launch_exec(bool bwd, const DevPlan& plan, const Batch& bt, const KArgs& ka, int grid, int nt,
                        size_t lds_bytes, hipStream_t s)
 {
-    if (bwd) {
-        hipLaunchKernelGGL(stl_exec_kernel<true>, dim3(grid), dim3(nt), lds_bytes, s, plan, bt, ka);
+    const dim3 g(grid), b(nt);     // (ka.nt = nt)
+    if (ka.garena) {
+        if (bwd) hipLaunchKernelGGL((stl_exec_kernel<true, true>), g, b, lds_bytes, s, plan, bt, ka);
+        else hipLaunchKernelGGL((stl_exec_kernel<false, true>), g, b, lds_bytes, s, plan, bt, ka);
     } else {
-        hipLaunchKernelGGL(stl_exec_kernel<false>, dim3(grid), dim3(nt), lds_bytes, s, plan, bt, ka);
+        if (bwd) hipLaunchKernelGGL((stl_exec_kernel<true, false>), g, b, lds_bytes, s, plan, bt, ka);
+        else hipLaunchKernelGGL((stl_exec_kernel<false, false>), g, b, lds_bytes, s, plan, bt, ka);
     }
     return hipGetLastError();
 }
 
 hipError_t set_max_lds(size_t bytes)
 {
-    hipError_t e1 = hipFuncSetAttribute((const void*)stl_exec_kernel<false>,
+    hipError_t e1 = hipFuncSetAttribute((const void*)stl_exec_kernel<false, false>,
                                         hipFuncAttributeMaxDynamicSharedMemorySize, (int)bytes);
-    hipError_t e2 = hipFuncSetAttribute((const void*)stl_exec_kernel<true>,
+    hipError_t e2 = hipFuncSetAttribute((const void*)stl_exec_kernel<true, false>,
                                         hipFuncAttributeMaxDynamicSharedMemorySize, (int)bytes);
     return e1 != hipSuccess ? e1 : e2;
 }

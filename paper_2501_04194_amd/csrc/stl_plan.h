@@ -41,7 +41,8 @@ constexpr int MAX_PRED = 32;
 constexpr int MAX_MASKS = 16;
 constexpr int MAX_D = 16;
 
-struct Instr {                  // 40 bytes
+struct Instr {                  // 44 bytes; the words the kernels index by are 32 bits wide (a 16-bit field of
+                                // the argument segment is a vector load from host memory, not a scalar load)
     int8_t kind, flags, nch, pad;
     int8_t f_out, f_in0, f_in1;             // forward slot map
     int8_t b_out, b_in0, b_in1;             // backward slot map (values)
@@ -50,12 +51,18 @@ struct Instr {                  // 40 bytes
     int8_t mask;                            // parameter index of (a,b,c,eps), -1
     int8_t mslot;                           // index of this mask in the d/da,d/db partials
     int8_t f_ch[MAX_NCH], b_ch[MAX_NCH], g_ch[MAX_NCH];
-    int16_t node;                           // caller's node index (trace output), -1
-    int16_t coef;                           // predicate / pad-value offset into coef[]
+    int32_t node;                           // caller's node index (trace output), -1
+    int32_t coef;                           // predicate / pad-value offset into coef[]
     int32_t a, b;                           // integer interval (b < 0: unbounded); K_MASK:
                                             // a = bits of the pad value (no interval)
 };
-static_assert(sizeof(Instr) == 40, "Instr layout");
+static_assert(sizeof(Instr) == 44, "Instr layout");
+
+// What the evaluation and the d/dx of a predicate need of its instruction.
+struct PredRef {
+    int32_t coef;
+    int8_t kind, f_out, b_out, g_out;
+};
 
 // Fused fast path (set by the plan compiler when the formula has the shape
 // root = smooth And/Or over up to 4 smooth-mask Eventually/Always nodes, each
@@ -77,13 +84,13 @@ struct DevPlan {
     int32_t D;
     int32_t n_masks;
     int32_t n_params;
-    int32_t n_pred;
+    int32_t n_pred;                         // predicates are instructions 0 .. n_pred-1
     int32_t root;                           // instruction index of the root
     float rho_max;
     float rho_pad;
-    int16_t pred_ins[MAX_PRED];             // instruction index of each predicate
-    int8_t mask_param[MAX_MASKS];           // parameter index of each learnable mask
     FusedDesc fused;
+    PredRef pred[MAX_PRED];
+    int32_t mask_param[MAX_MASKS];          // parameter index of each learnable mask
     Instr ins[MAX_INSTR];
     float coef[MAX_COEF];
 };
@@ -125,6 +132,9 @@ struct KArgs {
     const float* saved_in; // fused backward: mask-node traces in, or NULL (recompute)
     int* saved_flag;       // [B]: 1 where the saved traces of a trajectory are valid
     const int* scan;       // [B] or NULL: the generic executor takes the trajectories whose flag is set
+    int* saved_none;       // [B] or NULL: the generic executor marks its trajectories' saved traces unusable
+    float* gp_zero;        // backward of a plan without masks: parameter gradients to clear, or NULL
+    int nt;                // work-group size of the generic executor
     int part_stride;       // rows of mask_part per trajectory (1; a caller with more rows per
                            // trajectory has the generic executor clear the others)
 };
