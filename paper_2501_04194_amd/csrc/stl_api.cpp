@@ -19,7 +19,8 @@
 #include "stl_plan.h"
 
 namespace stlmi {
-size_t scratch_floats(int Lc, int nt, int max_until_b);
+size_t scratch_floats(int Lc, int nt, int units, int until_b, bool until_masked);
+size_t until_export_bytes(int nt);
 hipError_t launch_exec(bool bwd, const DevPlan& plan, const struct Batch& bt, const struct KArgs& ka, int grid,
                        int nt, size_t lds_bytes, hipStream_t s);
 hipError_t set_max_lds(size_t bytes);
@@ -78,7 +79,7 @@ DevInfo& devinfo()
     if (hipDeviceGetAttribute(&v, hipDeviceAttributeMultiprocessorCount, dev) == hipSuccess && v > 0) di.cus = v;
     if (hipDeviceGetAttribute(&v, hipDeviceAttributeMaxSharedMemoryPerBlock, dev) == hipSuccess && v > 0)
         di.lds_max = (size_t)v;
-    const size_t static_lds = 8192;   // Shared struct + headroom
+    const size_t static_lds = 2048;   // Shared struct + headroom
     di.lds_max = di.lds_max > static_lds ? di.lds_max - static_lds : 0;
     if (set_max_lds(di.lds_max) == hipSuccess) di.lds_set = true;
     (void)set_max_lds_fused(di.lds_max);
@@ -138,9 +139,13 @@ stl_status geometry(const stl_plan* plan, const stl_batch* bt, const stl_launch*
     if (bt->T < 1 || bt->T > (1 << 24)) return fail(STL_E_SHAPE, "T must be in [1, 2^24]");
     int Lc = (int)((bt->T + 3) / 4 * 4);
     const int nslots = bwd ? dp.n_slots_bwd : dp.n_slots_fwd;
-    const int ub = plan->has_until ? (int)std::min<int64_t>(plan->max_until_b, bt->T) : 0;
-    size_t arena = (size_t)nslots * Lc + scratch_floats(Lc, nt, ub);
-    size_t lds = arena * sizeof(float);
+    const int ub = bwd && plan->until_b >= 0 ? (int)std::min<int64_t>(plan->until_b, bt->T) : -1;
+    auto scratch = [&](int threads) {
+        return scratch_floats(Lc, threads, plan->scr_units[bwd], ub, plan->until_masked);
+    };
+    size_t arena = (size_t)nslots * Lc + scratch(nt);
+    auto export_bytes = [&](int threads) { return ub >= 0 ? until_export_bytes(threads) : 0; };
+    size_t lds = arena * sizeof(float) + export_bytes(nt);
     bool global = (cfg && cfg->global_slots) || lds > di.lds_max;
     if (!(cfg && cfg->threads) && bt->B < di.cus) {
         // fewer trajectories than compute units (one work-group each): size
@@ -149,12 +154,13 @@ stl_status geometry(const stl_plan* plan, const stl_batch* bt, const stl_launch*
         // 256 where the larger Until checkpoint area of 512 threads would
         // push the arena out of LDS
         const int want = bt->T <= 64 ? 64 : bt->T <= 128 ? 128 : bt->T <= 256 ? 256 : 512;
-        const size_t a2 = (size_t)nslots * Lc + scratch_floats(Lc, want, ub);
-        const bool g2 = (cfg && cfg->global_slots) || a2 * sizeof(float) > di.lds_max;
+        const size_t a2 = (size_t)nslots * Lc + scratch(want);
+        const size_t l2 = a2 * sizeof(float) + export_bytes(want);
+        const bool g2 = (cfg && cfg->global_slots) || l2 > di.lds_max;
         if (want < 256 || g2 == global) {
             nt = want;
             arena = a2;
-            lds = a2 * sizeof(float);
+            lds = l2;
             global = g2;
         }
     }
@@ -176,7 +182,7 @@ stl_status geometry(const stl_plan* plan, const stl_batch* bt, const stl_launch*
     g->Lc = Lc;
     g->global = global;
     g->arena_floats = arena;
-    g->lds_bytes = global ? 0 : lds;
+    g->lds_bytes = global ? export_bytes(nt) : lds;
     g->mx = false;
     g->mx_lds = 0;
     g->off_handed = g->off_mxtr = g->off_mxflag = g->off_mxrange = g->off_mxheads = 0;

@@ -53,8 +53,8 @@ struct Builder {
     std::vector<float> coef;
     int n_pred = 0;
     std::vector<int> mask_params;
-    int max_until_b = 0;
-    bool has_until = false;
+    int until_b = -1;            // largest end of a smooth Until (checkpoints of its adjoint)
+    bool until_masked = false;
 
     int new_instr(Instr I, std::vector<int> ch)
     {
@@ -193,7 +193,6 @@ stl_status emit(Builder& B, int id, int depth, int* out)
         break;
     case STL_UNTIL:
         I.kind = K_UNTIL;
-        B.has_until = true;
         if (n.mask_param >= 0) {
             // smooth mask on the Until index: the kernels walk its support,
             // which can reach the end of the trajectory
@@ -206,7 +205,10 @@ stl_status emit(Builder& B, int id, int depth, int* out)
             I.a = 0;
             I.b = -1;
             I.flags |= F_UNB;
-            B.max_until_b = 1 << 30;
+            if (smooth) {
+                B.until_b = 1 << 30;
+                B.until_masked = true;
+            }
             break;
         }
         if (n.a < 0 || (n.b >= 0 && n.b < n.a) || n.b < -1)
@@ -214,7 +216,7 @@ stl_status emit(Builder& B, int id, int depth, int* out)
         I.a = n.a;
         I.b = n.b;
         if (n.b < 0) I.flags |= F_UNB;
-        B.max_until_b = std::max(B.max_until_b, n.b < 0 ? (1 << 30) : n.b);
+        if (smooth) B.until_b = std::max(B.until_b, n.b < 0 ? (1 << 30) : n.b);
         break;
     default:
         return fail(STL_E_FORMULA, "node %d: unknown op %d", id, n.op);
@@ -242,6 +244,26 @@ void pred_refs(DevPlan& dp)
     for (int i = 0; i < dp.n_pred; ++i) {
         const Instr& I = dp.ins[i];
         dp.pred[i] = PredRef{I.coef, I.kind, I.f_out, I.b_out, I.g_out};
+    }
+}
+
+// scratch units (one float per timestep each) an instruction uses; the
+// backward runs both its forward and its adjoint
+int scratch_units(const Instr& I, bool bwd)
+{
+    const bool smooth = I.flags & F_SMOOTH;
+    switch (I.kind) {
+    case K_WIN:
+        if (I.flags & F_SOFT) return bwd ? 12 : 8;
+        return smooth ? 6 : (bwd ? 8 : 4);
+    case K_MASK:
+        return 16;
+    case K_UNTIL:
+        if (I.mask >= 0) return 7;
+        if (smooth) return 4;
+        return (I.flags & F_UNB) ? 16 : 4;
+    default:
+        return 0;
     }
 }
 
@@ -462,8 +484,11 @@ extern "C" stl_status stl_compile(const stl_node* nodes, int32_t n_nodes, const 
     p->n_nodes = n_nodes;
     p->n_params = n_params;
     p->D = D;
-    p->max_until_b = B.max_until_b;
-    p->has_until = B.has_until;
+    p->until_b = B.until_b;
+    p->until_masked = B.until_masked;
+    p->scr_units[0] = p->scr_units[1] = 0;
+    for (const Instr& I : B.ins)
+        for (int bwd = 0; bwd < 2; ++bwd) p->scr_units[bwd] = std::max(p->scr_units[bwd], scratch_units(I, bwd != 0));
     *out = p;
     return STL_OK;
 }

@@ -383,7 +383,7 @@ __global__ void __launch_bounds__(256) stl_mask_tables(DevPlan plan, const float
     const int m = blockIdx.x;
     const Instr& I = P.ins[P.fused.ins[m]];
     MaskTab& T = tabs[m];
-    const MaskInfo mi = mask_info(params, I, L, sh, blockDim.x, nullptr, nullptr, nullptr);
+    const MaskInfo mi = mask_info(params, I, L, sh, blockDim.x, threadIdx.x, nullptr, nullptr, nullptr);
     const bool core = mi.any && mi.clo <= mi.chi;
     const int le = core ? mi.clo : mi.khi + 1;
     const int kl0 = mi.any ? mi.klo : 0;

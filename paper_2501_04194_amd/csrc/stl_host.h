@@ -14,8 +14,9 @@ struct stl_plan {
     int32_t n_nodes = 0;  // caller's nodes
     int32_t n_params = 0;
     int32_t D = 0;
-    int32_t max_until_b = 0;
-    int32_t has_until = 0;
+    int32_t scr_units[2] = {0, 0};   // operator scratch of the forward / backward, in floats per timestep
+    int32_t until_b = -1;            // largest interval end over the smooth Untils (2^30: unbounded; -1: none)
+    bool until_masked = false;       // one of them has a smooth mask
 };
 
 namespace stlmi {

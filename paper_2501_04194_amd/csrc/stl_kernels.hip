@@ -28,6 +28,7 @@
 #include <stdint.h>
 #include <math.h>
 #include <algorithm>
+#include <type_traits>
 #include "stl_plan.h"
 
 namespace stlmi {
@@ -116,12 +117,20 @@ struct OpD {
 // ------------------------------------------------------------------ scans
 
 struct Shared {
-    double scan[MAX_NT];
-    int flag[MAX_NT];
+    double scan[2 * MAX_NT / 64];    // totals of the waves (two scans at a time)
+    int flag[2 * MAX_NT / 64];
     int ints[8];
-    float f[8];
     int scan_pos, scan_min;      // flag-scan fix-up: next row index of this work-group, first set flag
 };
+
+// the thread index as a value the compiler knows nothing more about
+DEV int exec_tid()
+{
+    int t = threadIdx.x;
+    asm volatile("" : "+v"(t));
+    __builtin_assume(t >= 0 && t < MAX_NT);
+    return t;
+}
 
 struct Env {
     const DevPlan* P;
@@ -129,8 +138,11 @@ struct Env {
     const float* params;
     int L, Lc, D;
     float* arena;      // slots
-    float* scr;        // op scratch (SCR_FLOATS(Lc) floats)
+    float* scr;        // op scratch
+    float* lds;        // nt UT_RMAX fp64 pairs in LDS: the export buffers of the smooth Until's adjoint
     Shared* sh;
+    int tid;           // threadIdx.x, opaque per instruction: what is derived from it is not kept in registers
+                       // across the program (hoisted, it spilled)
     int nt;            // work-group size (blockDim.x is a 16-bit field of the argument segment in host
                        // memory: a vector load of 1 to 2 us wherever the compiler reads it again)
 };
@@ -187,8 +199,8 @@ DEV int scan_chunk(int n, int nt) { return (n + nt - 1) / nt | 1; }
 template <bool REV, class T, class Op, class Leaf, class Head>
 DEV T scan_local(T* x, int n, T ident, Op op, Leaf leaf, Head head, const Env& e, int which, ScanPos& s)
 {
-    const int C = scan_chunk(n, e.nt), lane = threadIdx.x & 63;
-    const int ct = REV ? (int)e.nt - 1 - (int)threadIdx.x : (int)threadIdx.x;
+    const int C = scan_chunk(n, e.nt), lane = e.tid & 63;
+    const int ct = REV ? (int)e.nt - 1 - e.tid : e.tid;
     s.c0 = min(n, ct * C);
     s.c1 = min(n, s.c0 + C);
     const int m = s.c1 - s.c0;
@@ -220,8 +232,8 @@ DEV T scan_local(T* x, int n, T ident, Op op, Leaf leaf, Head head, const Env& e
 #undef STLMI_SCAN_STEP
     s.wave_carry = (hm & ((1ull << lane) - 1)) == 0;
     if (lane == 63) {
-        reinterpret_cast<T*>(e.sh->scan)[which * 8 + (threadIdx.x >> 6)] = acc;
-        e.sh->flag[which * 8 + (threadIdx.x >> 6)] = hm != 0;
+        reinterpret_cast<T*>(e.sh->scan)[which * 8 + (e.tid >> 6)] = acc;
+        e.sh->flag[which * 8 + (e.tid >> 6)] = hm != 0;
     }
     const T ex = dpp8<0x138>(acc);
     return lane == 0 ? ident : ex;
@@ -230,7 +242,7 @@ DEV T scan_local(T* x, int n, T ident, Op op, Leaf leaf, Head head, const Env& e
 template <bool REV, class T, class Op>
 DEV void scan_carry(T* x, T carry, Op op, const Env& e, int which, const ScanPos& s)
 {
-    const int w = threadIdx.x >> 6, lane = threadIdx.x & 63;
+    const int w = e.tid >> 6, lane = e.tid & 63;
     if (e.nt > 64) {
         // lane q % 8 scans the totals of waves 0 .. q (wave w needs those of 0 .. w-1)
         const int q = lane & 7;
@@ -254,7 +266,7 @@ DEV void scan_carry(T* x, T carry, Op op, const Env& e, int which, const ScanPos
         __builtin_memcpy(&c, cw, 8);
         if (s.wave_carry && w > 0) carry = lane == 0 ? c : scan_join<REV>(c, carry, op);
     }
-    if (threadIdx.x == 0) return;        // nothing comes before
+    if (e.tid == 0) return;        // nothing comes before
     for (int i = 0; i < s.free; ++i) {
         const int p = REV ? s.c1 - 1 - i : s.c0 + i;
         x[p] = scan_join<REV>(carry, x[p], op);
@@ -328,7 +340,7 @@ DEV T wg_sum(T v, const Env& e)
 #pragma unroll
     for (int d = 32; d > 0; d >>= 1) v += __shfl_xor(v, d);
     T* tot = reinterpret_cast<T*>(e.sh->scan);
-    if ((threadIdx.x & 63) == 0) tot[threadIdx.x >> 6] = v;
+    if ((e.tid & 63) == 0) tot[e.tid >> 6] = v;
     __syncthreads();
     T r = tot[0];
     for (int w = 1; w < e.nt >> 6; ++w) r += tot[w];
@@ -339,8 +351,8 @@ DEV T wg_sum(T v, const Env& e)
 // ------------------------------------------------------------------ context
 
 
-// scratch layout (floats): everything an operator needs, in units of Lc
-#define SCR_UNITS 16
+// scratch layout (floats): what an operator needs, in units of Lc (at most
+// 16; the plan compiler finds each plan's need)
 DEV float* S(const Env& e, int unit) { return e.scr + (size_t)unit * e.Lc; }
 
 DEV float* slot(const Env& e, int s) { return e.arena + (size_t)s * e.Lc; }
@@ -432,7 +444,7 @@ DEV void preds_fwd(const Env& e, bool bwdmap)
     const DevPlan& P = *e.P;
     const int nt = e.nt;
     const bool vec = vec_rows<D>(e.x);
-    for (int t0 = threadIdx.x; t0 < e.L; t0 += PRED_TB * nt) {
+    for (int t0 = e.tid; t0 < e.L; t0 += PRED_TB * nt) {
         float x[PRED_TB][D];
 #pragma unroll
         for (int j = 0; j < PRED_TB; ++j)
@@ -460,7 +472,7 @@ DEV void op_preds(const Env& e, bool bwdmap)
     for (int p = 0; p < P.n_pred; ++p) {
         const PredRef I = load_words(&P.pred[p]);
         float* out = slot(e, bwdmap ? I.b_out : I.f_out);
-        for (int t = threadIdx.x; t < e.L; t += e.nt)
+        for (int t = e.tid; t < e.L; t += e.nt)
             out[t] = pred_value(I.kind, P.coef + I.coef, e.D, e.x + (size_t)t * e.D);
     }
 }
@@ -498,7 +510,7 @@ template <int D>
 DEV void preds_dx(const Env& e, float* dx)
 {
     const bool vx = vec_rows<D>(e.x), vd = vec_rows<D>(dx);
-    for (int t = threadIdx.x; t < e.L; t += e.nt) {
+    for (int t = e.tid; t < e.L; t += e.nt) {
         float x[D], acc[D];
         load_row<D>(e.x + (size_t)t * D, vx, x);
 #pragma unroll
@@ -516,7 +528,7 @@ DEV void op_dx(const Env& e, float* dx)
     case 3: preds_dx<3>(e, dx); return;
     case 4: preds_dx<4>(e, dx); return;
     }
-    for (int t = threadIdx.x; t < e.L; t += e.nt) {
+    for (int t = e.tid; t < e.L; t += e.nt) {
         float acc[MAX_D];
 #pragma unroll
         for (int d = 0; d < MAX_D; ++d) acc[d] = 0.f;
@@ -534,7 +546,7 @@ DEV void nary_fwd(const Env& e, const Instr& I, const int8_t* ch, float* out)
     const float* c[N];
 #pragma unroll
     for (int k = 0; k < N; ++k) c[k] = slot(e, ch[k]);
-    for (int t = threadIdx.x; t < e.L; t += e.nt) {
+    for (int t = e.tid; t < e.L; t += e.nt) {
         float v[N], m = -INFINITY;
 #pragma unroll
         for (int k = 0; k < N; ++k) v[k] = sg * c[k][t];
@@ -585,7 +597,7 @@ DEV void nary_bwd(const Env& e, const Instr& I)
         c[k] = slot(e, I.b_ch[k]);
         gc[k] = slot(e, I.g_ch[k]);
     }
-    for (int t = threadIdx.x; t < e.L; t += e.nt) {
+    for (int t = e.tid; t < e.L; t += e.nt) {
         const float gt = g[t];
         float v[N];
 #pragma unroll
@@ -644,7 +656,7 @@ DEV void win_hard(const Env& e, const float* u, float* out, int* jstar, float sg
         scan_blocks(Pre, Suf, n, unb ? 0 : K, VI{-INFINITY, 0x7fffffff}, OpVI(),
                     [&](int i) { return VI{sg * u[klo + i], klo + i}; }, e);
     const float rho_pad = e.P->rho_pad;
-    for (int t = threadIdx.x; t < L; t += e.nt) {
+    for (int t = e.tid; t < L; t += e.nt) {
         VI r{-INFINITY, L};
         bool any = false;
         if (t < n) {
@@ -675,10 +687,10 @@ DEV void win_hard(const Env& e, const float* u, float* out, int* jstar, float sg
 DEV void win_hard_adj(const Env& e, const float* g, float* gu, const int* jstar, double* P)
 {
     const int L = e.L;
-    for (int j = threadIdx.x; j < L; j += e.nt) gu[j] = 0.f;
+    for (int j = e.tid; j < L; j += e.nt) gu[j] = 0.f;
     scan_one<false>(P, L, 0.0, OpD(), [&](int t) { return (double)g[t]; },
                     [&](int t) { return t == 0 || jstar[t] != jstar[t - 1]; }, e);
-    for (int t = threadIdx.x; t < L; t += e.nt) {
+    for (int t = e.tid; t < L; t += e.nt) {
         const int j = jstar[t];
         if (j < L && (t == L - 1 || jstar[t + 1] != j)) gu[j] = (float)P[t];
     }
@@ -702,7 +714,7 @@ DEV void win_smooth_sum(const Env& e, const float* u, SP* acc, float sgz, int kl
     if (n > 0)
         scan_blocks(Pre, Suf, n, unb ? 0 : K, sp_zero(), OpSP(), [&](int i) { return sp_leaf(sgz * u[klo + i]); },
                     e);
-    for (int t = threadIdx.x; t < L; t += e.nt) {
+    for (int t = e.tid; t < L; t += e.nt) {
         SP a = sp_zero();
         if (t < n) {
             const int e2 = min(t + K - 1, n - 1);
@@ -738,7 +750,7 @@ DEV void win_smooth_sum_w(const Env& e, const float* u, SP* acc, float sgz, int 
                         return v;
                     },
                     e);
-    for (int t = threadIdx.x; t < L; t += e.nt) {
+    for (int t = e.tid; t < L; t += e.nt) {
         SP a = sp_zero();
         if (t < n) {
             const int e2 = min(t + K - 1, n - 1);
@@ -767,7 +779,7 @@ DEV void win_smooth_adj_sum(const Env& e, Leaf h, SP* hSuf, SP* hPre, SP* res, i
     const float inv = 1.f / (float)K;
     if (unb) scan_one<false>(hPre, L, sp_zero(), OpSP(), h, HeadUp(0, L), e);
     else scan_blocks(hPre, hSuf, L, K, sp_zero(), OpSP(), h, e);
-    for (int j = threadIdx.x; j < L; j += e.nt) {
+    for (int j = e.tid; j < L; j += e.nt) {
         SP a = sp_zero();
         const int en = min(j - klo, n_valid - 1);
         const int st = unb ? 0 : max(0, j - khi);
@@ -896,16 +908,16 @@ DEV int wave_imax(int v)
 // Weights for k in [0, L) (stored when w != NULL), the support {w > 0} and
 // the core.  Without stored weights only the support's window is searched.
 template <class SH>
-DEV MaskInfo mask_info(const float* params, const Instr& I, int L, SH& sh, int nt, float* w, float* dwa, float* dwb)
+DEV MaskInfo mask_info(const float* params, const Instr& I, int L, SH& sh, int nt, int tid, float* w, float* dwa, float* dwb)
 {
     const MaskP mp = mask_params(params + I.mask, I.flags & F_MASK_UNB);
     int* si = sh.ints;
-    if (threadIdx.x == 0) { si[0] = L; si[1] = -1; }
+    if (tid == 0) { si[0] = L; si[1] = -1; }
     __syncthreads();
     int lo = L, hi = -1;
     int k0 = 0, k1 = L - 1;
     if (!w && !dwa) mask_window(mp, L, k0, k1);
-    for (int k = k0 + (int)threadIdx.x; k <= k1; k += nt) {
+    for (int k = k0 + tid; k <= k1; k += nt) {
         float da, db;
         const float wk = mask_wk(mp, k, dwa ? &da : nullptr, &db);
         if (w) w[k] = wk;
@@ -914,7 +926,7 @@ DEV MaskInfo mask_info(const float* params, const Instr& I, int L, SH& sh, int n
     }
     lo = wave_imin(lo);
     hi = wave_imax(hi);
-    if ((threadIdx.x & 63) == 0) {
+    if ((tid & 63) == 0) {
         atomicMin(&si[0], lo);
         atomicMax(&si[1], hi);
     }
@@ -930,7 +942,7 @@ DEV float mask_padv(const Instr& I) { return __int_as_float(I.a); }
 
 DEV MaskInfo mask_weights(const Env& e, const Instr& I, float* w, float* dwa, float* dwb)
 {
-    return mask_info(e.params, I, e.L, *e.sh, e.nt, w, dwa, dwb);
+    return mask_info(e.params, I, e.L, *e.sh, e.nt, e.tid, w, dwa, dwb);
 }
 
 // Offsets past the signal end, for the LAST / CONST pads of a bounded smooth
@@ -957,11 +969,11 @@ DEV MaskTail mask_tail(const Env& e, const Instr& I, bool grads)
         kend = ke >= (float)L ? (int)ke : -1;
     }
     int* si = e.sh->ints;
-    if (threadIdx.x == 0) { si[5] = INT_MAX; si[6] = -1; }
+    if (e.tid == 0) { si[5] = INT_MAX; si[6] = -1; }
     __syncthreads();
     int lo = INT_MAX, hi = -1;
     double s = 0.0, sa = 0.0, sb = 0.0;
-    for (int k = L + (int)threadIdx.x; k <= kend; k += e.nt) {
+    for (int k = L + e.tid; k <= kend; k += e.nt) {
         float da = 0.f, db = 0.f;
         const float wk = mask_wk(mp, k, grads ? &da : nullptr, &db);
         if (wk > 0.f) {
@@ -992,7 +1004,7 @@ DEV MaskTail mask_tail(const Env& e, const Instr& I, bool grads)
 DEV void tail_weights(const float* v, float* out, int L, double tail, const Env& e)
 {
     Shared& sh = *e.sh;
-    const int nt = e.nt, tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
+    const int nt = e.nt, tid = e.tid, lane = tid & 63, wv = tid >> 6;
     const int nw = (nt + 63) >> 6;
     const int ch = (L + nt - 1) / nt;
     const int k0 = min(L, tid * ch), k1 = min(L, k0 + ch);
@@ -1031,7 +1043,7 @@ DEV void until_hard(const Env& e, int a, int b, const float* phi, const float* p
 {
     const int L = e.L;
     const float rho_pad = e.P->rho_pad;
-    for (int t = threadIdx.x; t < L; t += e.nt) {
+    for (int t = e.tid; t < L; t += e.nt) {
         const int imax = b < 0 ? L - 1 - t : min(b, L - 1 - t);
         if (a > imax) {
             if (out) out[t] = -rho_pad;
@@ -1056,7 +1068,7 @@ DEV void until_hard(const Env& e, int a, int b, const float* phi, const float* p
     }
     if (!g) return;
     __syncthreads();
-    for (int j = threadIdx.x; j < L; j += e.nt) {
+    for (int j = e.tid; j < L; j += e.nt) {
         float sp = 0.f, sq = 0.f;
         for (int t = b < 0 ? 0 : max(0, j - b); t <= j; ++t) {
             const int c = code[t];
@@ -1116,7 +1128,7 @@ DEV void until_hard_unb(const Env& e, int a, const float* phi, const float* psi,
                    [&](int s) { return ClampMap{phi[s] <= psi[s] ? phi[s] : psi[s], phi[s]}; }, HeadDown(0, L),
                    e);                                                         // cm[s].lo = U(s)
     if (!g) {
-        for (int t = threadIdx.x; t < L; t += e.nt) {
+        for (int t = e.tid; t < L; t += e.nt) {
             float v = -rho_pad;
             if (t + a <= L - 1) {
                 const float u = cm[t + a].lo;
@@ -1130,7 +1142,7 @@ DEV void until_hard_unb(const Env& e, int a, const float* phi, const float* psi,
     int* code = (int*)S(e, 8);
     Affine* fa = (Affine*)S(e, 9);          // units 9, 10
     float* gw = S(e, 11);                   // adjoint sent to the window argmin of m_a
-    for (int s = threadIdx.x; s < L; s += e.nt) {
+    for (int s = e.tid; s < L; s += e.nt) {
         const float un = s + 1 < L ? cm[s + 1].lo : -INFINITY;
         int c = UH_PHI;
         if (!(phi[s] <= psi[s])) {
@@ -1155,7 +1167,7 @@ DEV void until_hard_unb(const Env& e, int a, const float* phi, const float* psi,
                         return Affine{h, s > 0 && code[s - 1] == UH_PASS ? 1 : 0};
                     },
                     HeadUp(0, L), e);                                         // fa[s].h = F(s)
-    for (int s = threadIdx.x; s < L; s += e.nt) {
+    for (int s = e.tid; s < L; s += e.nt) {
         if (code[s] == UH_PHI) gphi[s] += fa[s].h;
         else if (code[s] == UH_PSI) gpsi[s] += fa[s].h;
     }
@@ -1163,7 +1175,7 @@ DEV void until_hard_unb(const Env& e, int a, const float* phi, const float* psi,
     if (a > 0) {
         float* gu = S(e, 15);
         win_hard_adj(e, gw, gu, jA, (double*)S(e, 12));                          // units 12..14
-        for (int j = threadIdx.x; j < L; j += e.nt) gphi[j] += gu[j];
+        for (int j = e.tid; j < L; j += e.nt) gphi[j] += gu[j];
         __syncthreads();
     }
 }
@@ -1179,7 +1191,7 @@ DEV void until_smooth_fwd(const Env& e, int a, int b, const float* w, const SP* 
 {
     const int L = e.L;
     const float rho_pad = e.P->rho_pad;
-    for (int t = threadIdx.x; t < L; t += e.nt) {
+    for (int t = e.tid; t < L; t += e.nt) {
         const int imax = b < 0 ? L - 1 - t : min(b, L - 1 - t);
         if (a > imax) { out[t] = -rho_pad; continue; }
         SP P = sp_zero(), Z = sp_zero();
@@ -1195,7 +1207,14 @@ DEV void until_smooth_fwd(const Env& e, int a, int b, const float* w, const SP* 
 }
 
 constexpr int UCK = 16;   // checkpoint spacing of the smooth Until adjoint
-constexpr int UCK_UNIT = 7;   // scratch unit where its checkpoints start (units 4-6: mask tables)
+constexpr int UCK_UNIT = 4, UCK_UNIT_MASK = 7;    // scratch unit where its checkpoints start (mask tables: units 4-6)
+constexpr int UT_RMAX = 4;                        // outputs per lane at most
+
+// checkpoints per lane for the interval's end b (< 0: unbounded)
+static __host__ __device__ __forceinline__ int until_cks(int b, int L)
+{
+    return (b < 0 || b > L - 1 ? L - 1 : (b + UT_RMAX - 1 > L - 1 ? L - 1 : b + UT_RMAX - 1)) / UCK + 1;
+}
 
 // Smooth Until adjoint (checkpointed reverse sweep per output t):
 //   d out / d psi_{t+i} = w_i Y_i^2 Q_i / Z,  Q_i = 2^{-z_psi(t+i)}
@@ -1213,14 +1232,14 @@ DEV void until_smooth_adj(const Env& e, int a, int b, const float* w, const floa
                           int ncks, float& pa, float& pb)
 {
     const int L = e.L;
-    const int lane = threadIdx.x & 63;
+    const int lane = e.tid & 63;
     for (int base = 0; base < L; base += e.nt) {
-        const int tb = base + (int)threadIdx.x - lane;
+        const int tb = base + e.tid - lane;
         const int t = tb + lane;
         const int imax = t >= L ? -1 : (b < 0 ? L - 1 - t : min(b, L - 1 - t));
         const float gt = t < L ? g[t] : 0.f;
         const bool act = a <= imax && gt != 0.f;
-        SP* myck = ck + (size_t)threadIdx.x * ncks;
+        SP* myck = ck + (size_t)e.tid * ncks;
         SP Z = sp_zero();
         if (act) {
             SP P = sp_zero();
@@ -1320,7 +1339,7 @@ DEV bool until_ref(const float* phi, const float* psi, int L, float bl, const En
 {
     Shared& sh = *e.sh;
     int hi = INT_MIN, lo = INT_MAX, bad = 0;
-    for (int j = threadIdx.x; j < L; j += e.nt) {
+    for (int j = e.tid; j < L; j += e.nt) {
         const float u1 = -bl * phi[j], u2 = -bl * psi[j];
         if (!(fabsf(u1) < 1e9f) || !(fabsf(u2) < 1e9f)) {
             bad = 1;                                 // also catches NaN
@@ -1329,7 +1348,7 @@ DEV bool until_ref(const float* phi, const float* psi, int L, float bl, const En
             lo = min(lo, (int)floorf(fminf(u1, u2)));
         }
     }
-    if (threadIdx.x == 0) {
+    if (e.tid == 0) {
         sh.ints[2] = INT_MIN;
         sh.ints[3] = INT_MAX;
         sh.ints[4] = 0;
@@ -1346,65 +1365,151 @@ DEV bool until_ref(const float* phi, const float* psi, int L, float bl, const En
 }
 
 // leaf terms of both inputs as doubles 2^{u - M} (Ep, Eq)
-DEV void until_terms(const float* phi, const float* psi, int L, float bl, int M, double* Ep, double* Eq, int nt)
+DEV void until_terms(const float* phi, const float* psi, int L, float bl, int M, double* Ep, double* Eq, int nt, int tid)
 {
-    for (int j = threadIdx.x; j < L; j += nt) {
+    for (int j = tid; j < L; j += nt) {
         Ep[j] = uterm(-bl * phi[j], M);
         Eq[j] = uterm(-bl * psi[j], M);
     }
     __syncthreads();
 }
 
-// Z = sum_{i=a}^{imax} 1 / (P_i + q_i), P_i = sum_{k<=i} p_k, over the terms of
-// one output.  The terms are read eight at a time (independent loads ahead of
-// the dependent sums); the additions keep the plain sequential order.
-template <bool MW>
-DEV double until_z(const double* ep, const double* eq, int a, int imax, const float* w)
+// The fp64 forms: terms p_j = 2^{u_phi - M}, q_j = 2^{u_psi - M}; output t sums
+// Y = 1 / D, D_{t,j} = P_{t,j} + q_j, P_{t,j} = p_t + .. + p_j, over j = t+a ..
+// t+b: Z_t = sum_j Y (the same sums as until_smooth_fwd, with Y scaled by 2^{-M}).
+//
+// A lane owns R consecutive outputs t_0 .. t_0+R-1 and walks j = t_0 + s over
+// s = 0, 1, ..: since P_{t_0+r,j} = C_r + P_{t_0+R-1,j} with the constant
+// C_r = p_{t_0+r} + .. + p_{t_0+R-2}, the outputs share the two term reads
+// and the running sum of a step, and every D is one more addition of positive
+// terms (nothing cancels, whatever the range).  The walk is bound by vector
+// issue: per term an add, a reciprocal (4 issue slots) and the sum, against
+// two 8-byte LDS reads per term and a chain of dependent adds with one output
+// per thread.  R = 4 where the trajectory has enough outputs to give every
+// lane of the work-group four, else 2 or 1 (the lanes are worth more than the
+// shared reads).
+DEV int until_outputs(int L, int nt) { return L <= nt ? 1 : (L <= 2 * nt ? 2 : 4); }
+
+template <int R>
+DEV void until_fwd_r(const Env& e, int a, int b, const double* Ep, const double* Eq, float* out, double* zs, float bl,
+                     int M)
 {
-    double P = 0.0, Z = 0.0;
-    int i = 0;
-    for (; i + 8 <= a; i += 8) {
-        double v[8];
+    const int L = e.L;
+    const float rho_pad = e.P->rho_pad;
+    for (int t0 = e.tid * R; t0 < L; t0 += e.nt * R) {
+        const double* p = Ep + t0;
+        const double* q = Eq + t0;
+        const int last = L - 1 - t0;                                 // steps 0 .. last stay inside
+        const int smax = b < 0 ? last : min(b + R - 1, last);
+        double Z[R], C[R];
 #pragma unroll
-        for (int k = 0; k < 8; ++k) v[k] = ep[i + k];
+        for (int r = 0; r < R; ++r) Z[r] = 0.0;
+        if (R > 1 && a < R - 1) {
+            // steps before output t_0+R-1 begins
+            double Pr[R];
 #pragma unroll
-        for (int k = 0; k < 8; ++k) P += v[k];
-    }
-    for (; i < a; ++i) P += ep[i];
-    for (; i + 8 <= imax + 1; i += 8) {
-        double v[8], q[8];
+            for (int r = 0; r < R; ++r) Pr[r] = 0.0;
 #pragma unroll
-        for (int k = 0; k < 8; ++k) {
-            v[k] = ep[i + k];
-            q[k] = eq[i + k];
+            for (int s = 0; s < R - 1; ++s)
+                if (s <= smax) {
+                    const double ps = p[s], qs = q[s];
+#pragma unroll
+                    for (int r = 0; r <= s; ++r) {
+                        Pr[r] += ps;
+                        if (s - r >= a && (b < 0 || s - r <= b)) Z[r] += rcpd(Pr[r] + qs);
+                    }
+                }
         }
+        C[R - 1] = 0.0;
 #pragma unroll
-        for (int k = 0; k < 8; ++k) {
-            P += v[k];
-            const double y = rcpd(P + q[k]);
-            Z += MW ? (double)w[i + k] * y : y;
+        for (int r = R - 2; r >= 0; --r) C[r] = C[r + 1] + (t0 + r < L ? p[r] : 0.0);
+        double P = 0.0;
+        int s = R - 1;
+        for (; s + 8 <= min(a, smax + 1); s += 8) {
+            double v[8];
+#pragma unroll
+            for (int k = 0; k < 8; ++k) v[k] = p[s + k];
+#pragma unroll
+            for (int k = 0; k < 8; ++k) P += v[k];
+        }
+        for (; s < min(a, smax + 1); ++s) P += p[s];
+        // the window's two ends, where only some of the outputs take the term
+        auto edge = [&](int hi) {
+            for (; s <= hi; ++s) {
+                P += p[s];
+                const double d = P + q[s];
+#pragma unroll
+                for (int r = 0; r < R; ++r) {
+                    const double y = rcpd(d + C[r]);
+                    if (s - r >= a && (b < 0 || s - r <= b)) Z[r] += y;
+                }
+            }
+        };
+        const int full = b < 0 ? smax : min(b, smax);                // last step every output takes
+        edge(min(a + R - 2, smax));
+        constexpr int U = 8;
+        for (; s + U - 1 <= full; s += U) {
+            double v[U], w[U];
+#pragma unroll
+            for (int k = 0; k < U; ++k) {
+                v[k] = p[s + k];
+                w[k] = q[s + k];
+            }
+#pragma unroll
+            for (int k = 0; k < U; ++k) {
+                P += v[k];
+                const double d = P + w[k];
+#pragma unroll
+                for (int r = 0; r < R; ++r) Z[r] += rcpd(r == R - 1 ? d : d + C[r]);
+            }
+        }
+        edge(smax);
+#pragma unroll
+        for (int r = 0; r < R; ++r) {
+            const int t = t0 + r;
+            if (t >= L) continue;
+            if (a > (b < 0 ? L - 1 - t : min(b, L - 1 - t))) {
+                out[t] = -rho_pad;
+                continue;
+            }
+            out[t] = (float)(log2_minus(Z[r], M) / (double)bl);
+            if (zs) zs[t] = Z[r];
         }
     }
-    for (; i <= imax; ++i) {
-        P += ep[i];
-        const double y = rcpd(P + eq[i]);
-        Z += MW ? (double)w[i] * y : y;
-    }
-    return Z;
 }
 
-// Forward on the fp64 terms: the same sums as until_smooth_fwd, with
-// Y_i = 2^{-M} / (P_i + Q_i) in true units, so log2 Z_true = log2 Z - M.
-template <bool MW>
-DEV void until_fwd_d(const Env& e, int a, int b, const float* w, const double* Ep, const double* Eq, float* out,
+// The masked form (weights w_i by offset i): one output per thread, the terms
+// read eight at a time (independent loads ahead of the dependent sums).
+DEV void until_fwd_w(const Env& e, int a, int b, const float* w, const double* Ep, const double* Eq, float* out,
                      double* zs, float bl, int M)
 {
     const int L = e.L;
     const float rho_pad = e.P->rho_pad;
-    for (int t = threadIdx.x; t < L; t += e.nt) {
-        const int imax = b < 0 ? L - 1 - t : min(b, L - 1 - t);
+    for (int t = e.tid; t < L; t += e.nt) {
+        const int imax = min(b, L - 1 - t);
         if (a > imax) { out[t] = -rho_pad; continue; }
-        const double Z = until_z<MW>(Ep + t, Eq + t, a, imax, w);
+        const double* p = Ep + t;
+        const double* q = Eq + t;
+        double P = 0.0, Z = 0.0;
+        int i = 0;
+        for (; i < a; ++i) P += p[i];
+        for (; i + 8 <= imax + 1; i += 8) {
+            double v[8], x[8];
+#pragma unroll
+            for (int k = 0; k < 8; ++k) {
+                v[k] = p[i + k];
+                x[k] = q[i + k];
+            }
+#pragma unroll
+            for (int k = 0; k < 8; ++k) {
+                P += v[k];
+                Z += (double)w[i + k] * rcpd(P + x[k]);
+            }
+        }
+        for (; i <= imax; ++i) {
+            P += p[i];
+            Z += (double)w[i] * rcpd(P + q[i]);
+        }
         out[t] = (float)(log2_minus(Z, M) / (double)bl);
         if (zs) zs[t] = Z;
     }
@@ -1447,32 +1552,194 @@ DEV void lane_stage(int i, int tb, int lane, int L, float& accp, float& accq, fl
 }
 
 // Adjoint on the fp64 terms (the derivatives are ratios of terms, so the
-// reference cancels).  Z_t comes from the forward recompute (zs); a forward
-// sweep of additions keeps P every UCK steps; the reverse sweep rebuilds each
-// block's P from its checkpoint and carries the suffix sum A of Y_i^2:
-//   d out / d psi_{t+i} = Y_i^2 q_i / Z,  d out / d phi_{t+k} = p_k A_k / Z.
-// The lanes of a wave hold consecutive t and walk i downwards in step, so at
-// each step lane l adds to position t_0 + l + i: the wave keeps one register
-// accumulator per lane for these positions and moves them up one lane per
-// step.  The position leaving lane 63 is complete for this wave; it is parked
-// in one lane of a staging register, and every 64 steps the stage is added to
-// the adjoint slots.  The rest are added at the end.  All waves of the
-// work-group walk the same steps (those of the longest chain of the pass), so
-// the stages are added at the same points in every wave: at one point the
-// waves' stages cover disjoint positions, and a barrier separates the points,
-// which fixes the order of every addition (results are bitwise reproducible).
-// With smooth mask weights (MW) each term carries w_i: Z = sum w_i Y_i, A
-// sums w_i Y_i^2, and d out / d w_i = Y_i / (beta Z) is summed against
-// d w/da, d w/db into pa, pb (per thread, before the division by beta).
-template <bool MW>
-DEV void until_adj_d(const Env& e, int a, int b, const float* w, const float* dwa, const float* dwb,
+// reference cancels).  Z_t comes from the forward recompute (zs).  With
+// m_{t,j} = (G_t / Z_t) Y_{t,j}^2,
+//   d out / d psi_j = q_j sum_t m_{t,j},  d out / d phi_k = p_k sum_{t <= k <= j} m_{t,j}.
+// A lane owns the R outputs of until_fwd_r and walks j = t_0 + s downwards.  A
+// forward sweep of additions keeps P_{t_0+R-1,j} every UCK steps; the reverse
+// walk rebuilds each block's sums from its checkpoint.  Step s adds
+// S = sum_r m_{t_0+r,j} to the psi sum of position j, and the running sum A of
+// S over the steps so far (all terms at or past j) to its phi sum.  Below
+// step R-1 position t_0+s lies before the last outputs, so the sums B_r over
+// the first r+1 outputs are carried as well.
+// The lanes of a wave walk the same steps, so the position of lane l, sum c
+// (s = R m + c) is that of lane l-1 one macro-step m earlier: the 2 R fp64
+// sums move up one lane per R steps (a DPP shift), and the positions leaving
+// lane 63 are finished for this wave.  They go to a buffer of the wave, which
+// is added to the adjoint slots every 64 macro-steps and scaled by p_j, q_j
+// there.  All waves of the work-group walk the same steps (those of the
+// longest chain of the pass), so the buffers are added at the same points in
+// every wave, where they cover disjoint positions, and a barrier separates the
+// points: the order of every addition is fixed (bitwise reproducible).
+// Against one output per lane (three multiplies, two conversions, two float
+// adds, two lane reads and two shifts per term) a term takes an add, the
+// reciprocal, two multiplies and about 2.5 adds.
+template <int R>
+DEV void until_adj_r(const Env& e, int a, int b, const double* Ep, const double* Eq, const double* zs, const float* g,
+                     float* gphi, float* gpsi, double* ck, double* exb)
+{
+    const int L = e.L, nt = e.nt;
+    const int lane = e.tid & 63;
+    double* ex = exb + (size_t)(e.tid >> 6) * (128 * R);       // psi sums, then phi sums
+    for (int base = 0; base < L; base += nt * R) {
+        const int tb = base + (e.tid - lane) * R;
+        const int t0 = tb + lane * R;
+        const double* p = Ep + t0;
+        const double* q = Eq + t0;
+        const int last = L - 1 - t0;
+        double wz[R], C[R];
+        bool any = false;
+#pragma unroll
+        for (int r = 0; r < R; ++r) {
+            const int t = t0 + r;
+            const float gt = t < L ? g[t] : 0.f;
+            const bool act = gt != 0.f && a <= (b < 0 ? L - 1 - t : min(b, L - 1 - t));
+            wz[r] = act ? (double)gt / zs[t] : 0.0;
+            any |= act;
+        }
+        C[R - 1] = 0.0;
+#pragma unroll
+        for (int r = R - 2; r >= 0; --r) C[r] = C[r + 1] + (t0 + r < L ? p[r] : 0.0);
+        // own steps (none where no output has an adjoint), steps of the pass
+        const int smax = any ? (b < 0 ? last : min(b + R - 1, last)) : -1;
+        const int sw = b < 0 ? L - 1 - base : min(b + R - 1, L - 1 - base);
+        const int wblk = a <= sw ? sw / UCK + 1 : 0;
+        {
+            double P = 0.0;
+            for (int blk = 0; blk <= smax / UCK && smax >= 0; ++blk) {
+                ck[blk * nt + e.tid] = P;
+                if ((blk + 1) * UCK <= smax) {                       // a next block: this one is whole
+                    double v[UCK];
+#pragma unroll
+                    for (int k = 0; k < UCK; ++k) v[k] = p[blk * UCK + k];
+#pragma unroll
+                    for (int k = 0; k < UCK; ++k)
+                        if (k >= R - 1 || blk > 0) P += v[k];
+                }
+            }
+        }
+        double A = 0.0, B[R], sq[R], sp[R];
+#pragma unroll
+        for (int r = 0; r < R; ++r) {
+            B[r] = sq[r] = sp[r] = 0.0;
+            ex[lane * R + r] = ex[64 * R + lane * R + r] = 0.0;
+        }
+        for (int blk = wblk - 1; blk >= 0; --blk) {
+            const int s0 = blk * UCK;
+            const int n = min(UCK, smax - s0 + 1);                   // own steps of the block (<= 0: none)
+            double v[UCK], d[UCK];
+            if (__all(n >= UCK)) {
+#pragma unroll
+                for (int k = 0; k < UCK; ++k) {
+                    v[k] = p[s0 + k];
+                    d[k] = q[s0 + k];
+                }
+            } else {
+#pragma unroll
+                for (int k = 0; k < UCK; ++k) {
+                    v[k] = k < n ? p[s0 + k] : 0.0;
+                    d[k] = k < n ? q[s0 + k] : 1e300;                // Y^2 = 0 past the own steps
+                }
+            }
+            double P = n > 0 ? ck[blk * nt + e.tid] : 0.0;
+#pragma unroll
+            for (int k = 0; k < UCK; ++k) {
+                if (k >= R - 1 || blk > 0) P += v[k];
+                d[k] += P;
+            }
+            auto steps = [&](auto inner) {
+#pragma unroll
+                for (int k = UCK - 1; k >= 0; --k) {
+                    const int s = s0 + k, c = k % R;
+                    double S = 0.0;
+                    if (decltype(inner)::value || s >= a) {
+                        double Dn[R];
+#pragma unroll
+                        for (int r = 0; r < R; ++r) Dn[r] = r == R - 1 ? d[k] : d[k] + C[r];
+                        if (R > 1 && !decltype(inner)::value && k < R - 1 && blk == 0) {
+                            // before output t_0+R-1 begins: P of output r is p_{t_0+r} + .. + p_j
+#pragma unroll
+                            for (int r = 0; r < R; ++r) {
+                                double Pr = 0.0;
+#pragma unroll
+                                for (int i = r; i <= k; ++i) Pr += v[i];
+                                Dn[r] = Pr + d[k];
+                            }
+                        }
+#pragma unroll
+                        for (int r = 0; r < R; ++r) {
+                            const double y = rcpd(Dn[r]);
+                            double m = (wz[r] * y) * y;
+                            if (!decltype(inner)::value && !(s - r >= a && (b < 0 || s - r <= b))) m = 0.0;
+                            S += m;
+                            B[r] += S;
+                        }
+                        A = B[R - 1];
+                    }
+                    sq[c] += S;
+                    sp[c] += (R > 1 && !decltype(inner)::value && k < R - 1 && blk == 0) ? B[k % R] : A;
+                    if (c == 0 && s > 0) {
+                        // macro-step m = s / R is done: lane 63's positions leave the wave
+                        const int i = ((s / R - 1) & 63) * R;
+                        if (lane == 63) {
+#pragma unroll
+                            for (int r = 0; r < R; ++r) {
+                                ex[i + r] = sq[r];
+                                ex[64 * R + i + r] = sp[r];
+                            }
+                        }
+                        if (i == 0) {
+                            __threadfence_block();                   // lane 63's values, for the other lanes
+                            const int m1 = s / R - 1;
+#pragma unroll
+                            for (int r = 0; r < R; ++r) {
+                                const int at = lane * R + r, j = tb + 64 * R + m1 * R + at;
+                                if (j < L) {
+                                    gpsi[j] += (float)(ex[at] * Eq[j]);
+                                    gphi[j] += (float)(ex[64 * R + at] * Ep[j]);
+                                }
+                                ex[at] = ex[64 * R + at] = 0.0;
+                            }
+                            __syncthreads();
+                        }
+#pragma unroll
+                        for (int r = 0; r < R; ++r) {
+                            sq[r] = dpp8<0x138>(sq[r]);
+                            sp[r] = dpp8<0x138>(sp[r]);
+                        }
+                    }
+                    // (interleaving more steps than this spills)
+                    if (k % 4 == 0) __builtin_amdgcn_sched_barrier(0);
+                }
+            };
+            if (s0 >= a + R - 1 && s0 > 0 && (b < 0 || s0 + UCK - 1 <= b)) steps(std::true_type());
+            else steps(std::false_type());
+        }
+        if (wblk > 0)
+#pragma unroll
+            for (int r = 0; r < R; ++r) {
+                const int j = t0 + r;
+                if (j < L) {
+                    gpsi[j] += (float)(sq[r] * Eq[j]);
+                    gphi[j] += (float)(sp[r] * Ep[j]);
+                }
+            }
+        __syncthreads();
+    }
+}
+
+// The masked form (weights w_i by offset i, one output per lane): Z = sum w_i Y_i,
+// A sums w_i Y_i^2, and d out / d w_i = Y_i / (beta Z) is summed against
+// d w/da, d w/db into pa, pb (per thread, before the division by beta).  The
+// lane-shifted sums are floats, parked in a staging register pair.
+DEV void until_adj_w(const Env& e, int a, int b, const float* w, const float* dwa, const float* dwb,
                      const double* Ep, const double* Eq, const double* zs, const float* g, float* gphi, float* gpsi,
                      double* ck, int ncks, float& pa, float& pb)
 {
     const int L = e.L;
-    const int lane = threadIdx.x & 63;
+    const int lane = e.tid & 63;
     for (int base = 0; base < L; base += e.nt) {
-        const int tb = base + (int)threadIdx.x - lane;
+        const int tb = base + e.tid - lane;
         const int t = tb + lane;
         const int imax = t >= L ? -1 : (b < 0 ? L - 1 - t : min(b, L - 1 - t));
         const float gt = t < L ? g[t] : 0.f;
@@ -1480,7 +1747,7 @@ DEV void until_adj_d(const Env& e, int a, int b, const float* w, const float* dw
         const int nblk = act ? imax / UCK + 1 : 0;
         const double* ep = Ep + t;
         const double* eq = Eq + t;
-        double* myck = ck + (size_t)threadIdx.x * ncks;
+        double* myck = ck + (size_t)e.tid * ncks;
         double Z = 1.0;
         if (act) {
             // Z comes from the forward recompute: only the block-start prefixes of P
@@ -1504,7 +1771,7 @@ DEV void until_adj_d(const Env& e, int a, int b, const float* w, const float* dw
         float accp = 0.f, accq = 0.f;
         float stp = 0.f, stq = 0.f;         // staged finished sums (see the shift below)
         double A = 0.0;                     // G/Z times the suffix sum of w_i Y_i^2
-        double da = 0.0, db = 0.0;          // sum of dw_i Y_i (MW)
+        double da = 0.0, db = 0.0;          // sum of dw_i Y_i
         for (int blk = wblk - 1; blk >= 0; --blk) {
             const int i0 = blk * UCK;
             const int n = blk < nblk ? min(UCK, imax - i0 + 1) : 0;
@@ -1526,13 +1793,11 @@ DEV void until_adj_d(const Env& e, int a, int b, const float* w, const float* dw
                 if (k < n) {
                     if (i >= a) {
                         const double y = rcpd(Ps[k] + q[k]);
-                        const double y2 = (MW ? wz * (double)w[i] : wz) * y * y;   // G/Z w_i Y_i^2
+                        const double y2 = wz * (double)w[i] * y * y;       // G/Z w_i Y_i^2
                         A += y2;
                         accq += (float)(y2 * q[k]);
-                        if (MW) {
-                            da += (double)dwa[i] * y;
-                            db += (double)dwb[i] * y;
-                        }
+                        da += (double)dwa[i] * y;
+                        db += (double)dwb[i] * y;
                     }
                     accp += (float)(A * v[k]);
                 }
@@ -1544,26 +1809,40 @@ DEV void until_adj_d(const Env& e, int a, int b, const float* w, const float* dw
             gpsi[t] += accq;
         }
         __syncthreads();
-        if (MW) {
-            pa += (float)(wz * da);
-            pb += (float)(wz * db);
-        }
+        pa += (float)(wz * da);
+        pb += (float)(wz * db);
     }
 }
 
 DEV void until_smooth_fwd_d(const Env& e, int a, int b, const float* w, const double* Ep, const double* Eq, float* out,
                             double* zs, float bl, int M)
 {
-    if (w) until_fwd_d<true>(e, a, b, w, Ep, Eq, out, zs, bl, M);
-    else until_fwd_d<false>(e, a, b, w, Ep, Eq, out, zs, bl, M);
+    if (w) {
+        until_fwd_w(e, a, b, w, Ep, Eq, out, zs, bl, M);
+        return;
+    }
+    switch (until_outputs(e.L, e.nt)) {
+    case 1: until_fwd_r<1>(e, a, b, Ep, Eq, out, zs, bl, M); break;
+    case 2: until_fwd_r<2>(e, a, b, Ep, Eq, out, zs, bl, M); break;
+    default: until_fwd_r<4>(e, a, b, Ep, Eq, out, zs, bl, M); break;
+    }
 }
 
+// ck: nt checkpoints per UCK steps
 DEV void until_smooth_adj_d(const Env& e, int a, int b, const float* w, const float* dwa, const float* dwb,
                             const double* Ep, const double* Eq, const double* zs, const float* g, float* gphi,
                             float* gpsi, double* ck, int ncks, float& pa, float& pb)
 {
-    if (w) until_adj_d<true>(e, a, b, w, dwa, dwb, Ep, Eq, zs, g, gphi, gpsi, ck, ncks, pa, pb);
-    else until_adj_d<false>(e, a, b, w, dwa, dwb, Ep, Eq, zs, g, gphi, gpsi, ck, ncks, pa, pb);
+    double* exb = (double*)e.lds;
+    if (w) {
+        until_adj_w(e, a, b, w, dwa, dwb, Ep, Eq, zs, g, gphi, gpsi, ck, ncks, pa, pb);
+        return;
+    }
+    switch (until_outputs(e.L, e.nt)) {
+    case 1: until_adj_r<1>(e, a, b, Ep, Eq, zs, g, gphi, gpsi, ck, exb); break;
+    case 2: until_adj_r<2>(e, a, b, Ep, Eq, zs, g, gphi, gpsi, ck, exb); break;
+    default: until_adj_r<4>(e, a, b, Ep, Eq, zs, g, gphi, gpsi, ck, exb); break;
+    }
 }
 
 // ------------------------------------------------------------------ instructions
@@ -1581,14 +1860,14 @@ DEV void exec_fwd(const Env& e, const Instr& I, bool bwdmap)
     const float sg = (I.flags & F_MIN) ? -1.f : 1.f;
     switch (I.kind) {
     case K_TRUE:
-        for (int t = threadIdx.x; t < L; t += e.nt) out[t] = e.P->rho_max;
+        for (int t = e.tid; t < L; t += e.nt) out[t] = e.P->rho_max;
         break;
     case K_LIN:
     case K_NORM:
         break;          // op_preds, before the first instruction
     case K_NOT: {
         const float* u = slot(e, i0);
-        for (int t = threadIdx.x; t < L; t += e.nt) out[t] = -u[t];
+        for (int t = e.tid; t < L; t += e.nt) out[t] = -u[t];
         break;
     }
     case K_NARY:
@@ -1609,7 +1888,7 @@ DEV void exec_fwd(const Env& e, const Instr& I, bool bwdmap)
             win_smooth_sum(e, u, den, sg * bl, I.a, khi, I.pad, padv, (SP*)S(e, 0), (SP*)S(e, 2));
             win_smooth_sum_w(e, u, num, sg * bl, I.a, khi, (SP*)S(e, 0), (SP*)S(e, 2));
             const float v = I.pad == PAD_LAST ? u[L - 1] : padv;
-            for (int t = threadIdx.x; t < L; t += e.nt) {
+            for (int t = e.tid; t < L; t += e.nt) {
                 SP nm = num[t];
                 const bool padded = khi >= 0 && I.pad != PAD_NEUTRAL && t + khi > L - 1;
                 if (padded) {
@@ -1625,7 +1904,7 @@ DEV void exec_fwd(const Env& e, const Instr& I, bool bwdmap)
             SP* acc = (SP*)S(e, 4);
             win_smooth_sum(e, u, acc, sg * bl, I.a, khi, I.pad, padv, (SP*)S(e, 0), (SP*)S(e, 2));
             const bool unb = khi < 0;
-            for (int t = threadIdx.x; t < L; t += e.nt) {
+            for (int t = e.tid; t < L; t += e.nt) {
                 const bool any = (t + I.a <= L - 1) || (!unb && I.pad != PAD_NEUTRAL && t + khi > L - 1);
                 out[t] = any ? sg * sp_log2(acc[t]) / bl : -sg * e.P->rho_pad;
             }
@@ -1646,7 +1925,7 @@ DEV void exec_fwd(const Env& e, const Instr& I, bool bwdmap)
         const float padv = mask_padv(I);
         if (!is_smooth(I)) {
             if (!anyk) {
-                for (int t = threadIdx.x; t < L; t += e.nt) out[t] = -sg * e.P->rho_pad;
+                for (int t = e.tid; t < L; t += e.nt) out[t] = -sg * e.P->rho_pad;
             } else {
                 const int kh = ((I.flags & F_MASK_UNB) && khi == L - 1) ? -1 : khi;
                 win_hard(e, u, out, nullptr, sg, klo, kh, padm ? I.pad : PAD_NEUTRAL, padv, (VI*)S(e, 0),
@@ -1663,11 +1942,11 @@ DEV void exec_fwd(const Env& e, const Instr& I, bool bwdmap)
             const int kh = ((I.flags & F_MASK_UNB) && mi.chi == L - 1) ? -1 : mi.chi;
             win_smooth_sum(e, u, acc, sg * bl, mi.clo, kh, PAD_NEUTRAL, 0.f, (SP*)S(e, 0), (SP*)S(e, 2));
         }
-        for (int j = threadIdx.x; j < L; j += e.nt) E[j] = sp_leaf(sg * bl * u[j]);
+        for (int j = e.tid; j < L; j += e.nt) E[j] = sp_leaf(sg * bl * u[j]);
         if (padm) tail_weights(w, TW, L, mt.s, e);
         __syncthreads();
         const SP Ev = sp_leaf(sg * bl * (I.pad == PAD_LAST ? u[L - 1] : padv));
-        for (int t = threadIdx.x; t < L; t += e.nt) {
+        for (int t = e.tid; t < L; t += e.nt) {
             // band terms are summed one by one (up to a few hundred of them):
             // accumulate with a double mantissa so the error does not grow with the count
             SPD a{0.0, SP_NEG};
@@ -1695,7 +1974,7 @@ DEV void exec_fwd(const Env& e, const Instr& I, bool bwdmap)
             float* wt = S(e, 4);
             const MaskInfo mi = mask_weights(e, I, wt, nullptr, nullptr);
             if (!mi.any) {
-                for (int t = threadIdx.x; t < L; t += e.nt) out[t] = -e.P->rho_pad;
+                for (int t = e.tid; t < L; t += e.nt) out[t] = -e.P->rho_pad;
                 break;
             }
             ua = mi.klo;
@@ -1711,7 +1990,7 @@ DEV void exec_fwd(const Env& e, const Instr& I, bool bwdmap)
             if (until_ref(phi, psi, L, bl, e, M)) {
                 double* Ep = (double*)S(e, 0);
                 double* Eq = (double*)S(e, 2);
-                until_terms(phi, psi, L, bl, M, Ep, Eq, e.nt);
+                until_terms(phi, psi, L, bl, M, Ep, Eq, e.nt, e.tid);
                 // the backward's recompute keeps Z in the instruction's slot pair for the adjoint
                 double* zs = bwdmap ? (double*)slot(e, I.coef) : nullptr;
                 until_smooth_fwd_d(e, ua, ub, w, Ep, Eq, out, zs, bl, M);
@@ -1719,7 +1998,7 @@ DEV void exec_fwd(const Env& e, const Instr& I, bool bwdmap)
             }
             SP* Ephi = (SP*)S(e, 0);
             SP* Epsi = (SP*)S(e, 2);
-            for (int j = threadIdx.x; j < L; j += e.nt) {
+            for (int j = e.tid; j < L; j += e.nt) {
                 Ephi[j] = sp_leaf(-bl * phi[j]);
                 Epsi[j] = sp_leaf(-bl * psi[j]);
             }
@@ -1747,7 +2026,7 @@ DEV void exec_adj(const Env& e, const Instr& I, float* mask_part)
         break;
     case K_NOT: {
         float* gu = slot(e, I.g_in0);
-        for (int t = threadIdx.x; t < L; t += e.nt) gu[t] = -g[t];
+        for (int t = e.tid; t < L; t += e.nt) gu[t] = -g[t];
         break;
     }
     case K_NARY:
@@ -1776,7 +2055,7 @@ DEV void exec_adj(const Env& e, const Instr& I, float* mask_part)
             win_smooth_sum(e, u, den, sg * bl, I.a, khi, I.pad, padv, (SP*)S(e, 0), (SP*)S(e, 2));
             float lastpad = 0.f;
             const SP zv = sp_leaf(sg * bl * u[L - 1]);
-            for (int t = threadIdx.x; t < L; t += e.nt) {
+            for (int t = e.tid; t < L; t += e.nt) {
                 if (khi >= 0 && I.pad == PAD_LAST && t + khi > L - 1) {
                     const int np = min(khi - I.a + 1, t + khi - (L - 1));
                     const float pv = sp_ratio(zv, den[t]);
@@ -1800,7 +2079,7 @@ DEV void exec_adj(const Env& e, const Instr& I, float* mask_part)
                     return t < n ? SP{g[t] * out[t] / d.s, -d.r} : sp_zero();
                 },
                 (SP*)S(e, 0), (SP*)S(e, 2), res2, I.a, khi, n);
-            for (int j = threadIdx.x; j < L; j += e.nt) {
+            for (int j = e.tid; j < L; j += e.nt) {
                 const SP r1 = res[j], r2 = res2[j];
                 const SP c = sp_add(SP{r1.s * (1.f + kap * u[j]), r1.r}, SP{-kap * r2.s, r2.r});
                 float vj = sp_times_exp2(c, sg * bl * u[j]);
@@ -1815,7 +2094,7 @@ DEV void exec_adj(const Env& e, const Instr& I, float* mask_part)
         const int n = L - I.a;
         float lastpad = 0.f;
         if (!unb && I.pad == PAD_LAST) {
-            for (int t = threadIdx.x; t < L; t += e.nt)
+            for (int t = e.tid; t < L; t += e.nt)
                 if (t + khi > L - 1) {
                     const int np = min(khi - I.a + 1, t + khi - (L - 1));
                     const SP q = sp_leaf(-sg * bl * out[t]);
@@ -1831,7 +2110,7 @@ DEV void exec_adj(const Env& e, const Instr& I, float* mask_part)
                 return t < n ? SP{g[t] * q.s, q.r} : sp_zero();
             },
             (SP*)S(e, 0), (SP*)S(e, 2), res, I.a, khi, n);
-        for (int j = threadIdx.x; j < L; j += e.nt) {
+        for (int j = e.tid; j < L; j += e.nt) {
             float v = sp_times_exp2(res[j], sg * bl * u[j]);
             if (j == L - 1) v += lastpad;
             gu[j] = v;
@@ -1853,7 +2132,7 @@ DEV void exec_adj(const Env& e, const Instr& I, float* mask_part)
         const bool anyk = mi.any || mt.hi >= 0;
         if (!is_smooth(I) || !anyk) {
             if (!anyk) {
-                for (int j = threadIdx.x; j < L; j += e.nt) gu[j] = 0.f;
+                for (int j = e.tid; j < L; j += e.nt) gu[j] = 0.f;
             } else {
                 const int khi = ((I.flags & F_MASK_UNB) && khi_all == L - 1) ? -1 : khi_all;
                 int* js = (int*)S(e, 4);
@@ -1861,7 +2140,7 @@ DEV void exec_adj(const Env& e, const Instr& I, float* mask_part)
                          (VI*)S(e, 0), (VI*)S(e, 2));
                 win_hard_adj(e, g, gu, js, (double*)S(e, 10));
             }
-            if (I.mslot >= 0 && threadIdx.x == 0) { mask_part[2 * I.mslot] = 0.f; mask_part[2 * I.mslot + 1] = 0.f; }
+            if (I.mslot >= 0 && e.tid == 0) { mask_part[2 * I.mslot] = 0.f; mask_part[2 * I.mslot + 1] = 0.f; }
             break;
         }
         const float bl = pbeta(e, I) * LOG2E;
@@ -1884,7 +2163,7 @@ DEV void exec_adj(const Env& e, const Instr& I, float* mask_part)
             tail_weights(dwb, TWb, L, mt.sb, e);
             const float zv = sg * bl * (I.pad == PAD_LAST ? u[L - 1] : mask_padv(I));
             const float ib0 = sg / pbeta(e, I);
-            for (int t = threadIdx.x; t < L; t += e.nt) {
+            for (int t = e.tid; t < L; t += e.nt) {
                 if (t + khi_all <= L - 1 || !(TW[t] > 0.f)) continue;
                 const float f = exp2f(zv - sg * bl * out[t] + log2f(TW[t]));
                 const float gf = g[t] * f;
@@ -1894,7 +2173,7 @@ DEV void exec_adj(const Env& e, const Instr& I, float* mask_part)
             }
             if (I.pad == PAD_LAST) lastpad = wg_sum(lastpad, e);
         }
-        for (int t = threadIdx.x; t < L; t += e.nt) {
+        for (int t = e.tid; t < L; t += e.nt) {
             E[t] = sp_leaf(sg * bl * u[t]);
             SP hv = sp_zero();
             if (t < nvalid) {
@@ -1905,7 +2184,7 @@ DEV void exec_adj(const Env& e, const Instr& I, float* mask_part)
         }
         __syncthreads();
         // d/da, d/db: per t, sum over the support bands of dw_k 2^{z_{t+k} - O_t}
-        for (int t = threadIdx.x; t < nvalid; t += e.nt) {
+        for (int t = e.tid; t < nvalid; t += e.nt) {
             SPD aa{0.0, SP_NEG}, ab{0.0, SP_NEG};
             const int b0 = mi.klo, b1 = core ? mi.clo - 1 : mi.khi;
             for (int k = b0; k <= b1 && t + k < L; ++k) {
@@ -1924,14 +2203,14 @@ DEV void exec_adj(const Env& e, const Instr& I, float* mask_part)
         }
         pa = wg_sum(pa, e);
         pb = wg_sum(pb, e);
-        if (I.mslot >= 0 && threadIdx.x == 0) { mask_part[2 * I.mslot] = pa; mask_part[2 * I.mslot + 1] = pb; }
+        if (I.mslot >= 0 && e.tid == 0) { mask_part[2 * I.mslot] = pa; mask_part[2 * I.mslot + 1] = pb; }
         // dx: core via the transposed van Herk sum, bands term by term
         SP* res = (SP*)S(e, 4);
         if (core) {
             const int khi = ((I.flags & F_MASK_UNB) && mi.chi == L - 1) ? -1 : mi.chi;
             win_smooth_adj_sum(e, [&](int t) { return hb[t]; }, (SP*)S(e, 0), (SP*)S(e, 2), res, mi.clo, khi, nvalid);
         }
-        for (int j = threadIdx.x; j < L; j += e.nt) {
+        for (int j = e.tid; j < L; j += e.nt) {
             // signed adjoint terms: accumulate with a double mantissa
             SPD a{0.0, SP_NEG};
             if (core) a = spd_add(a, SP{res[j].s * mi.wc, res[j].r});
@@ -1951,7 +2230,7 @@ DEV void exec_adj(const Env& e, const Instr& I, float* mask_part)
         const float* psi = slot(e, I.b_in1);
         float* gphi = slot(e, I.g_in0);
         float* gpsi = slot(e, I.g_in1);
-        for (int t = threadIdx.x; t < L; t += e.nt) { gphi[t] = 0.f; gpsi[t] = 0.f; }
+        for (int t = e.tid; t < L; t += e.nt) { gphi[t] = 0.f; gpsi[t] = 0.f; }
         __syncthreads();
         int ua = I.a, ub = I.b;
         const float *w = nullptr, *dwa = nullptr, *dwb = nullptr;
@@ -1976,25 +2255,26 @@ DEV void exec_adj(const Env& e, const Instr& I, float* mask_part)
             else until_hard(e, ua, ub, phi, psi, nullptr, g, gphi, gpsi, (int*)S(e, 0));
         } else {
             const float bl = pbeta(e, I) * LOG2E;
-            const int bmax = ub < 0 ? L - 1 : min(ub, L - 1);
+            const int ncks = until_cks(ub, L);
+            const int cku = I.mask >= 0 ? UCK_UNIT_MASK : UCK_UNIT;
             int M;
             if (until_ref(phi, psi, L, bl, e, M)) {
                 double* Ep = (double*)S(e, 0);
                 double* Eq = (double*)S(e, 2);
-                until_terms(phi, psi, L, bl, M, Ep, Eq, e.nt);
+                until_terms(phi, psi, L, bl, M, Ep, Eq, e.nt, e.tid);
                 const double* zs = (const double*)slot(e, I.coef);
-                until_smooth_adj_d(e, ua, ub, w, dwa, dwb, Ep, Eq, zs, g, gphi, gpsi, (double*)S(e, UCK_UNIT),
-                                   bmax / UCK + 1, pa, pb);
+                until_smooth_adj_d(e, ua, ub, w, dwa, dwb, Ep, Eq, zs, g, gphi, gpsi, (double*)S(e, cku), ncks,
+                                   pa, pb);
             } else {
                 SP* Ephi = (SP*)S(e, 0);
                 SP* Epsi = (SP*)S(e, 2);
-                for (int j = threadIdx.x; j < L; j += e.nt) {
+                for (int j = e.tid; j < L; j += e.nt) {
                     Ephi[j] = sp_leaf(-bl * phi[j]);
                     Epsi[j] = sp_leaf(-bl * psi[j]);
                 }
                 __syncthreads();
-                until_smooth_adj(e, ua, ub, w, dwa, dwb, Ephi, Epsi, g, gphi, gpsi, (SP*)S(e, UCK_UNIT),
-                                 bmax / UCK + 1, pa, pb);
+                until_smooth_adj(e, ua, ub, w, dwa, dwb, Ephi, Epsi, g, gphi, gpsi, (SP*)S(e, cku), ncks, pa,
+                                 pb);
             }
         }
         if (I.mslot >= 0) {
@@ -2002,7 +2282,7 @@ DEV void exec_adj(const Env& e, const Instr& I, float* mask_part)
             const float ib = is_smooth(I) ? 1.f / pbeta(e, I) : 0.f;
             const float sa = wg_sum(pa * ib, e);
             const float sb = wg_sum(pb * ib, e);
-            if (threadIdx.x == 0) { mask_part[2 * I.mslot] = sa; mask_part[2 * I.mslot + 1] = sb; }
+            if (e.tid == 0) { mask_part[2 * I.mslot] = sa; mask_part[2 * I.mslot + 1] = sb; }
         }
         // d phi / d psi are sums of scaled terms: convert the scaled psi/phi sums in place
         break;
@@ -2135,13 +2415,16 @@ __global__ void __launch_bounds__(MAX_NT) stl_exec_kernel(DevPlan plan, Batch bt
         e.D = bt.D;
         e.arena = arena;
         e.scr = arena + (size_t)nslots * Lc;
+        e.lds = GLOBAL ? smem : smem + ka.arena_floats;
         e.sh = &sh;
         e.nt = ka.nt;
+        e.tid = exec_tid();
         op_preds(e, BWD);
         for (int k = P->n_pred; k < P->n_ins; ++k) {
             const Instr I = load_words(&P->ins[k]);
             const bool x = crosses_threads(I);
             if (x) __syncthreads();
+            e.tid = exec_tid();
             exec_fwd(e, I, BWD);
             if (x) __syncthreads();
         }
@@ -2177,9 +2460,11 @@ __global__ void __launch_bounds__(MAX_NT) stl_exec_kernel(DevPlan plan, Batch bt
                 const Instr I = load_words(&P->ins[k]);
                 const bool x = crosses_threads(I);
                 if (x) __syncthreads();
+                e.tid = exec_tid();
                 exec_adj(e, I, mp);
                 if (x) __syncthreads();
             }
+            e.tid = exec_tid();
             op_dx(e, ka.dx + off * bt.D);
             __syncthreads();
         }
@@ -2257,14 +2542,19 @@ namespace stlmi {
 
 namespace stlmi {
 
-size_t scratch_floats(int Lc, int nt, int max_until_b)
+size_t scratch_floats(int Lc, int nt, int units, int until_b, bool until_masked)
 {
-    size_t s = (size_t)SCR_UNITS * Lc + 64;
-    // smooth Until checkpoints: nt * (b/UCK + 1) scaled pairs, placed at unit UCK_UNIT
-    size_t ck = (size_t)nt * (size_t)(max_until_b / UCK + 1) * 2;
-    if ((size_t)UCK_UNIT * Lc + ck + 64 > s) s = (size_t)UCK_UNIT * Lc + ck + 64;
-    return s;
+    size_t s = (size_t)units * Lc;
+    // smooth Until adjoint: nt checkpoints per UCK steps
+    if (until_b >= 0) {
+        const size_t ck = (size_t)nt * until_cks(until_b, Lc) * 2;
+        s = std::max(s, (size_t)(until_masked ? UCK_UNIT_MASK : UCK_UNIT) * Lc + ck);
+    }
+    return s + 64;
 }
+
+// LDS of the waves' export buffers (smooth Until adjoint), after the arena
+size_t until_export_bytes(int nt) { return (size_t)nt * UT_RMAX * 16; }
 
 hipError_t launch_exec(bool bwd, const DevPlan& plan, const Batch& bt, const KArgs& ka, int grid, int nt,
                        size_t lds_bytes, hipStream_t s)
@@ -2286,6 +2576,9 @@ hipError_t set_max_lds(size_t bytes)
                                         hipFuncAttributeMaxDynamicSharedMemorySize, (int)bytes);
     hipError_t e2 = hipFuncSetAttribute((const void*)stl_exec_kernel<true, false>,
                                         hipFuncAttributeMaxDynamicSharedMemorySize, (int)bytes);
+    if (e2 == hipSuccess)
+        e2 = hipFuncSetAttribute((const void*)stl_exec_kernel<true, true>,
+                                 hipFuncAttributeMaxDynamicSharedMemorySize, (int)bytes);
     return e1 != hipSuccess ? e1 : e2;
 }
 
