@@ -99,10 +99,8 @@ struct VI {
     int i;
 };
 
-DEV VI vi_best(VI a, VI b)
-{
-    return (b.v > a.v || (b.v == a.v && b.i < a.i)) ? b : a;
-}
+// a's elements come before b's
+DEV VI vi_best(VI a, VI b) { return b.v > a.v ? b : a; }
 
 struct OpSP {
     __device__ __forceinline__ SP operator()(SP a, SP b) const { return sp_add(a, b); }
@@ -139,7 +137,9 @@ struct Env {
     int L, Lc, D;
     float* arena;      // slots
     float* scr;        // op scratch
-    float* lds;        // nt UT_RMAX fp64 pairs in LDS: the export buffers of the smooth Until's adjoint
+    float* lds;        // LDS beside the slots (smooth Until): export buffers, with slots in the workspace
+                       // also the term tile and the checkpoints
+    bool global;       // slots in the workspace
     Shared* sh;
     int tid;           // threadIdx.x, opaque per instruction: what is derived from it is not kept in registers
                        // across the program (hoisted, it spilled)
@@ -172,107 +172,6 @@ DEV int div_k(int n, int K, float inv)
     return r < 0 ? q - 1 : (r >= K ? q + 1 : q);
 }
 
-// Segmented inclusive scan of leaf(p), p in [0, n), into x, in two parts with
-// a work-group barrier between them (the caller's, so that scans which do not
-// depend on each other share it) and one after.  REV scans from n-1 down.
-// head(p) starts a segment (asked in scan order).  A short serial chain per
-// thread, then DPP steps inside the wave, then the totals of the waves before
-// through LDS: the scans are bound by latency (a few elements per thread), and
-// a Hillis-Steele pass over the work-group cost two barriers and two LDS trips
-// per step (a 100-sample hard formula: forward 17.1 us, backward 37.7 us).
-// Every thread must call both parts.
-struct ScanPos {
-    int c0, c1;        // this thread's elements
-    int free;          // how many of them, in scan order, precede its first segment head
-    bool wave_carry;   // no segment head in the lanes before
-};
-
-template <bool REV, class T, class Op>
-DEV T scan_join(T before, T v, Op op)
-{
-    return REV ? op(v, before) : op(before, v);
-}
-
-// elements per thread: odd, so that the lanes' 8-byte accesses fall on distinct banks
-DEV int scan_chunk(int n, int nt) { return (n + nt - 1) / nt | 1; }
-
-template <bool REV, class T, class Op, class Leaf, class Head>
-DEV T scan_local(T* x, int n, T ident, Op op, Leaf leaf, Head head, const Env& e, int which, ScanPos& s)
-{
-    const int C = scan_chunk(n, e.nt), lane = e.tid & 63;
-    const int ct = REV ? (int)e.nt - 1 - e.tid : e.tid;
-    s.c0 = min(n, ct * C);
-    s.c1 = min(n, s.c0 + C);
-    const int m = s.c1 - s.c0;
-    s.free = m;
-    T acc = ident;
-    for (int i = 0; i < m; ++i) {
-        const int p = REV ? s.c1 - 1 - i : s.c0 + i;
-        const bool h = head(p);
-        const T v = leaf(p);
-        acc = (h || i == 0) ? v : scan_join<REV>(acc, v, op);
-        if (h) s.free = min(s.free, i);
-        x[p] = acc;
-    }
-    // wave: combine with the lane k below while no head lies in between
-    const unsigned long long hm = __ballot(s.free < m);
-    const unsigned long long upto = hm & (~0ull >> (63 - lane));
-    const int d = upto ? lane - (63 - __builtin_clzll(upto)) : lane;
-#define STLMI_SCAN_STEP(CTRL, COND)                    \
-    {                                                  \
-        const T b = dpp8<CTRL>(acc);                   \
-        if (COND) acc = scan_join<REV>(b, acc, op);    \
-    }
-    STLMI_SCAN_STEP(0x111, (lane & 15) >= 1 && d >= 1)
-    STLMI_SCAN_STEP(0x112, (lane & 15) >= 2 && d >= 2)
-    STLMI_SCAN_STEP(0x114, (lane & 15) >= 4 && d >= 4)
-    STLMI_SCAN_STEP(0x118, (lane & 15) >= 8 && d >= 8)
-    STLMI_SCAN_STEP(0x142, (lane & 16) && d >= (lane & 15) + 1)
-    STLMI_SCAN_STEP(0x143, lane >= 32 && d >= lane - 31)
-#undef STLMI_SCAN_STEP
-    s.wave_carry = (hm & ((1ull << lane) - 1)) == 0;
-    if (lane == 63) {
-        reinterpret_cast<T*>(e.sh->scan)[which * 8 + (e.tid >> 6)] = acc;
-        e.sh->flag[which * 8 + (e.tid >> 6)] = hm != 0;
-    }
-    const T ex = dpp8<0x138>(acc);
-    return lane == 0 ? ident : ex;
-}
-
-template <bool REV, class T, class Op>
-DEV void scan_carry(T* x, T carry, Op op, const Env& e, int which, const ScanPos& s)
-{
-    const int w = e.tid >> 6, lane = e.tid & 63;
-    if (e.nt > 64) {
-        // lane q % 8 scans the totals of waves 0 .. q (wave w needs those of 0 .. w-1)
-        const int q = lane & 7;
-        T c = reinterpret_cast<const T*>(e.sh->scan)[which * 8 + q];
-        const unsigned hm = (unsigned)__ballot(e.sh->flag[which * 8 + q] != 0) & 0xffu & ((2u << q) - 1u);
-        const int d = hm ? q - (31 - __builtin_clz(hm)) : q;
-#define STLMI_CARRY_STEP(CTRL, K)                        \
-    {                                                  \
-        const T b = dpp8<CTRL>(c);                     \
-        if (q >= K && d >= K) c = scan_join<REV>(b, c, op); \
-    }
-        STLMI_CARRY_STEP(0x111, 1)
-        STLMI_CARRY_STEP(0x112, 2)
-        STLMI_CARRY_STEP(0x114, 4)
-#undef STLMI_CARRY_STEP
-        int cw[2];
-        __builtin_memcpy(cw, &c, 8);
-        const int src = __builtin_amdgcn_readfirstlane(max(w - 1, 0));
-        cw[0] = __builtin_amdgcn_readlane(cw[0], src);
-        cw[1] = __builtin_amdgcn_readlane(cw[1], src);
-        __builtin_memcpy(&c, cw, 8);
-        if (s.wave_carry && w > 0) carry = lane == 0 ? c : scan_join<REV>(c, carry, op);
-    }
-    if (e.tid == 0) return;        // nothing comes before
-    for (int i = 0; i < s.free; ++i) {
-        const int p = REV ? s.c1 - 1 - i : s.c0 + i;
-        x[p] = scan_join<REV>(carry, x[p], op);
-    }
-}
-
 // segment heads of the van Herk blocks: p % K == 0 upwards, p % K == K-1 (and
 // the last position) downwards; K <= 0: one segment
 struct BlockHead {
@@ -298,18 +197,172 @@ struct HeadDown : BlockHead {
     }
 };
 
+// Segmented inclusive scan of leaf(p), p in [0, n), into x, in two parts with
+// a work-group barrier between them (the caller's, so that scans which do not
+// depend on each other share it) and one after.  REV scans from n-1 down.
+// head(p) starts a segment (asked in scan order by each lane).  Each wave takes
+// a contiguous range of the elements and scans it a tile at a time: up to
+// SCAN_E consecutive elements per lane, DPP steps over the lanes, a running
+// carry between tiles; the totals of the waves before are then joined to what
+// precedes a wave's first head.  The scans are bound by latency in short
+// trajectories (a Hillis-Steele pass over the work-group cost two barriers and
+// two LDS trips per step: a 100-sample hard formula took 17.1 us forward and
+// 37.7 us backward) and, with slots in the workspace, by the lines a wave's
+// accesses touch (contiguous chunks per thread took 1.4M cycles for a window of
+// an 8,192-sample trajectory).  The order of the additions depends on n and
+// the work-group size only, not on where the slots lie.
+// Every thread must call both parts.
+constexpr int SCAN_E = 4;
+
+struct ScanPos {
+    int c0, c1;        // the wave's elements
+    int free;          // how many of them, in scan order, precede its first segment head
+};
+
+template <bool REV, class T, class Op>
+DEV T scan_join(T before, T v, Op op)
+{
+    return REV ? op(v, before) : op(before, v);
+}
+
+template <class T>
+DEV T readlane8(T v, int l)
+{
+    int w[2];
+    __builtin_memcpy(w, &v, 8);
+    w[0] = __builtin_amdgcn_readlane(w[0], l);
+    w[1] = __builtin_amdgcn_readlane(w[1], l);
+    __builtin_memcpy(&v, w, 8);
+    return v;
+}
+
+// inclusive scan over the lanes of a wave within the segments that begin at
+// the lanes of hm; d: lanes since the last head at or before this one
+template <bool REV, class T, class Op>
+DEV T scan_wave(T acc, unsigned long long hm, int lane, Op op)
+{
+    const unsigned long long upto = hm & (~0ull >> (63 - lane));
+    const int d = upto ? lane - (63 - __builtin_clzll(upto)) : lane;
+#define STLMI_SCAN_STEP(CTRL, COND)                    \
+    {                                                  \
+        const T b = dpp8<CTRL>(acc);                   \
+        if (COND) acc = scan_join<REV>(b, acc, op);    \
+    }
+    const int dr = min(lane & 15, d);
+    STLMI_SCAN_STEP(0x111, dr >= 1)
+    STLMI_SCAN_STEP(0x112, dr >= 2)
+    STLMI_SCAN_STEP(0x114, dr >= 4)
+    STLMI_SCAN_STEP(0x118, dr >= 8)
+    STLMI_SCAN_STEP(0x142, (lane & 16) && d >= (lane & 15) + 1)
+    STLMI_SCAN_STEP(0x143, lane >= 32 && d >= lane - 31)
+#undef STLMI_SCAN_STEP
+    return acc;
+}
+
+template <bool REV, int E, class T, class Op, class Leaf, class Head>
+DEV void scan_local_e(T* x, int n, T ident, Op op, Leaf leaf, Head head, const Env& e, int which, ScanPos& s)
+{
+    // (E = 1: one tile per wave; the work-group size is a power of two)
+    const int nw = e.nt >> 6, w = e.tid >> 6, lane = e.tid & 63;
+    const int seg = E == 1 ? 64 : ((n + E * e.nt - 1) >> __builtin_ctz(E * e.nt)) * (64 * E);
+    const int cw = REV ? nw - 1 - w : w;
+    s.c0 = min(n, cw * seg);
+    s.c1 = min(n, s.c0 + seg);
+    const int m = s.c1 - s.c0;
+    auto pos = [&](int i) { return REV ? s.c1 - 1 - i : s.c0 + i; };
+    s.free = m;
+    T run = ident, v[E];
+    bool seen = false;
+#pragma unroll
+    for (int j = 0; j < E; ++j) v[j] = lane * E + j < m ? leaf(pos(lane * E + j)) : ident;
+#pragma unroll 1
+    for (int i0 = 0; i0 < (E == 1 ? 1 : m); i0 += 64 * E) {
+        const int i = i0 + lane * E;
+        T vn[E];                                   // the next tile's leaves, read ahead
+        if (E > 1) {
+#pragma unroll
+            for (int j = 0; j < E; ++j) vn[j] = i + 64 * E + j < m ? leaf(pos(i + 64 * E + j)) : ident;
+        }
+        int first = E;                             // this lane's first head
+        Head h = head;
+#pragma unroll
+        for (int j = 0; j < E; ++j) {
+            const bool hj = i + j < m && h(pos(i + j));
+            if (j > 0 && !hj) v[j] = scan_join<REV>(v[j - 1], v[j], op);
+            if (hj) first = min(first, j);
+        }
+        const unsigned long long hm = __ballot(first < E);
+        const T acc = scan_wave<REV>(v[E - 1], hm, lane, op);
+        T carry = dpp8<0x138>(acc);
+        const bool open = (hm & ((1ull << lane) - 1)) == 0;      // no head in the lanes before
+        if (open && i0 > 0) carry = lane == 0 ? run : scan_join<REV>(run, carry, op);
+        const int nf = i0 + lane > 0 ? first : 0;
+#pragma unroll
+        for (int j = 0; j < E; ++j) {
+            if (j < nf) v[j] = scan_join<REV>(carry, v[j], op);
+            if (i + j < m) x[pos(i + j)] = v[j];
+        }
+        if (!seen && hm) {
+            const int fl = __builtin_ctzll(hm);
+            s.free = i0 + fl * E + __builtin_amdgcn_readlane(first, fl);
+            seen = true;
+        }
+        run = readlane8(v[E - 1], 63);
+        if (E > 1) {
+#pragma unroll
+            for (int j = 0; j < E; ++j) v[j] = vn[j];
+        }
+    }
+    if (lane == 0) {
+        reinterpret_cast<T*>(e.sh->scan)[which * 8 + w] = run;
+        e.sh->flag[which * 8 + w] = seen;
+    }
+}
+
+template <bool REV, class T, class Op, class Leaf, class Head>
+DEV void scan_local(T* x, int n, T ident, Op op, Leaf leaf, Head head, const Env& e, int which, ScanPos& s)
+{
+    if (n <= e.nt) scan_local_e<REV, 1>(x, n, ident, op, leaf, head, e, which, s);
+    else scan_local_e<REV, SCAN_E>(x, n, ident, op, leaf, head, e, which, s);
+}
+
+template <bool REV, class T, class Op>
+DEV void scan_carry(T* x, Op op, const Env& e, int which, const ScanPos& s)
+{
+    const int w = e.tid >> 6, lane = e.tid & 63;
+    if (w == 0) return;                            // nothing comes before
+    // lane q % 8 scans the totals of waves 0 .. q (wave w needs those of 0 .. w-1)
+    const int q = lane & 7;
+    T c = reinterpret_cast<const T*>(e.sh->scan)[which * 8 + q];
+    const unsigned hm = (unsigned)__ballot(e.sh->flag[which * 8 + q] != 0) & 0xffu & ((2u << q) - 1u);
+    const int d = hm ? q - (31 - __builtin_clz(hm)) : q;
+#define STLMI_CARRY_STEP(CTRL, K)                           \
+    {                                                       \
+        const T b = dpp8<CTRL>(c);                          \
+        if (q >= K && d >= K) c = scan_join<REV>(b, c, op); \
+    }
+    STLMI_CARRY_STEP(0x111, 1)
+    STLMI_CARRY_STEP(0x112, 2)
+    STLMI_CARRY_STEP(0x114, 4)
+#undef STLMI_CARRY_STEP
+    c = readlane8(c, __builtin_amdgcn_readfirstlane(w - 1));
+    for (int i = lane; i < s.free; i += 64) {
+        const int p = REV ? s.c1 - 1 - i : s.c0 + i;
+        x[p] = scan_join<REV>(c, x[p], op);
+    }
+}
+
 // block prefixes and suffixes of the same leaves (K <= 0: suffixes of the
 // whole range only)
 template <class T, class Op, class Leaf>
 DEV void scan_blocks(T* pre, T* suf, int n, int K, T ident, Op op, Leaf leaf, const Env& e)
 {
     ScanPos sp, ss;
-    T cp = ident;
-    const T cs = scan_local<true>(suf, n, ident, op, leaf, HeadDown(K, n), e, 0, ss);
-    if (K > 0) cp = scan_local<false>(pre, n, ident, op, leaf, HeadUp(K, n), e, 1, sp);
+    scan_local<true>(suf, n, ident, op, leaf, HeadDown(K, n), e, 0, ss);
+    if (K > 0) scan_local<false>(pre, n, ident, op, leaf, HeadUp(K, n), e, 1, sp);
     __syncthreads();
-    scan_carry<true>(suf, cs, op, e, 0, ss);
-    if (K > 0) scan_carry<false>(pre, cp, op, e, 1, sp);
+    scan_carry<true>(suf, op, e, 0, ss);
+    if (K > 0) scan_carry<false>(pre, op, e, 1, sp);
     __syncthreads();
 }
 
@@ -318,9 +371,9 @@ template <bool REV, class T, class Op, class Leaf, class Head>
 DEV void scan_one(T* x, int n, T ident, Op op, Leaf leaf, Head head, const Env& e)
 {
     ScanPos s;
-    const T c = scan_local<REV>(x, n, ident, op, leaf, head, e, 0, s);
+    scan_local<REV>(x, n, ident, op, leaf, head, e, 0, s);
     __syncthreads();
-    scan_carry<REV>(x, c, op, e, 0, s);
+    scan_carry<REV>(x, op, e, 0, s);
     __syncthreads();
 }
 
@@ -377,7 +430,9 @@ DEV T load_words(const T* p)
 // The predicates are evaluated for the whole formula at once: a row of x is
 // read once (per predicate it cost 0.5 to 1 us of latency in a short
 // trajectory) and feeds every predicate.
-constexpr int PRED_TB = 4;    // rows per thread and pass
+constexpr int PRED_TB = 4;    // timesteps per thread and pass of the pointwise loops where a thread has
+                              // several: their reads are in flight together (the compiler cannot move
+                              // them past the stores)
 
 template <int D>
 DEV void load_row(const float* p, bool vec, float (&r)[D])
@@ -438,23 +493,23 @@ DEV float pred_value(int kind, const float* cf, int D, Row x)
     return cf[2] * (sqrtf(norm_rows(cf, (int)cf[0], D, x, z)) - cf[1]);
 }
 
-template <int D>
+template <int D, int TB>
 DEV void preds_fwd(const Env& e, bool bwdmap)
 {
     const DevPlan& P = *e.P;
     const int nt = e.nt;
     const bool vec = vec_rows<D>(e.x);
-    for (int t0 = e.tid; t0 < e.L; t0 += PRED_TB * nt) {
-        float x[PRED_TB][D];
+    for (int t0 = e.tid; t0 < e.L; t0 += TB * nt) {
+        float x[TB][D];
 #pragma unroll
-        for (int j = 0; j < PRED_TB; ++j)
+        for (int j = 0; j < TB; ++j)
             if (t0 + j * nt < e.L) load_row<D>(e.x + (size_t)(t0 + j * nt) * D, vec, x[j]);
 #pragma unroll 2
         for (int p = 0; p < P.n_pred; ++p) {
             const PredRef I = load_words(&P.pred[p]);
             float* out = slot(e, bwdmap ? I.b_out : I.f_out);
 #pragma unroll
-            for (int j = 0; j < PRED_TB; ++j)
+            for (int j = 0; j < TB; ++j)
                 if (t0 + j * nt < e.L) out[t0 + j * nt] = pred_value(I.kind, P.coef + I.coef, D, x[j]);
         }
     }
@@ -462,11 +517,12 @@ DEV void preds_fwd(const Env& e, bool bwdmap)
 
 DEV void op_preds(const Env& e, bool bwdmap)
 {
+    const bool one = e.L <= e.nt;
     switch (e.D) {
-    case 1: preds_fwd<1>(e, bwdmap); return;
-    case 2: preds_fwd<2>(e, bwdmap); return;
-    case 3: preds_fwd<3>(e, bwdmap); return;
-    case 4: preds_fwd<4>(e, bwdmap); return;
+    case 1: one ? preds_fwd<1, 1>(e, bwdmap) : preds_fwd<1, PRED_TB>(e, bwdmap); return;
+    case 2: one ? preds_fwd<2, 1>(e, bwdmap) : preds_fwd<2, PRED_TB>(e, bwdmap); return;
+    case 3: one ? preds_fwd<3, 1>(e, bwdmap) : preds_fwd<3, PRED_TB>(e, bwdmap); return;
+    case 4: one ? preds_fwd<4, 1>(e, bwdmap) : preds_fwd<4, PRED_TB>(e, bwdmap); return;
     }
     const DevPlan& P = *e.P;
     for (int p = 0; p < P.n_pred; ++p) {
@@ -477,67 +533,80 @@ DEV void op_preds(const Env& e, bool bwdmap)
     }
 }
 
-// d/dx of all predicates: dx[t, d] = sum_p dmu_p/dx_d * g_p[t]
+// d/dx of the predicates: dx[t, d] = sum_p dmu_p/dx_d * g_p[t]; one predicate's part
 template <class Row, class Acc>
-DEV void pred_dx(const Env& e, int D, int t, Row x, Acc& acc)
+DEV void pred_dx(int kind, const float* cf, int D, float g, Row x, Acc& acc)
 {
-    const DevPlan& P = *e.P;
-    for (int p = 0; p < P.n_pred; ++p) {
-        const PredRef I = load_words(&P.pred[p]);
-        const float g = slot(e, I.g_out)[t];
-        const float* cf = P.coef + I.coef;
-        if (I.kind == K_LIN) {
-            for (int d = 0; d < D; ++d) acc[d] = fmaf(cf[1 + d], g, acc[d]);
-            continue;
-        }
-        const int m = (int)cf[0];
-        float z[4];
-        const float q = norm_rows(cf, m, D, x, z);
-        if (q > 0.f) {
-            const float k = cf[2] * g / sqrtf(q);
-            for (int d = 0; d < D; ++d) {
-                float v = 0.f;
+    if (kind == K_LIN) {
+        for (int d = 0; d < D; ++d) acc[d] = fmaf(cf[1 + d], g, acc[d]);
+        return;
+    }
+    const int m = (int)cf[0];
+    float z[4];
+    const float q = norm_rows(cf, m, D, x, z);
+    if (q > 0.f) {
+        const float k = cf[2] * g / sqrtf(q);
+        for (int d = 0; d < D; ++d) {
+            float v = 0.f;
 #pragma unroll
-                for (int i = 0; i < 4; ++i)
-                    if (i < m) v = fmaf(cf[7 + i * D + d], z[i], v);
-                acc[d] = fmaf(k, v, acc[d]);
-            }
+            for (int i = 0; i < 4; ++i)
+                if (i < m) v = fmaf(cf[7 + i * D + d], z[i], v);
+            acc[d] = fmaf(k, v, acc[d]);
         }
     }
 }
 
-template <int D>
+template <int D, int TB>
 DEV void preds_dx(const Env& e, float* dx)
 {
+    const DevPlan& P = *e.P;
     const bool vx = vec_rows<D>(e.x), vd = vec_rows<D>(dx);
-    for (int t = e.tid; t < e.L; t += e.nt) {
-        float x[D], acc[D];
-        load_row<D>(e.x + (size_t)t * D, vx, x);
+    for (int t0 = e.tid; t0 < e.L; t0 += TB * e.nt) {
+        float x[TB][D], acc[TB][D];
 #pragma unroll
-        for (int d = 0; d < D; ++d) acc[d] = 0.f;
-        pred_dx(e, D, t, x, acc);
-        store_row<D>(dx + (size_t)t * D, vd, acc);
+        for (int j = 0; j < TB; ++j) {
+#pragma unroll
+            for (int d = 0; d < D; ++d) acc[j][d] = 0.f;
+            if (t0 + j * e.nt < e.L) load_row<D>(e.x + (size_t)(t0 + j * e.nt) * D, vx, x[j]);
+        }
+        for (int p = 0; p < P.n_pred; ++p) {
+            const PredRef I = load_words(&P.pred[p]);
+            const float* gs = slot(e, I.g_out);
+            float g[TB];
+#pragma unroll
+            for (int j = 0; j < TB; ++j) g[j] = t0 + j * e.nt < e.L ? gs[t0 + j * e.nt] : 0.f;
+#pragma unroll
+            for (int j = 0; j < TB; ++j)
+                if (t0 + j * e.nt < e.L) pred_dx(I.kind, P.coef + I.coef, D, g[j], x[j], acc[j]);
+        }
+#pragma unroll
+        for (int j = 0; j < TB; ++j)
+            if (t0 + j * e.nt < e.L) store_row<D>(dx + (size_t)(t0 + j * e.nt) * D, vd, acc[j]);
     }
 }
 
 DEV void op_dx(const Env& e, float* dx)
 {
+    const bool one = e.L <= e.nt;
     switch (e.D) {
-    case 1: preds_dx<1>(e, dx); return;
-    case 2: preds_dx<2>(e, dx); return;
-    case 3: preds_dx<3>(e, dx); return;
-    case 4: preds_dx<4>(e, dx); return;
+    case 1: one ? preds_dx<1, 1>(e, dx) : preds_dx<1, PRED_TB>(e, dx); return;
+    case 2: one ? preds_dx<2, 1>(e, dx) : preds_dx<2, PRED_TB>(e, dx); return;
+    case 3: one ? preds_dx<3, 1>(e, dx) : preds_dx<3, PRED_TB>(e, dx); return;
+    case 4: one ? preds_dx<4, 1>(e, dx) : preds_dx<4, PRED_TB>(e, dx); return;
     }
     for (int t = e.tid; t < e.L; t += e.nt) {
         float acc[MAX_D];
 #pragma unroll
         for (int d = 0; d < MAX_D; ++d) acc[d] = 0.f;
-        pred_dx(e, e.D, t, e.x + (size_t)t * e.D, acc);
+        for (int p = 0; p < e.P->n_pred; ++p) {
+            const PredRef I = load_words(&e.P->pred[p]);
+            pred_dx(I.kind, e.P->coef + I.coef, e.D, slot(e, I.g_out)[t], e.x + (size_t)t * e.D, acc);
+        }
         for (int d = 0; d < e.D; ++d) dx[(size_t)t * e.D + d] = acc[d];
     }
 }
 
-template <int N>
+template <int N, int TB>
 DEV void nary_fwd(const Env& e, const Instr& I, const int8_t* ch, float* out)
 {
     const float sg = (I.flags & F_MIN) ? -1.f : 1.f;
@@ -546,43 +615,52 @@ DEV void nary_fwd(const Env& e, const Instr& I, const int8_t* ch, float* out)
     const float* c[N];
 #pragma unroll
     for (int k = 0; k < N; ++k) c[k] = slot(e, ch[k]);
-    for (int t = e.tid; t < e.L; t += e.nt) {
-        float v[N], m = -INFINITY;
+    for (int tb = e.tid; tb < e.L; tb += TB * e.nt) {
+        float vv[TB][N];
 #pragma unroll
-        for (int k = 0; k < N; ++k) v[k] = sg * c[k][t];
-        if (!smooth) {
-            m = v[0];
+        for (int j = 0; j < TB; ++j)
 #pragma unroll
-            for (int k = 1; k < N; ++k)
-                if (v[k] > m) m = v[k];
-            out[t] = sg * m;
-            continue;
+            for (int k = 0; k < N; ++k) vv[j][k] = tb + j * e.nt < e.L ? sg * c[k][tb + j * e.nt] : 0.f;
+#pragma unroll
+        for (int j = 0; j < TB; ++j) {
+            const int t = tb + j * e.nt;
+            if (t >= e.L) break;
+            const float(&v)[N] = vv[j];
+            float m = v[0];
+            if (!smooth) {
+#pragma unroll
+                for (int k = 1; k < N; ++k)
+                    if (v[k] > m) m = v[k];
+                out[t] = sg * m;
+                continue;
+            }
+#pragma unroll
+            for (int k = 1; k < N; ++k) m = fmaxf(m, v[k]);
+            float s0 = 0.f, s1 = 0.f;
+#pragma unroll
+            for (int k = 0; k < N; ++k) {
+                const float q = exp2f((v[k] - m) * bl);
+                s0 += q;
+                s1 = fmaf(q, v[k], s1);
+            }
+            // softmax-weighted mean of the oriented values, or logsumexp (Sec. III-C)
+            out[t] = sg * (soft ? s1 / s0 : m + log2f(s0) / bl);
         }
-#pragma unroll
-        for (int k = 0; k < N; ++k) m = fmaxf(m, v[k]);
-        float s0 = 0.f, s1 = 0.f;
-#pragma unroll
-        for (int k = 0; k < N; ++k) {
-            const float q = exp2f((v[k] - m) * bl);
-            s0 += q;
-            s1 = fmaf(q, v[k], s1);
-        }
-        // softmax-weighted mean of the oriented values, or logsumexp (Sec. III-C)
-        out[t] = sg * (soft ? s1 / s0 : m + log2f(s0) / bl);
     }
 }
 
 DEV void op_nary_fwd(const Env& e, const Instr& I, const int8_t* ch, float* out)
 {
+    const bool one = e.L <= e.nt;
     switch (I.nch) {
-    case 1: nary_fwd<1>(e, I, ch, out); break;
-    case 2: nary_fwd<2>(e, I, ch, out); break;
-    case 3: nary_fwd<3>(e, I, ch, out); break;
-    default: nary_fwd<4>(e, I, ch, out); break;
+    case 1: one ? nary_fwd<1, 1>(e, I, ch, out) : nary_fwd<1, PRED_TB>(e, I, ch, out); break;
+    case 2: one ? nary_fwd<2, 1>(e, I, ch, out) : nary_fwd<2, PRED_TB>(e, I, ch, out); break;
+    case 3: one ? nary_fwd<3, 1>(e, I, ch, out) : nary_fwd<3, PRED_TB>(e, I, ch, out); break;
+    default: one ? nary_fwd<4, 1>(e, I, ch, out) : nary_fwd<4, PRED_TB>(e, I, ch, out); break;
     }
 }
 
-template <int N>
+template <int N, int TB>
 DEV void nary_bwd(const Env& e, const Instr& I)
 {
     const float sg = (I.flags & F_MIN) ? -1.f : 1.f;
@@ -597,45 +675,58 @@ DEV void nary_bwd(const Env& e, const Instr& I)
         c[k] = slot(e, I.b_ch[k]);
         gc[k] = slot(e, I.g_ch[k]);
     }
-    for (int t = e.tid; t < e.L; t += e.nt) {
-        const float gt = g[t];
-        float v[N];
+    for (int tb = e.tid; tb < e.L; tb += TB * e.nt) {
+        float vv[TB][N], gg[TB], oo[TB];
 #pragma unroll
-        for (int k = 0; k < N; ++k) v[k] = sg * c[k][t];
-        if (!smooth) {
-            int kb = 0;
-            float best = v[0];
+        for (int j = 0; j < TB; ++j) {
+            const int t = tb + j * e.nt;
+            const bool in = t < e.L;
+            gg[j] = in ? g[t] : 0.f;
+            oo[j] = in && smooth ? sg * out[t] : 0.f;
 #pragma unroll
-            for (int k = 1; k < N; ++k)
-                if (v[k] > best) { best = v[k]; kb = k; }
+            for (int k = 0; k < N; ++k) vv[j][k] = in ? sg * c[k][t] : 0.f;
+        }
 #pragma unroll
-            for (int k = 0; k < N; ++k) gc[k][t] = (k == kb) ? gt : 0.f;
-        } else if (soft) {
-            // d r / d v_k = p_k (1 + beta (v_k - r)), r = sg out
-            const float r = sg * out[t], beta = bl / LOG2E;
-            float m = -INFINITY, s0 = 0.f;
+        for (int j = 0; j < TB; ++j) {
+            const int t = tb + j * e.nt;
+            if (t >= e.L) break;
+            const float(&v)[N] = vv[j];
+            const float gt = gg[j], o = oo[j];
+            if (!smooth) {
+                int kb = 0;
+                float best = v[0];
 #pragma unroll
-            for (int k = 0; k < N; ++k) m = fmaxf(m, v[k]);
+                for (int k = 1; k < N; ++k)
+                    if (v[k] > best) { best = v[k]; kb = k; }
 #pragma unroll
-            for (int k = 0; k < N; ++k) s0 += exp2f((v[k] - m) * bl);
+                for (int k = 0; k < N; ++k) gc[k][t] = (k == kb) ? gt : 0.f;
+            } else if (soft) {
+                // d r / d v_k = p_k (1 + beta (v_k - r)), r = sg out
+                const float beta = bl / LOG2E;
+                float m = v[0], s0 = 0.f;
 #pragma unroll
-            for (int k = 0; k < N; ++k)
-                gc[k][t] = gt * (exp2f((v[k] - m) * bl) / s0) * (1.f + beta * (v[k] - r));
-        } else {
-            const float o = sg * out[t];
+                for (int k = 1; k < N; ++k) m = fmaxf(m, v[k]);
 #pragma unroll
-            for (int k = 0; k < N; ++k) gc[k][t] = gt * exp2f((v[k] - o) * bl);
+                for (int k = 0; k < N; ++k) s0 += exp2f((v[k] - m) * bl);
+#pragma unroll
+                for (int k = 0; k < N; ++k)
+                    gc[k][t] = gt * (exp2f((v[k] - m) * bl) / s0) * (1.f + beta * (v[k] - o));
+            } else {
+#pragma unroll
+                for (int k = 0; k < N; ++k) gc[k][t] = gt * exp2f((v[k] - o) * bl);
+            }
         }
     }
 }
 
 DEV void op_nary_bwd(const Env& e, const Instr& I)
 {
+    const bool one = e.L <= e.nt;
     switch (I.nch) {
-    case 1: nary_bwd<1>(e, I); break;
-    case 2: nary_bwd<2>(e, I); break;
-    case 3: nary_bwd<3>(e, I); break;
-    default: nary_bwd<4>(e, I); break;
+    case 1: one ? nary_bwd<1, 1>(e, I) : nary_bwd<1, PRED_TB>(e, I); break;
+    case 2: one ? nary_bwd<2, 1>(e, I) : nary_bwd<2, PRED_TB>(e, I); break;
+    case 3: one ? nary_bwd<3, 1>(e, I) : nary_bwd<3, PRED_TB>(e, I); break;
+    default: one ? nary_bwd<4, 1>(e, I) : nary_bwd<4, PRED_TB>(e, I); break;
     }
 }
 
@@ -2415,6 +2506,7 @@ __global__ void __launch_bounds__(MAX_NT) stl_exec_kernel(DevPlan plan, Batch bt
         e.D = bt.D;
         e.arena = arena;
         e.scr = arena + (size_t)nslots * Lc;
+        e.global = GLOBAL;
         e.lds = GLOBAL ? smem : smem + ka.arena_floats;
         e.sh = &sh;
         e.nt = ka.nt;
