@@ -20,7 +20,8 @@
 
 namespace stlmi {
 size_t scratch_floats(int Lc, int nt, int units, int until_b, bool until_masked);
-size_t until_export_bytes(int nt);
+int until_tile_len(int nt, int until_b, bool until_masked);
+size_t until_lds_bytes(int nt, int until_b, bool bwd, int tile, int Lc);
 hipError_t launch_exec(bool bwd, const DevPlan& plan, const struct Batch& bt, const struct KArgs& ka, int grid,
                        int nt, size_t lds_bytes, hipStream_t s);
 hipError_t set_max_lds(size_t bytes);
@@ -99,6 +100,7 @@ struct Geom {
     bool global;
     size_t arena_floats;
     size_t lds_bytes;
+    int tile;               // positions of the smooth Until's LDS tile (slots in the workspace)
     size_t ws_bytes;        // total workspace
     size_t off_part;        // mask partials (bytes)
     size_t off_arena;       // global arenas (bytes)
@@ -139,13 +141,20 @@ stl_status geometry(const stl_plan* plan, const stl_batch* bt, const stl_launch*
     if (bt->T < 1 || bt->T > (1 << 24)) return fail(STL_E_SHAPE, "T must be in [1, 2^24]");
     int Lc = (int)((bt->T + 3) / 4 * 4);
     const int nslots = bwd ? dp.n_slots_bwd : dp.n_slots_fwd;
-    const int ub = bwd && plan->until_b >= 0 ? (int)std::min<int64_t>(plan->until_b, bt->T) : -1;
+    const int ub = plan->until_b >= 0 ? (int)std::min<int64_t>(plan->until_b, bt->T) : -1;
     auto scratch = [&](int threads) {
-        return scratch_floats(Lc, threads, plan->scr_units[bwd], ub, plan->until_masked);
+        return scratch_floats(Lc, threads, plan->scr_units[bwd], bwd ? ub : -1, plan->until_masked);
+    };
+    // (a tile whose checkpoints do not fit beside it is not used)
+    auto until_tile = [&](int threads) {
+        const int t = until_tile_len(threads, ub, plan->until_masked);
+        return until_lds_bytes(threads, ub, bwd, t, Lc) <= di.lds_max ? t : 0;
+    };
+    auto until_lds = [&](int threads, bool glob) {
+        return until_lds_bytes(threads, ub, bwd, glob ? until_tile(threads) : 0, Lc);
     };
     size_t arena = (size_t)nslots * Lc + scratch(nt);
-    auto export_bytes = [&](int threads) { return ub >= 0 ? until_export_bytes(threads) : 0; };
-    size_t lds = arena * sizeof(float) + export_bytes(nt);
+    size_t lds = arena * sizeof(float) + until_lds(nt, false);
     bool global = (cfg && cfg->global_slots) || lds > di.lds_max;
     if (!(cfg && cfg->threads) && bt->B < di.cus) {
         // fewer trajectories than compute units (one work-group each): size
@@ -155,7 +164,7 @@ stl_status geometry(const stl_plan* plan, const stl_batch* bt, const stl_launch*
         // push the arena out of LDS
         const int want = bt->T <= 64 ? 64 : bt->T <= 128 ? 128 : bt->T <= 256 ? 256 : 512;
         const size_t a2 = (size_t)nslots * Lc + scratch(want);
-        const size_t l2 = a2 * sizeof(float) + export_bytes(want);
+        const size_t l2 = a2 * sizeof(float) + until_lds(want, false);
         const bool g2 = (cfg && cfg->global_slots) || l2 > di.lds_max;
         if (want < 256 || g2 == global) {
             nt = want;
@@ -182,7 +191,8 @@ stl_status geometry(const stl_plan* plan, const stl_batch* bt, const stl_launch*
     g->Lc = Lc;
     g->global = global;
     g->arena_floats = arena;
-    g->lds_bytes = global ? export_bytes(nt) : lds;
+    g->lds_bytes = global ? until_lds(nt, true) : lds;
+    g->tile = global ? until_tile(nt) : 0;
     g->mx = false;
     g->mx_lds = 0;
     g->off_handed = g->off_mxtr = g->off_mxflag = g->off_mxrange = g->off_mxheads = 0;
@@ -368,6 +378,7 @@ static stl_status run(const stl_plan* plan, const stl_batch* bt, const float* pa
     ka.counter = (int*)wsb;
     ka.persistent = g.persistent;
     ka.nt = g.nt;
+    ka.tile = g.tile;
     // dense node traces are [n_nodes][B*T]; a ragged batch's N_total (offsets[B])
     // is read by the kernel itself
     if (nodes && !bt->offsets) ka.n_total = bt->B * bt->T;

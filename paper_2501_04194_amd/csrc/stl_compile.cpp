@@ -373,43 +373,43 @@ extern "C" stl_status stl_compile(const stl_node* nodes, int32_t n_nodes, const 
         for (int k = 0; k < n; ++k)
             if (!pred(k)) fslot[k] = fa.get(k, parent[k] < 0 ? n : parent[k]);
     }
-    // backward map: values get their own slots (kept through the adjoint sweep);
-    // adjoints are allocated over the reverse sweep.  Step numbering for the
-    // sweep: step of adjoint(k) = n - 1 - k; predicates' adjoints live to the
-    // final d/dx stage (step n).
+    // backward map: value k has slot k, from the recompute through the adjoint
+    // sweep until its last reader (its own adjoint step, n - 1 - k; a
+    // predicate's: its parent's step).  Adjoint k is written at its parent's
+    // step and read at its own (a predicate's: at the final d/dx stage, step n);
+    // it takes the slot of a value or adjoint whose last reader came before.
     SlotAlloc ga;
     std::vector<int> gslot(n, -1);
-    for (int k = n - 1; k >= 0; --k) {
-        int def = parent[k] < 0 ? -1 : (n - 1 - parent[k]);
+    for (int k = 0; k < n; ++k) {
         const bool pred = B.ins[k].kind == K_LIN || B.ins[k].kind == K_NORM;
-        int last = pred ? n : (n - 1 - k);
-        gslot[k] = ga.get(def, last);   // the parent's own slot stays busy through its step
+        const int last = pred ? (parent[k] < 0 ? -1 : n - 1 - parent[k]) : n - 1 - k;
+        ga.free_at.push_back(last + 1);
     }
-    // adjoints written by a parent must not share a slot with the parent's own
-    // adjoint: the allocation above already keeps the parent's slot busy
-    // through its own step (n-1-parent), and children are defined at def+1.
-    const int nval = n;
-    const int nadj = (int)ga.free_at.size();
+    for (int k = n - 1; k >= 0; --k) {
+        const int def = parent[k] < 0 ? -1 : n - 1 - parent[k];
+        const bool pred = B.ins[k].kind == K_LIN || B.ins[k].kind == K_NORM;
+        gslot[k] = ga.get(def, pred ? n : n - 1 - k);
+    }
     for (int k = 0; k < n; ++k) {
         Instr& I = B.ins[k];
         const auto& ch = B.kids[k];
         I.f_out = (int8_t)fslot[k];
         I.b_out = (int8_t)k;
-        I.g_out = (int8_t)(nval + gslot[k]);
+        I.g_out = (int8_t)gslot[k];
         if (I.kind == K_NARY) {
             for (int j = 0; j < (int)ch.size(); ++j) {
                 I.f_ch[j] = (int8_t)fslot[ch[j]];
                 I.b_ch[j] = (int8_t)ch[j];
-                I.g_ch[j] = (int8_t)(nval + gslot[ch[j]]);
+                I.g_ch[j] = (int8_t)gslot[ch[j]];
             }
         } else {
-            if (ch.size() > 0) { I.f_in0 = (int8_t)fslot[ch[0]]; I.b_in0 = (int8_t)ch[0]; I.g_in0 = (int8_t)(nval + gslot[ch[0]]); }
-            if (ch.size() > 1) { I.f_in1 = (int8_t)fslot[ch[1]]; I.b_in1 = (int8_t)ch[1]; I.g_in1 = (int8_t)(nval + gslot[ch[1]]); }
+            if (ch.size() > 0) { I.f_in0 = (int8_t)fslot[ch[0]]; I.b_in0 = (int8_t)ch[0]; I.g_in0 = (int8_t)gslot[ch[0]]; }
+            if (ch.size() > 1) { I.f_in1 = (int8_t)fslot[ch[1]]; I.b_in1 = (int8_t)ch[1]; I.g_in1 = (int8_t)gslot[ch[1]]; }
         }
     }
     // each smooth Until gets a slot pair in the backward map where the
     // recompute keeps its fp64 outer sums Z_t for the adjoint (index in I.coef)
-    int nbwd = nval + nadj;
+    int nbwd = (int)ga.free_at.size();
     for (int k = 0; k < n; ++k) {
         Instr& I = B.ins[k];
         if (I.kind != K_UNTIL) continue;

@@ -139,6 +139,7 @@ struct Env {
     float* scr;        // op scratch
     float* lds;        // LDS beside the slots (smooth Until): export buffers, with slots in the workspace
                        // also the term tile and the checkpoints
+    int tile;          // positions of the smooth Until's term tile in lds (0: terms in the scratch)
     bool global;       // slots in the workspace
     Shared* sh;
     int tid;           // threadIdx.x, opaque per instruction: what is derived from it is not kept in registers
@@ -1297,21 +1298,25 @@ DEV void until_smooth_fwd(const Env& e, int a, int b, const float* w, const SP* 
     }
 }
 
-constexpr int UCK = 16;   // checkpoint spacing of the smooth Until adjoint
-constexpr int UCK_UNIT = 4, UCK_UNIT_MASK = 7;    // scratch unit where its checkpoints start (mask tables: units 4-6)
+constexpr int UCK = 16;       // steps per block of the fp64 smooth Until adjoints
+constexpr int UCK_SP = 32;    // of the scaled-pair adjoint (a checkpoint per block)
+constexpr int UCK_CS = 32;    // checkpoint spacing of until_adj_r (two blocks)
+constexpr int UCK_UNIT = 4, UCK_UNIT_MASK = 7;    // scratch unit where the checkpoints start (mask tables: units 4-6)
 constexpr int UT_RMAX = 4;                        // outputs per lane at most
+constexpr int UT_EX = 32;                         // positions of a wave's export buffer
+constexpr int UT_TILE_B = 1024;                   // longest interval whose terms are staged in LDS
 
-// checkpoints per lane for the interval's end b (< 0: unbounded)
-static __host__ __device__ __forceinline__ int until_cks(int b, int L)
+// checkpoints per lane, one per `per` steps, for the interval's end b (< 0: unbounded)
+static __host__ __device__ __forceinline__ int until_cks(int b, int L, int per)
 {
-    return (b < 0 || b > L - 1 ? L - 1 : (b + UT_RMAX - 1 > L - 1 ? L - 1 : b + UT_RMAX - 1)) / UCK + 1;
+    return (b < 0 || b > L - 1 ? L - 1 : (b + UT_RMAX - 1 > L - 1 ? L - 1 : b + UT_RMAX - 1)) / per + 1;
 }
 
 // Smooth Until adjoint (checkpointed reverse sweep per output t):
 //   d out / d psi_{t+i} = w_i Y_i^2 Q_i / Z,  Q_i = 2^{-z_psi(t+i)}
 //   d out / d phi_{t+k} = e_k / Z * sum_{i >= max(k,a)} w_i Y_i^2,  e_k = 2^{-z_phi(t+k)}
 //   d out / d w_i = Y_i / (beta Z)   (summed against d w/da, d w/db into pa, pb)
-// Pass 1 recomputes Z and stores P every UCK steps; pass 2 walks the
+// Pass 1 recomputes Z and stores P every UCK_SP steps; pass 2 walks the
 // checkpoint blocks backward, recomputing P inside each block.  The float
 // contributions go through the lane-shifted accumulators of lane_stage
 // (defined below), in the same fixed order as the fp64 adjoint.
@@ -1335,7 +1340,7 @@ DEV void until_smooth_adj(const Env& e, int a, int b, const float* w, const floa
         if (act) {
             SP P = sp_zero();
             for (int i = 0; i <= imax; ++i) {
-                if (i % UCK == 0) myck[i / UCK] = P;
+                if (i % UCK_SP == 0) myck[i / UCK_SP] = P;
                 P = sp_add(P, Ephi[t + i]);
                 if (i >= a) {
                     SP Dn = sp_add(P, Epsi[t + i]);
@@ -1345,21 +1350,21 @@ DEV void until_smooth_adj(const Env& e, int a, int b, const float* w, const floa
         }
         const float gz = act ? gt / Z.s : 0.f;      // G / Z = gz * 2^{-Z.r}
         const int imax0 = b < 0 ? L - 1 - base : min(b, L - 1 - base);     // t = base: the longest chain
-        const int wblk = a <= imax0 ? imax0 / UCK + 1 : 0;
+        const int wblk = a <= imax0 ? imax0 / UCK_SP + 1 : 0;
         float accp = 0.f, accq = 0.f, stp = 0.f, stq = 0.f;
         SP A = sp_zero();                   // suffix sum of w_i Y_i^2
         for (int blk = wblk - 1; blk >= 0; --blk) {
-            const int i0 = blk * UCK;
-            const int i1 = act ? min(imax, i0 + UCK - 1) : i0 - 1;      // this lane's last step in the block
-            SP Ps[UCK];
+            const int i0 = blk * UCK_SP;
+            const int i1 = act ? min(imax, i0 + UCK_SP - 1) : i0 - 1;      // this lane's last step in the block
+            SP Ps[UCK_SP];
             SP Pc = i0 <= i1 ? myck[blk] : sp_zero();
 #pragma unroll
-            for (int q = 0; q < UCK; ++q) {
+            for (int q = 0; q < UCK_SP; ++q) {
                 if (i0 + q <= i1) Pc = sp_add(Pc, Ephi[t + i0 + q]);
                 Ps[q] = Pc;
             }
 #pragma unroll
-            for (int q = UCK - 1; q >= 0; --q) {
+            for (int q = UCK_SP - 1; q >= 0; --q) {
                 const int i = i0 + q;
                 if (i <= i1) {
                     if (i >= a) {
@@ -1479,17 +1484,39 @@ DEV void until_terms(const float* phi, const float* psi, int L, float bl, int M,
 // per thread.  R = 4 where the trajectory has enough outputs to give every
 // lane of the work-group four, else 2 or 1 (the lanes are worth more than the
 // shared reads).
+// n consecutive terms from p: 16-byte reads where the lanes are 2 or 4 outputs
+// apart (p is then 16-byte aligned; the 8-byte reads of lanes 32 bytes apart
+// fall on each LDS bank four times, and bound the walk)
+template <int R, int N>
+DEV void load_terms(const double* p, double (&v)[N])
+{
+    if (R == 1) {
+#pragma unroll
+        for (int k = 0; k < N; ++k) v[k] = p[k];
+    } else {
+#pragma unroll
+        for (int k = 0; k < N; k += 2) {
+            const double2 t = *(const double2*)(p + k);
+            v[k] = t.x;
+            v[k + 1] = t.y;
+        }
+    }
+}
+
 DEV int until_outputs(int L, int nt) { return L <= nt ? 1 : (L <= 2 * nt ? 2 : 4); }
 
+// One pass: the outputs base .. base + nt R - 1; Ep, Eq hold the terms from
+// position j0 on.
 template <int R>
-DEV void until_fwd_r(const Env& e, int a, int b, const double* Ep, const double* Eq, float* out, double* zs, float bl,
-                     int M)
+DEV void until_fwd_r(const Env& e, int a, int b, const double* Ep, const double* Eq, int j0, int base, float* out,
+                     double* zs, float bl, int M)
 {
     const int L = e.L;
     const float rho_pad = e.P->rho_pad;
-    for (int t0 = e.tid * R; t0 < L; t0 += e.nt * R) {
-        const double* p = Ep + t0;
-        const double* q = Eq + t0;
+    const int t0 = base + e.tid * R;
+    if (t0 < L) {
+        const double* p = Ep + (t0 - j0);
+        const double* q = Eq + (t0 - j0);
         const int last = L - 1 - t0;                                 // steps 0 .. last stay inside
         const int smax = b < 0 ? last : min(b + R - 1, last);
         double Z[R], C[R];
@@ -1537,15 +1564,12 @@ DEV void until_fwd_r(const Env& e, int a, int b, const double* Ep, const double*
             }
         };
         const int full = b < 0 ? smax : min(b, smax);                // last step every output takes
-        edge(min(a + R - 2, smax));
+        edge(min((a + 2 * R - 2) / R * R - 1, smax));                // (to a multiple of R)
         constexpr int U = 8;
         for (; s + U - 1 <= full; s += U) {
             double v[U], w[U];
-#pragma unroll
-            for (int k = 0; k < U; ++k) {
-                v[k] = p[s + k];
-                w[k] = q[s + k];
-            }
+            load_terms<R>(p + s, v);
+            load_terms<R>(q + s, w);
 #pragma unroll
             for (int k = 0; k < U; ++k) {
                 P += v[k];
@@ -1647,7 +1671,7 @@ DEV void lane_stage(int i, int tb, int lane, int L, float& accp, float& accq, fl
 // m_{t,j} = (G_t / Z_t) Y_{t,j}^2,
 //   d out / d psi_j = q_j sum_t m_{t,j},  d out / d phi_k = p_k sum_{t <= k <= j} m_{t,j}.
 // A lane owns the R outputs of until_fwd_r and walks j = t_0 + s downwards.  A
-// forward sweep of additions keeps P_{t_0+R-1,j} every UCK steps; the reverse
+// forward sweep of additions keeps P_{t_0+R-1,j} every UCK_CS steps; the reverse
 // walk rebuilds each block's sums from its checkpoint.  Step s adds
 // S = sum_r m_{t_0+r,j} to the psi sum of position j, and the running sum A of
 // S over the steps so far (all terms at or past j) to its phi sum.  Below
@@ -1657,7 +1681,7 @@ DEV void lane_stage(int i, int tb, int lane, int L, float& accp, float& accq, fl
 // (s = R m + c) is that of lane l-1 one macro-step m earlier: the 2 R fp64
 // sums move up one lane per R steps (a DPP shift), and the positions leaving
 // lane 63 are finished for this wave.  They go to a buffer of the wave, which
-// is added to the adjoint slots every 64 macro-steps and scaled by p_j, q_j
+// is added to the adjoint slots every UT_EX positions and scaled by p_j, q_j
 // there.  All waves of the work-group walk the same steps (those of the
 // longest chain of the pass), so the buffers are added at the same points in
 // every wave, where they cover disjoint positions, and a barrier separates the
@@ -1665,18 +1689,20 @@ DEV void lane_stage(int i, int tb, int lane, int L, float& accp, float& accq, fl
 // Against one output per lane (three multiplies, two conversions, two float
 // adds, two lane reads and two shifts per term) a term takes an add, the
 // reciprocal, two multiplies and about 2.5 adds.
+// One pass: the outputs base .. base + nt R - 1; Ep, Eq hold the terms of the
+// positions j0 .. jl - 1.
 template <int R>
-DEV void until_adj_r(const Env& e, int a, int b, const double* Ep, const double* Eq, const double* zs, const float* g,
-                     float* gphi, float* gpsi, double* ck, double* exb)
+DEV void until_adj_r(const Env& e, int a, int b, const double* Ep, const double* Eq, int j0, int jl, int base,
+                     const double* zs, const float* g, float* gphi, float* gpsi, double* ck, double* exb)
 {
     const int L = e.L, nt = e.nt;
     const int lane = e.tid & 63;
-    double* ex = exb + (size_t)(e.tid >> 6) * (128 * R);       // psi sums, then phi sums
-    for (int base = 0; base < L; base += nt * R) {
+    double* ex = exb + (e.tid >> 6) * (2 * UT_EX);             // psi sums, then phi sums
+    {
         const int tb = base + (e.tid - lane) * R;
         const int t0 = tb + lane * R;
-        const double* p = Ep + t0;
-        const double* q = Eq + t0;
+        const double* p = Ep + (t0 - j0);
+        const double* q = Eq + (t0 - j0);
         const int last = L - 1 - t0;
         double wz[R], C[R];
         bool any = false;
@@ -1698,11 +1724,10 @@ DEV void until_adj_r(const Env& e, int a, int b, const double* Ep, const double*
         {
             double P = 0.0;
             for (int blk = 0; blk <= smax / UCK && smax >= 0; ++blk) {
-                ck[blk * nt + e.tid] = P;
+                if (blk % 2 == 0) ck[blk / 2 * nt + e.tid] = P;
                 if ((blk + 1) * UCK <= smax) {                       // a next block: this one is whole
                     double v[UCK];
-#pragma unroll
-                    for (int k = 0; k < UCK; ++k) v[k] = p[blk * UCK + k];
+                    load_terms<R>(p + blk * UCK, v);
 #pragma unroll
                     for (int k = 0; k < UCK; ++k)
                         if (k >= R - 1 || blk > 0) P += v[k];
@@ -1713,18 +1738,15 @@ DEV void until_adj_r(const Env& e, int a, int b, const double* Ep, const double*
 #pragma unroll
         for (int r = 0; r < R; ++r) {
             B[r] = sq[r] = sp[r] = 0.0;
-            ex[lane * R + r] = ex[64 * R + lane * R + r] = 0.0;
         }
+        ex[lane] = 0.0;                                        // (2 UT_EX = 64 sums)
         for (int blk = wblk - 1; blk >= 0; --blk) {
             const int s0 = blk * UCK;
             const int n = min(UCK, smax - s0 + 1);                   // own steps of the block (<= 0: none)
             double v[UCK], d[UCK];
             if (__all(n >= UCK)) {
-#pragma unroll
-                for (int k = 0; k < UCK; ++k) {
-                    v[k] = p[s0 + k];
-                    d[k] = q[s0 + k];
-                }
+                load_terms<R>(p + s0, v);
+                load_terms<R>(q + s0, d);
             } else {
 #pragma unroll
                 for (int k = 0; k < UCK; ++k) {
@@ -1732,7 +1754,14 @@ DEV void until_adj_r(const Env& e, int a, int b, const double* Ep, const double*
                     d[k] = k < n ? q[s0 + k] : 1e300;                // Y^2 = 0 past the own steps
                 }
             }
-            double P = n > 0 ? ck[blk * nt + e.tid] : 0.0;
+            double P = n > 0 ? ck[blk / 2 * nt + e.tid] : 0.0;
+            if (blk % 2 == 1 && n > 0) {                             // the block before, from its checkpoint
+                double u[UCK];
+                load_terms<R>(p + (s0 - UCK), u);
+#pragma unroll
+                for (int k = 0; k < UCK; ++k)
+                    if (k >= R - 1 || blk > 1) P += u[k];
+            }
 #pragma unroll
             for (int k = 0; k < UCK; ++k) {
                 if (k >= R - 1 || blk > 0) P += v[k];
@@ -1771,26 +1800,23 @@ DEV void until_adj_r(const Env& e, int a, int b, const double* Ep, const double*
                     sp[c] += (R > 1 && !decltype(inner)::value && k < R - 1 && blk == 0) ? B[k % R] : A;
                     if (c == 0 && s > 0) {
                         // macro-step m = s / R is done: lane 63's positions leave the wave
-                        const int i = ((s / R - 1) & 63) * R;
+                        const int i = (s / R - 1) * R & (UT_EX - 1);
                         if (lane == 63) {
 #pragma unroll
                             for (int r = 0; r < R; ++r) {
                                 ex[i + r] = sq[r];
-                                ex[64 * R + i + r] = sp[r];
+                                ex[UT_EX + i + r] = sp[r];
                             }
                         }
                         if (i == 0) {
                             __threadfence_block();                   // lane 63's values, for the other lanes
-                            const int m1 = s / R - 1;
-#pragma unroll
-                            for (int r = 0; r < R; ++r) {
-                                const int at = lane * R + r, j = tb + 64 * R + m1 * R + at;
-                                if (j < L) {
-                                    gpsi[j] += (float)(ex[at] * Eq[j]);
-                                    gphi[j] += (float)(ex[64 * R + at] * Ep[j]);
-                                }
-                                ex[at] = ex[64 * R + at] = 0.0;
+                            const int at = lane & (UT_EX - 1), j = tb + 64 * R + s - R + at;
+                            const double sum = ex[lane];
+                            if (j < jl) {
+                                if (lane < UT_EX) gpsi[j] += (float)(sum * Eq[j - j0]);
+                                else gphi[j] += (float)(sum * Ep[j - j0]);
                             }
+                            ex[lane] = 0.0;
                             __syncthreads();
                         }
 #pragma unroll
@@ -1811,8 +1837,8 @@ DEV void until_adj_r(const Env& e, int a, int b, const double* Ep, const double*
             for (int r = 0; r < R; ++r) {
                 const int j = t0 + r;
                 if (j < L) {
-                    gpsi[j] += (float)(sq[r] * Eq[j]);
-                    gphi[j] += (float)(sp[r] * Ep[j]);
+                    gpsi[j] += (float)(sq[r] * Eq[j - j0]);
+                    gphi[j] += (float)(sp[r] * Ep[j - j0]);
                 }
             }
         __syncthreads();
@@ -1905,34 +1931,76 @@ DEV void until_adj_w(const Env& e, int a, int b, const float* w, const float* dw
     }
 }
 
-DEV void until_smooth_fwd_d(const Env& e, int a, int b, const float* w, const double* Ep, const double* Eq, float* out,
-                            double* zs, float bl, int M)
+// Terms of both inputs for the outputs of the pass at `base` (their windows end
+// at b + R - 1 steps) into the LDS tile; returns the first position past it.
+// With slots in the workspace the Until's reads (two terms per step and lane,
+// 32 bytes apart) would otherwise go through the vector cache.
+DEV int until_tile(const Env& e, const float* phi, const float* psi, int base, int n, float bl, int M, double* Ep,
+                   double* Eq)
 {
-    if (w) {
-        until_fwd_w(e, a, b, w, Ep, Eq, out, zs, bl, M);
-        return;
+    const int jl = min(e.L, base + n);
+    __syncthreads();                        // the previous pass has read its tile
+#pragma unroll 4
+    for (int j = base + e.tid; j < jl; j += e.nt) {
+        Ep[j - base] = uterm(-bl * phi[j], M);
+        Eq[j - base] = uterm(-bl * psi[j], M);
     }
-    switch (until_outputs(e.L, e.nt)) {
-    case 1: until_fwd_r<1>(e, a, b, Ep, Eq, out, zs, bl, M); break;
-    case 2: until_fwd_r<2>(e, a, b, Ep, Eq, out, zs, bl, M); break;
-    default: until_fwd_r<4>(e, a, b, Ep, Eq, out, zs, bl, M); break;
+    __syncthreads();
+    return jl;
+}
+
+template <int R>
+DEV void until_fwd_passes(const Env& e, int a, int b, const float* phi, const float* psi, double* Ep, double* Eq,
+                          float* out, double* zs, float bl, int M)
+{
+    for (int base = 0; base < e.L; base += e.nt * R) {
+        if (e.tile) until_tile(e, phi, psi, base, e.nt * R + (b < 0 ? e.L - 1 : b) + R, bl, M, Ep, Eq);
+        until_fwd_r<R>(e, a, b, Ep, Eq, e.tile ? base : 0, base, out, zs, bl, M);
     }
 }
 
-// ck: nt checkpoints per UCK steps
-DEV void until_smooth_adj_d(const Env& e, int a, int b, const float* w, const float* dwa, const float* dwb,
-                            const double* Ep, const double* Eq, const double* zs, const float* g, float* gphi,
-                            float* gpsi, double* ck, int ncks, float& pa, float& pb)
+template <int R>
+DEV void until_adj_passes(const Env& e, int a, int b, const float* phi, const float* psi, double* Ep, double* Eq,
+                          const double* zs, const float* g, float* gphi, float* gpsi, double* ck, double* exb, float bl,
+                          int M)
 {
-    double* exb = (double*)e.lds;
-    if (w) {
-        until_adj_w(e, a, b, w, dwa, dwb, Ep, Eq, zs, g, gphi, gpsi, ck, ncks, pa, pb);
-        return;
+    for (int base = 0; base < e.L; base += e.nt * R) {
+        int j0 = 0, jl = e.L;
+        if (e.tile) {
+            jl = until_tile(e, phi, psi, base, e.nt * R + (b < 0 ? e.L - 1 : b) + R, bl, M, Ep, Eq);
+            j0 = base;
+        }
+        until_adj_r<R>(e, a, b, Ep, Eq, j0, jl, base, zs, g, gphi, gpsi, ck, exb);
     }
+}
+
+// The smooth Until without a mask, fp64 form.  The terms lie in the scratch
+// (all of them) or pass by pass in the LDS tile (e.tile > 0: its positions).
+DEV void until_smooth_fwd_d(const Env& e, int a, int b, const float* phi, const float* psi, float* out, double* zs,
+                            float bl, int M)
+{
+    double* Ep = e.tile ? (double*)e.lds : (double*)S(e, 0);
+    double* Eq = e.tile ? Ep + e.tile : (double*)S(e, 2);
+    if (!e.tile) until_terms(phi, psi, e.L, bl, M, Ep, Eq, e.nt, e.tid);
     switch (until_outputs(e.L, e.nt)) {
-    case 1: until_adj_r<1>(e, a, b, Ep, Eq, zs, g, gphi, gpsi, ck, exb); break;
-    case 2: until_adj_r<2>(e, a, b, Ep, Eq, zs, g, gphi, gpsi, ck, exb); break;
-    default: until_adj_r<4>(e, a, b, Ep, Eq, zs, g, gphi, gpsi, ck, exb); break;
+    case 1: until_fwd_passes<1>(e, a, b, phi, psi, Ep, Eq, out, zs, bl, M); break;
+    case 2: until_fwd_passes<2>(e, a, b, phi, psi, Ep, Eq, out, zs, bl, M); break;
+    default: until_fwd_passes<4>(e, a, b, phi, psi, Ep, Eq, out, zs, bl, M); break;
+    }
+}
+
+DEV void until_smooth_adj_d(const Env& e, int a, int b, const float* phi, const float* psi, const double* zs,
+                            const float* g, float* gphi, float* gpsi, float bl, int M)
+{
+    double* exb = (double*)e.lds;                       // nt of them: 2 UT_EX per wave
+    double* Ep = e.tile ? exb + e.nt : (double*)S(e, 0);
+    double* Eq = e.tile ? Ep + e.tile : (double*)S(e, 2);
+    double* ck = e.tile ? Eq + e.tile : (double*)S(e, UCK_UNIT);
+    if (!e.tile) until_terms(phi, psi, e.L, bl, M, Ep, Eq, e.nt, e.tid);
+    switch (until_outputs(e.L, e.nt)) {
+    case 1: until_adj_passes<1>(e, a, b, phi, psi, Ep, Eq, zs, g, gphi, gpsi, ck, exb, bl, M); break;
+    case 2: until_adj_passes<2>(e, a, b, phi, psi, Ep, Eq, zs, g, gphi, gpsi, ck, exb, bl, M); break;
+    default: until_adj_passes<4>(e, a, b, phi, psi, Ep, Eq, zs, g, gphi, gpsi, ck, exb, bl, M); break;
     }
 }
 
@@ -2079,12 +2147,16 @@ DEV void exec_fwd(const Env& e, const Instr& I, bool bwdmap)
             const float bl = pbeta(e, I) * LOG2E;
             int M;
             if (until_ref(phi, psi, L, bl, e, M)) {
+                // the backward's recompute keeps Z in the instruction's slot pair for the adjoint
+                double* zs = bwdmap ? (double*)slot(e, I.coef) : nullptr;
+                if (!w) {
+                    until_smooth_fwd_d(e, ua, ub, phi, psi, out, zs, bl, M);
+                    break;
+                }
                 double* Ep = (double*)S(e, 0);
                 double* Eq = (double*)S(e, 2);
                 until_terms(phi, psi, L, bl, M, Ep, Eq, e.nt, e.tid);
-                // the backward's recompute keeps Z in the instruction's slot pair for the adjoint
-                double* zs = bwdmap ? (double*)slot(e, I.coef) : nullptr;
-                until_smooth_fwd_d(e, ua, ub, w, Ep, Eq, out, zs, bl, M);
+                until_fwd_w(e, ua, ub, w, Ep, Eq, out, zs, bl, M);
                 break;
             }
             SP* Ephi = (SP*)S(e, 0);
@@ -2346,16 +2418,19 @@ DEV void exec_adj(const Env& e, const Instr& I, float* mask_part)
             else until_hard(e, ua, ub, phi, psi, nullptr, g, gphi, gpsi, (int*)S(e, 0));
         } else {
             const float bl = pbeta(e, I) * LOG2E;
-            const int ncks = until_cks(ub, L);
             const int cku = I.mask >= 0 ? UCK_UNIT_MASK : UCK_UNIT;
             int M;
             if (until_ref(phi, psi, L, bl, e, M)) {
-                double* Ep = (double*)S(e, 0);
-                double* Eq = (double*)S(e, 2);
-                until_terms(phi, psi, L, bl, M, Ep, Eq, e.nt, e.tid);
                 const double* zs = (const double*)slot(e, I.coef);
-                until_smooth_adj_d(e, ua, ub, w, dwa, dwb, Ep, Eq, zs, g, gphi, gpsi, (double*)S(e, cku), ncks,
-                                   pa, pb);
+                if (!w) {
+                    until_smooth_adj_d(e, ua, ub, phi, psi, zs, g, gphi, gpsi, bl, M);
+                } else {
+                    double* Ep = (double*)S(e, 0);
+                    double* Eq = (double*)S(e, 2);
+                    until_terms(phi, psi, L, bl, M, Ep, Eq, e.nt, e.tid);
+                    until_adj_w(e, ua, ub, w, dwa, dwb, Ep, Eq, zs, g, gphi, gpsi, (double*)S(e, cku),
+                                until_cks(ub, L, UCK), pa, pb);
+                }
             } else {
                 SP* Ephi = (SP*)S(e, 0);
                 SP* Epsi = (SP*)S(e, 2);
@@ -2364,8 +2439,8 @@ DEV void exec_adj(const Env& e, const Instr& I, float* mask_part)
                     Epsi[j] = sp_leaf(-bl * psi[j]);
                 }
                 __syncthreads();
-                until_smooth_adj(e, ua, ub, w, dwa, dwb, Ephi, Epsi, g, gphi, gpsi, (SP*)S(e, cku), ncks, pa,
-                                 pb);
+                until_smooth_adj(e, ua, ub, w, dwa, dwb, Ephi, Epsi, g, gphi, gpsi, (SP*)S(e, cku),
+                                 until_cks(ub, L, UCK_SP), pa, pb);
             }
         }
         if (I.mslot >= 0) {
@@ -2507,6 +2582,7 @@ __global__ void __launch_bounds__(MAX_NT) stl_exec_kernel(DevPlan plan, Batch bt
         e.arena = arena;
         e.scr = arena + (size_t)nslots * Lc;
         e.global = GLOBAL;
+        e.tile = GLOBAL ? ka.tile : 0;
         e.lds = GLOBAL ? smem : smem + ka.arena_floats;
         e.sh = &sh;
         e.nt = ka.nt;
@@ -2639,14 +2715,27 @@ size_t scratch_floats(int Lc, int nt, int units, int until_b, bool until_masked)
     size_t s = (size_t)units * Lc;
     // smooth Until adjoint: nt checkpoints per UCK steps
     if (until_b >= 0) {
-        const size_t ck = (size_t)nt * until_cks(until_b, Lc) * 2;
+        const size_t ck = (size_t)nt * until_cks(until_b, Lc, until_masked ? UCK : UCK_CS) * 2;
         s = std::max(s, (size_t)(until_masked ? UCK_UNIT_MASK : UCK_UNIT) * Lc + ck);
     }
     return s + 64;
 }
 
-// LDS of the waves' export buffers (smooth Until adjoint), after the arena
-size_t until_export_bytes(int nt) { return (size_t)nt * UT_RMAX * 16; }
+// positions of the smooth Until's LDS tile for slots in the workspace (0: none)
+int until_tile_len(int nt, int until_b, bool until_masked)
+{
+    return until_b < 0 || until_masked || until_b > UT_TILE_B ? 0 : (nt * UT_RMAX + until_b + UT_RMAX + 1) & ~1;
+}
+
+// LDS beside the slots for a plan with smooth Untils: the waves' export
+// buffers, and the tile with the backward's checkpoints
+size_t until_lds_bytes(int nt, int until_b, bool bwd, int tile, int Lc)
+{
+    if (until_b < 0) return 0;
+    size_t s = (size_t)tile * 16;
+    if (bwd) s += (size_t)nt * 8 + (tile ? (size_t)nt * until_cks(until_b, Lc, UCK_CS) * 8 : 0);
+    return s;
+}
 
 hipError_t launch_exec(bool bwd, const DevPlan& plan, const Batch& bt, const KArgs& ka, int grid, int nt,
                        size_t lds_bytes, hipStream_t s)
@@ -2670,6 +2759,9 @@ hipError_t set_max_lds(size_t bytes)
                                         hipFuncAttributeMaxDynamicSharedMemorySize, (int)bytes);
     if (e2 == hipSuccess)
         e2 = hipFuncSetAttribute((const void*)stl_exec_kernel<true, true>,
+                                 hipFuncAttributeMaxDynamicSharedMemorySize, (int)bytes);
+    if (e2 == hipSuccess)
+        e2 = hipFuncSetAttribute((const void*)stl_exec_kernel<false, true>,
                                  hipFuncAttributeMaxDynamicSharedMemorySize, (int)bytes);
     return e1 != hipSuccess ? e1 : e2;
 }

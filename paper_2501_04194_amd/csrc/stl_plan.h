@@ -135,6 +135,7 @@ struct KArgs {
     int* saved_none;       // [B] or NULL: the generic executor marks its trajectories' saved traces unusable
     float* gp_zero;        // backward of a plan without masks: parameter gradients to clear, or NULL
     int nt;                // work-group size of the generic executor
+    int tile;              // generic executor, slots in the workspace: positions of the smooth Until's LDS tile
     int part_stride;       // rows of mask_part per trajectory (1; a caller with more rows per
                            // trajectory has the generic executor clear the others)
 };
