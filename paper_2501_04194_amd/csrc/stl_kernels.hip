@@ -2008,7 +2008,9 @@ DEV void until_smooth_adj_d(const Env& e, int a, int b, const float* phi, const 
 
 DEV bool is_smooth(const Instr& I) { return I.flags & F_SMOOTH; }
 
-// Run one instruction forward with the given slot map (fwd or bwd).
+// Run one instruction forward with the given slot map (fwd or bwd).  FULL =
+// false leaves out the operators of plan_is_plain's complement.
+template <bool FULL>
 DEV void exec_fwd(const Env& e, const Instr& I, bool bwdmap)
 {
     const int o = bwdmap ? I.b_out : I.f_out;
@@ -2038,7 +2040,7 @@ DEV void exec_fwd(const Env& e, const Instr& I, bool bwdmap)
         const float padv = e.P->coef[I.coef];
         if (!is_smooth(I)) {
             win_hard(e, u, out, nullptr, sg, I.a, khi, I.pad, padv, (VI*)S(e, 0), (VI*)S(e, 2));
-        } else if (I.flags & F_SOFT) {
+        } else if (FULL && (I.flags & F_SOFT)) {
             // softmax-weighted mean over the window: out = sum u 2^{z} / sum 2^{z};
             // LAST / CONST add np copies of the pad value v to both sums
             const float bl = pbeta(e, I) * LOG2E;
@@ -2071,6 +2073,7 @@ DEV void exec_fwd(const Env& e, const Instr& I, bool bwdmap)
         break;
     }
     case K_MASK: {
+        if constexpr (FULL) {
         const float* u = slot(e, i0);
         float* w = S(e, 6);
         MaskInfo mi = mask_weights(e, I, w, nullptr, nullptr);
@@ -2120,6 +2123,7 @@ DEV void exec_fwd(const Env& e, const Instr& I, bool bwdmap)
             const bool any = (mi.any && t + mi.klo <= L - 1) || pt;
             out[t] = any ? sg * sp_log2(spd_to_sp(a)) / bl : -sg * e.P->rho_pad;
         }
+        }
         break;
     }
     case K_UNTIL: {
@@ -2129,7 +2133,7 @@ DEV void exec_fwd(const Env& e, const Instr& I, bool bwdmap)
         // its support {w > 0} and weights the terms
         int ua = I.a, ub = I.b;
         const float* w = nullptr;
-        if (I.mask >= 0) {
+        if constexpr (FULL) if (I.mask >= 0) {
             float* wt = S(e, 4);
             const MaskInfo mi = mask_weights(e, I, wt, nullptr, nullptr);
             if (!mi.any) {
@@ -2143,7 +2147,7 @@ DEV void exec_fwd(const Env& e, const Instr& I, bool bwdmap)
         if (!is_smooth(I)) {
             if (ub < 0 && I.mask < 0) until_hard_unb(e, ua, phi, psi, out, nullptr, nullptr, nullptr);
             else until_hard(e, ua, ub, phi, psi, out, nullptr, nullptr, nullptr, nullptr);
-        } else {
+        } else if constexpr (FULL) {
             const float bl = pbeta(e, I) * LOG2E;
             int M;
             if (until_ref(phi, psi, L, bl, e, M)) {
@@ -2177,6 +2181,7 @@ DEV void exec_fwd(const Env& e, const Instr& I, bool bwdmap)
 
 // Adjoint of one instruction (backward slot map).  Children adjoints are
 // written (not accumulated): every node has exactly one parent.
+template <bool FULL>
 DEV void exec_adj(const Env& e, const Instr& I, float* mask_part)
 {
     const int L = e.L;
@@ -2206,7 +2211,7 @@ DEV void exec_adj(const Env& e, const Instr& I, float* mask_part)
             win_hard_adj(e, g, gu, js, (double*)S(e, 6));
             break;
         }
-        if (I.flags & F_SOFT) {
+        if constexpr (FULL) if (I.flags & F_SOFT) {
             // d out_t / d u_j = p_j(t) (1 + k (u_j - out_t)), p_j(t) = 2^{z_j} / S0(t), k = sg beta:
             // gu_j = 2^{z_j} [(1 + k u_j) sum_t G_t / S0(t) - k sum_t G_t out_t / S0(t)]
             // over the t whose window holds j (transposed window sums)
@@ -2281,6 +2286,7 @@ DEV void exec_adj(const Env& e, const Instr& I, float* mask_part)
         break;
     }
     case K_MASK: {
+        if constexpr (FULL) {
         const float* u = slot(e, I.b_in0);
         float* gu = slot(e, I.g_in0);
         float* w = S(e, 6);
@@ -2386,6 +2392,7 @@ DEV void exec_adj(const Env& e, const Instr& I, float* mask_part)
             if (padm && I.pad == PAD_LAST && j == L - 1) v += lastpad;
             gu[j] = v;
         }
+        }
         break;
     }
     case K_UNTIL: {
@@ -2398,7 +2405,7 @@ DEV void exec_adj(const Env& e, const Instr& I, float* mask_part)
         int ua = I.a, ub = I.b;
         const float *w = nullptr, *dwa = nullptr, *dwb = nullptr;
         bool none = false;
-        if (I.mask >= 0) {
+        if constexpr (FULL) if (I.mask >= 0) {
             float* wt = S(e, 4);
             float* wa = S(e, 5);
             float* wb = S(e, 6);
@@ -2416,7 +2423,7 @@ DEV void exec_adj(const Env& e, const Instr& I, float* mask_part)
         } else if (!is_smooth(I)) {
             if (ub < 0 && I.mask < 0) until_hard_unb(e, ua, phi, psi, nullptr, g, gphi, gpsi);
             else until_hard(e, ua, ub, phi, psi, nullptr, g, gphi, gpsi, (int*)S(e, 0));
-        } else {
+        } else if constexpr (FULL) {
             const float bl = pbeta(e, I) * LOG2E;
             const int cku = I.mask >= 0 ? UCK_UNIT_MASK : UCK_UNIT;
             int M;
@@ -2523,7 +2530,11 @@ DEV void plan_touch(const DevPlan* P)
 
 // GLOBAL: the slots lie in the workspace instead of LDS (two kernels, so that
 // every slot access of the LDS one is an LDS instruction, not a flat one).
-template <bool BWD, bool GLOBAL>
+// FULL = false: for plans of predicates, n-ary nodes, integer windows and hard
+// Untils only (plan_is_plain).  The smooth Until and the masks set the full
+// kernels' registers (256 in the backward: two waves per SIMD), which 1,000
+// short trajectories of such a plan would wait for.
+template <bool BWD, bool GLOBAL, bool FULL>
 __global__ void __launch_bounds__(MAX_NT) stl_exec_kernel(DevPlan plan, Batch bt, KArgs ka)
 {
     extern __shared__ __align__(16) float smem[];
@@ -2593,7 +2604,7 @@ __global__ void __launch_bounds__(MAX_NT) stl_exec_kernel(DevPlan plan, Batch bt
             const bool x = crosses_threads(I);
             if (x) __syncthreads();
             e.tid = exec_tid();
-            exec_fwd(e, I, BWD);
+            exec_fwd<FULL>(e, I, BWD);
             if (x) __syncthreads();
         }
         if (!BWD) {
@@ -2629,7 +2640,7 @@ __global__ void __launch_bounds__(MAX_NT) stl_exec_kernel(DevPlan plan, Batch bt
                 const bool x = crosses_threads(I);
                 if (x) __syncthreads();
                 e.tid = exec_tid();
-                exec_adj(e, I, mp);
+                exec_adj<FULL>(e, I, mp);
                 if (x) __syncthreads();
             }
             e.tid = exec_tid();
@@ -2737,33 +2748,43 @@ size_t until_lds_bytes(int nt, int until_b, bool bwd, int tile, int Lc)
     return s;
 }
 
+// no smooth mask, no smooth Until, no softmax-weighted window: the small kernels
+static bool plan_is_plain(const DevPlan& plan)
+{
+    for (int k = plan.n_pred; k < plan.n_ins; ++k) {
+        const Instr& I = plan.ins[k];
+        if (I.kind == K_MASK || (I.kind == K_UNTIL && (I.mask >= 0 || (I.flags & F_SMOOTH))) ||
+            (I.kind == K_WIN && (I.flags & F_SOFT)))
+            return false;
+    }
+    return true;
+}
+
 hipError_t launch_exec(bool bwd, const DevPlan& plan, const Batch& bt, const KArgs& ka, int grid, int nt,
                        size_t lds_bytes, hipStream_t s)
 {
     const dim3 g(grid), b(nt);     // (ka.nt = nt)
-    if (ka.garena) {
-        if (bwd) hipLaunchKernelGGL((stl_exec_kernel<true, true>), g, b, lds_bytes, s, plan, bt, ka);
-        else hipLaunchKernelGGL((stl_exec_kernel<false, true>), g, b, lds_bytes, s, plan, bt, ka);
-    } else {
-        if (bwd) hipLaunchKernelGGL((stl_exec_kernel<true, false>), g, b, lds_bytes, s, plan, bt, ka);
-        else hipLaunchKernelGGL((stl_exec_kernel<false, false>), g, b, lds_bytes, s, plan, bt, ka);
-    }
+#define STLMI_EXEC(BW, GL, FU)                                                                                       \
+    if (bwd == BW && (ka.garena != nullptr) == GL && full == FU)                                                     \
+        hipLaunchKernelGGL((stl_exec_kernel<BW, GL, FU>), g, b, lds_bytes, s, plan, bt, ka);
+    const bool full = !plan_is_plain(plan);
+    STLMI_EXEC(false, false, false) STLMI_EXEC(false, false, true) STLMI_EXEC(false, true, false)
+    STLMI_EXEC(false, true, true) STLMI_EXEC(true, false, false) STLMI_EXEC(true, false, true)
+    STLMI_EXEC(true, true, false) STLMI_EXEC(true, true, true)
+#undef STLMI_EXEC
     return hipGetLastError();
 }
 
 hipError_t set_max_lds(size_t bytes)
 {
-    hipError_t e1 = hipFuncSetAttribute((const void*)stl_exec_kernel<false, false>,
-                                        hipFuncAttributeMaxDynamicSharedMemorySize, (int)bytes);
-    hipError_t e2 = hipFuncSetAttribute((const void*)stl_exec_kernel<true, false>,
-                                        hipFuncAttributeMaxDynamicSharedMemorySize, (int)bytes);
-    if (e2 == hipSuccess)
-        e2 = hipFuncSetAttribute((const void*)stl_exec_kernel<true, true>,
-                                 hipFuncAttributeMaxDynamicSharedMemorySize, (int)bytes);
-    if (e2 == hipSuccess)
-        e2 = hipFuncSetAttribute((const void*)stl_exec_kernel<false, true>,
-                                 hipFuncAttributeMaxDynamicSharedMemorySize, (int)bytes);
-    return e1 != hipSuccess ? e1 : e2;
+    const void* fns[] = {(const void*)stl_exec_kernel<false, false, false>, (const void*)stl_exec_kernel<false, false, true>,
+                         (const void*)stl_exec_kernel<false, true, true>,   (const void*)stl_exec_kernel<true, false, false>,
+                         (const void*)stl_exec_kernel<true, false, true>,   (const void*)stl_exec_kernel<true, true, true>};
+    for (const void* f : fns) {
+        const hipError_t e = hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, (int)bytes);
+        if (e != hipSuccess) return e;
+    }
+    return hipSuccess;
 }
 
 size_t fused_lds(int Lc, int n, int D, bool bwd)
