@@ -30,9 +30,6 @@ DEV uint16_t f2bf(float f)
 
 DEV float bf2f(uint16_t h) { return __uint_as_float((uint32_t)h << 16); }
 
-constexpr int TM = 64, TN = 64, TK = 32;
-constexpr int LDK = TK + 8;     // LDS row: 32 k-values and 8 of pad (rows 80 bytes apart fall on distinct banks)
-
 typedef __bf16 bf16x8_t __attribute__((ext_vector_type(8)));
 
 // 8 elements p[0], p[s], .., p[7 s] of which the first nvalid exist (zeros
@@ -50,75 +47,104 @@ DEV void load8(const uint16_t* p, int64_t s, int nvalid, bool vec, uint16_t* v)
 
 DEV bool al16(const void* p) { return (((uintptr_t)p) & 15) == 0; }
 
+// 8 elements of one operand: rows r (of n_r), k-values kk .. along whichever of
+// the two is contiguous (k_cont), zeros outside
+DEV void stage_load(const uint16_t* P, int64_t sr, int64_t sk, bool k_cont, int r, int n_r, int k, int K, uint16_t* v)
+{
+    const int nv = k_cont ? (r < n_r ? max(0, min(8, K - k)) : 0) : (k < K ? max(0, min(8, n_r - r)) : 0);
+    const uint16_t* p = P + (int64_t)(k_cont ? min(r, n_r - 1) : r) * sr + (int64_t)(k_cont ? k : min(k, K - 1)) * sk;
+    const int64_t st = k_cont ? sk : sr;
+    load8(p, st, nv, st == 1 && nv == 8 && al16(p), v);
+}
+
 // C[M,N] = act(A[M,K] B[K,N] + bias) on v_mfma_f32_16x16x32_bf16.  Work-group
-// tile 64x64, four waves of 32x32 (2x2 blocks of 16x16), K in steps of 32.
-// LDS holds A as [m][k] and B as [n][k] (k contiguous), so each lane's MFMA
-// operand (row or column l % 16, k = 8 (l / 16) .. + 7) is one 16-byte read.
-// Each of the 256 threads stages 8 consecutive elements of A and of B along
-// the dimension that is contiguous in memory (one 16-byte load when aligned
-// and in range); any strides work, transposed operands included.
+// tile T x T, four waves of (T/2) x (T/2), K in stages of 2048 / T values: each
+// of the 256 threads stages 8 consecutive elements of A and of B along the
+// dimension that is contiguous in memory (one 16-byte load when aligned and in
+// range); any strides work, transposed operands included.  LDS holds A as
+// [m][k] and B as [n][k] (k contiguous), so each lane's MFMA operand (row or
+// column l % 16, k = 8 (l / 16) .. + 7) is one 16-byte read.
+// The network's products are small (1,024 x 256 x 256): with 64 x 64 tiles they
+// fill a quarter of the chip, and a stage that loads, waits and multiplies is
+// bound by the loads' latency.  So PD stages are in flight in registers, LDS is
+// double-buffered (one barrier per stage), and the tiles are 32 x 32 where 64 x
+// 64 ones would leave compute units with less than two work-groups (measured at
+// 1,024 x 256 x 256: 18 us before; the accumulation order, K ascending in steps
+// of 32, is the same for both).
+template <int T>
 __global__ void __launch_bounds__(256) gemm_bf16_kernel(const uint16_t* A, int64_t sam, int64_t sak,
                                                         const uint16_t* B, int64_t sbk, int64_t sbn, int M, int N,
-                                                        int K, const float* bias, int relu, float* c32,
-                                                        int64_t ldc32, int beta32, uint16_t* c16, int64_t ldc16)
+                                                        int K, const float* bias, int relu, const uint16_t* pos,
+                                                        int64_t ldpos, float* c32, int64_t ldc32, int beta32,
+                                                        uint16_t* c16, int64_t ldc16)
 {
-    __shared__ __align__(16) uint16_t As[TM][LDK];
-    __shared__ __align__(16) uint16_t Bs[TN][LDK];
+    constexpr int TK = 2048 / T, LDK = TK + 8;   // (8 of pad: rows fall on distinct banks)
+    constexpr int PD = 3, W = T / 32;
+    __shared__ __align__(16) uint16_t As[2][T][LDK];
+    __shared__ __align__(16) uint16_t Bs[2][T][LDK];
     const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
-    const int m0 = blockIdx.y * TM, n0 = blockIdx.x * TN;
-    const int wm = (w >> 1) * 32, wn = (w & 1) * 32;
+    const int m0 = blockIdx.y * T, n0 = blockIdx.x * T;
+    const int wm = (w >> 1) * (T / 2), wn = (w & 1) * (T / 2);
     const bool a_k = sak == 1;      // A rows contiguous in k (else chunks run along m)
     const bool b_k = sbk == 1;      // B columns contiguous in k (else chunks run along n)
-    float4_t acc[2][2];
-    for (int i = 0; i < 2; ++i)
-        for (int j = 0; j < 2; ++j) acc[i][j] = float4_t{0.f, 0.f, 0.f, 0.f};
-    for (int k0 = 0; k0 < K; k0 += TK) {
-        uint16_t v[8];
-        if (a_k) {
-            const int r = tid >> 2, kk = (tid & 3) * 8, gm = m0 + r, gk = k0 + kk;
-            const int nv = gm < M ? max(0, min(8, K - gk)) : 0;
-            const uint16_t* p = A + (int64_t)min(gm, M - 1) * sam + (int64_t)gk;
-            load8(p, 1, nv, nv == 8 && al16(p), v);
-            *(uint4*)&As[r][kk] = *(const uint4*)v;
-        } else {
-            const int kk = tid >> 3, m8 = (tid & 7) * 8, gm = m0 + m8, gk = k0 + kk;
-            const int nv = gk < K ? max(0, min(8, M - gm)) : 0;
-            const uint16_t* p = A + (int64_t)gm * sam + (int64_t)min(gk, K - 1) * sak;
-            load8(p, sam, nv, sam == 1 && nv == 8 && al16(p), v);
+    // this thread's chunk: (row, k) of the operand's tile
+    const int kr = tid / (TK / 8), kk = tid % (TK / 8) * 8;          // contiguous in k
+    const int tk = tid / (T / 8), tr = tid % (T / 8) * 8;            // contiguous in m or n
+    const int ar = a_k ? kr : tr, ak = a_k ? kk : tk, br = b_k ? kr : tr, bk = b_k ? kk : tk;
+    const int S = (K + TK - 1) / TK;
+    float4_t acc[W][W];
 #pragma unroll
-            for (int i = 0; i < 8; ++i) As[m8 + i][kk] = v[i];
+    for (int i = 0; i < W; ++i)
+#pragma unroll
+        for (int j = 0; j < W; ++j) acc[i][j] = float4_t{0.f, 0.f, 0.f, 0.f};
+    __align__(16) uint16_t va[PD][8], vb[PD][8];
+#pragma unroll
+    for (int d = 0; d < PD; ++d)
+        if (d < S) {
+            stage_load(A, sam, sak, a_k, m0 + ar, M, d * TK + ak, K, va[d]);
+            stage_load(B, sbn, sbk, b_k, n0 + br, N, d * TK + bk, K, vb[d]);
         }
-        if (b_k) {
-            const int n = tid >> 2, kk = (tid & 3) * 8, gn = n0 + n, gk = k0 + kk;
-            const int nv = gn < N ? max(0, min(8, K - gk)) : 0;
-            const uint16_t* p = B + (int64_t)gk + (int64_t)min(gn, N - 1) * sbn;
-            load8(p, 1, nv, nv == 8 && al16(p), v);
-            *(uint4*)&Bs[n][kk] = *(const uint4*)v;
-        } else {
-            const int kk = tid >> 3, n8 = (tid & 7) * 8, gn = n0 + n8, gk = k0 + kk;
-            const int nv = gk < K ? max(0, min(8, N - gn)) : 0;
-            const uint16_t* p = B + (int64_t)min(gk, K - 1) * sbk + (int64_t)gn * sbn;
-            load8(p, sbn, nv, sbn == 1 && nv == 8 && al16(p), v);
+    for (int s0 = 0; s0 < S; s0 += PD) {
 #pragma unroll
-            for (int i = 0; i < 8; ++i) Bs[n8 + i][kk] = v[i];
+        for (int d = 0; d < PD; ++d) {
+            const int st = s0 + d;
+            if (st >= S) break;
+            const int buf = st & 1;
+            if (a_k) *(uint4*)&As[buf][ar][ak] = *(const uint4*)va[d];
+            else
+#pragma unroll
+                for (int i = 0; i < 8; ++i) As[buf][ar + i][ak] = va[d][i];
+            if (b_k) *(uint4*)&Bs[buf][br][bk] = *(const uint4*)vb[d];
+            else
+#pragma unroll
+                for (int i = 0; i < 8; ++i) Bs[buf][br + i][bk] = vb[d][i];
+            if (st + PD < S) {
+                stage_load(A, sam, sak, a_k, m0 + ar, M, (st + PD) * TK + ak, K, va[d]);
+                stage_load(B, sbn, sbk, b_k, n0 + br, N, (st + PD) * TK + bk, K, vb[d]);
+            }
+            // (a wave writes this buffer again two stages on, behind the next
+            // barrier, which every wave reaches after its reads of it)
+            __syncthreads();
+#pragma unroll
+            for (int k = 0; k < TK; k += 32) {
+                const int kq = k + 8 * (lane >> 4);
+                bf16x8_t a[W], b[W];
+#pragma unroll
+                for (int i = 0; i < W; ++i) a[i] = *(const bf16x8_t*)&As[buf][wm + 16 * i + (lane & 15)][kq];
+#pragma unroll
+                for (int j = 0; j < W; ++j) b[j] = *(const bf16x8_t*)&Bs[buf][wn + 16 * j + (lane & 15)][kq];
+#pragma unroll
+                for (int i = 0; i < W; ++i)
+#pragma unroll
+                    for (int j = 0; j < W; ++j)
+                        acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[i], b[j], acc[i][j], 0, 0, 0);
+            }
         }
-        __syncthreads();
-        const int kq = 8 * (lane >> 4);
-        bf16x8_t a[2], b[2];
-#pragma unroll
-        for (int i = 0; i < 2; ++i) a[i] = *(const bf16x8_t*)&As[wm + 16 * i + (lane & 15)][kq];
-#pragma unroll
-        for (int j = 0; j < 2; ++j) b[j] = *(const bf16x8_t*)&Bs[wn + 16 * j + (lane & 15)][kq];
-#pragma unroll
-        for (int i = 0; i < 2; ++i)
-#pragma unroll
-            for (int j = 0; j < 2; ++j) acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[i], b[j], acc[i][j], 0, 0, 0);
-        __syncthreads();
     }
 #pragma unroll
-    for (int i = 0; i < 2; ++i)
+    for (int i = 0; i < W; ++i)
 #pragma unroll
-        for (int j = 0; j < 2; ++j)
+        for (int j = 0; j < W; ++j)
 #pragma unroll
             for (int q = 0; q < 4; ++q) {
                 const int row = m0 + wm + 16 * i + 4 * (lane >> 4) + q;
@@ -127,6 +153,7 @@ __global__ void __launch_bounds__(256) gemm_bf16_kernel(const uint16_t* A, int64
                 float v = acc[i][j][q];
                 if (bias) v += bias[col];
                 if (relu) v = v > 0.f ? v : 0.f;
+                if (pos && !(bf2f(pos[(int64_t)row * ldpos + col]) > 0.f)) v = 0.f;
                 if (c32) {
                     float* p = c32 + (int64_t)row * ldc32 + col;
                     *p = beta32 ? *p + v : v;
@@ -150,55 +177,102 @@ __global__ void relu_grad_kernel(const float* g, const uint16_t* h, uint16_t* g1
     }
 }
 
-// one thread per column, rows summed in order (deterministic)
-__global__ void colsum_kernel(const float* x, int rows, int cols, int64_t ld, float* out)
+DEV float as_float(float v) { return v; }
+DEV float as_float(uint16_t v) { return bf2f(v); }
+
+// Column sums in a fixed order: a work-group takes 16 columns, 64 groups of
+// rows (group r the rows r, r + 64, ..), whose sums a tree adds in LDS.  One
+// thread per column walked 1,024 rows one load at a time (236 us).
+template <class T>
+__global__ void __launch_bounds__(1024) colsum_kernel(const T* x, int rows, int cols, int64_t ld, float* out)
 {
-    const int j = blockIdx.x * blockDim.x + threadIdx.x;
-    if (j >= cols) return;
+    __shared__ float red[64][17];
+    const int c = threadIdx.x & 15, r = threadIdx.x >> 4;
+    const int j = blockIdx.x * 16 + c;
     float s = 0.f;
-    for (int i = 0; i < rows; ++i) s += x[(int64_t)i * ld + j];
-    out[j] = s;
+    if (j < cols) {
+#pragma unroll 8
+        for (int i = r; i < rows; i += 64) s += as_float(x[(int64_t)i * ld + j]);
+    }
+    red[r][c] = s;
+    __syncthreads();
+    for (int k = 32; k > 0; k >>= 1) {
+        if (r < k) red[r][c] += red[r + k][c];
+        __syncthreads();
+    }
+    if (r == 0 && j < cols) out[j] = red[0][c];
 }
 
-__global__ void mse_grad_kernel(const float* y, const float* t, float* g, float* partial, int64_t n)
+// work-group sum of one float per thread (256 threads), in thread 0
+DEV float wg_sum256(float s)
 {
     __shared__ float red[256];
-    float s = 0.f;
-    const float sc = 2.f / (float)n;
-    for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (int64_t)gridDim.x * blockDim.x) {
-        const float d = y[i] - t[i];
-        g[i] = sc * d;
-        s += d * d;
-    }
     red[threadIdx.x] = s;
     __syncthreads();
-    for (int k = blockDim.x >> 1; k > 0; k >>= 1) {
+    for (int k = 128; k > 0; k >>= 1) {
         if ((int)threadIdx.x < k) red[threadIdx.x] += red[threadIdx.x + k];
         __syncthreads();
     }
-    if (partial && threadIdx.x == 0) partial[blockIdx.x] = red[0];
+    return red[0];
 }
 
-__global__ void finish_loss_kernel(const float* partial, int nb, int64_t n, float* loss)
+// g = 2 (y - t) / n; with more than one work-group the partial sums of
+// (y - t)^2 stand in for g[0 .. grid) until mse_finish_kernel has read them
+// (no scratch buffer is passed, and one work-group took 463 us for 409,600
+// elements); one work-group writes its sum to loss
+__global__ void __launch_bounds__(256) mse_grad_kernel(const float* y, const float* t, float* g, float* loss, int64_t n)
 {
-    if (threadIdx.x != 0) return;
+    const float sc = 2.f / (float)n;
+    const int64_t held = loss && gridDim.x > 1 ? gridDim.x : 0;
     float s = 0.f;
-    for (int b = 0; b < nb; ++b) s += partial[b];
-    loss[0] = s / (float)n;
+#pragma unroll 4
+    for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < n; i += (int64_t)gridDim.x * 256) {
+        const float d = y[i] - t[i];
+        if (i >= held) g[i] = sc * d;
+        s += d * d;
+    }
+    if (!loss) return;
+    s = wg_sum256(s);
+    if (threadIdx.x != 0) return;
+    if (held) g[blockIdx.x] = s;
+    else loss[0] = s / (float)n;
 }
 
-__global__ void adam_kernel(float* w, const float* g, float* m, float* v, uint16_t* w16, int64_t n, float lr, float b1,
-                            float b2, float eps, float c1, float c2)
+__global__ void __launch_bounds__(256) mse_finish_kernel(const float* y, const float* t, float* g, float* loss, int nb,
+                                                         int64_t n)
 {
-    for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (int64_t)gridDim.x * blockDim.x) {
-        const float gi = g[i];
-        const float mi = b1 * m[i] + (1.f - b1) * gi;
-        const float vi = b2 * v[i] + (1.f - b2) * gi * gi;
-        m[i] = mi;
-        v[i] = vi;
-        const float wi = w[i] - lr * (mi / c1) / (sqrtf(vi / c2) + eps);
-        w[i] = wi;
-        if (w16) w16[i] = f2bf(wi);
+    const int i = threadIdx.x;
+    const float s = wg_sum256(i < nb ? g[i] : 0.f);      // (every partial is read before the first is overwritten)
+    if (i == 0) loss[0] = s / (float)n;
+    if (i < nb) g[i] = 2.f / (float)n * (y[i] - t[i]);
+}
+
+// Adam on up to ADAM_MAX tensors in one launch (a launch per tensor of a small
+// network costs more than its work); tensor k takes the work-groups
+// first[k] .. first[k+1]-1
+constexpr int ADAM_MAX = 16;
+struct AdamArgs {
+    stl_adam_tensor t[ADAM_MAX];
+    int first[ADAM_MAX + 1];
+    int n;
+    float lr, b1, b2, eps, c1, c2;
+};
+
+__global__ void __launch_bounds__(256) adam_kernel(AdamArgs A)
+{
+    int k = 0;
+    while (k + 1 < A.n && (int)blockIdx.x >= A.first[k + 1]) ++k;
+    const stl_adam_tensor t = A.t[k];
+    const int64_t nb = A.first[k + 1] - A.first[k];
+    for (int64_t i = (int64_t)(blockIdx.x - A.first[k]) * 256 + threadIdx.x; i < t.n; i += nb * 256) {
+        const float gi = t.g[i];
+        const float mi = A.b1 * t.m[i] + (1.f - A.b1) * gi;
+        const float vi = A.b2 * t.v[i] + (1.f - A.b2) * gi * gi;
+        t.m[i] = mi;
+        t.v[i] = vi;
+        const float wi = t.w[i] - A.lr * (mi / A.c1) / (sqrtf(vi / A.c2) + A.eps);
+        t.w[i] = wi;
+        if (t.w16) t.w16[i] = f2bf(wi);
     }
 }
 
@@ -253,6 +327,25 @@ stl_status launched(const char* what)
 }
 }  // namespace
 
+static stl_status gemm(const char* what, const uint16_t* A, int64_t sam, int64_t sak, const uint16_t* B, int64_t sbk,
+                       int64_t sbn, int32_t M, int32_t N, int32_t K, const float* bias, int32_t relu,
+                       const uint16_t* pos, int64_t ldpos, float* c32, int64_t ldc32, int32_t beta32, uint16_t* c16,
+                       int64_t ldc16, void* stream)
+{
+    const int64_t g64 = ((int64_t)M + 63) / 64 * (((int64_t)N + 63) / 64);
+    // 32 x 32 tiles below two 64 x 64 work-groups per compute unit (256 of them)
+    const int T = g64 < 512 ? 32 : 64;
+    const dim3 grid((N + T - 1) / T, (M + T - 1) / T);
+    if (grid.y > 65535) return mfail(STL_E_UNSUPPORTED, "stl_bf16_gemm: M too large");
+    if (T == 32)
+        hipLaunchKernelGGL(gemm_bf16_kernel<32>, grid, dim3(256), 0, (hipStream_t)stream, A, sam, sak, B, sbk, sbn, M, N,
+                           K, bias, relu, pos, ldpos, c32, ldc32, beta32, c16, ldc16);
+    else
+        hipLaunchKernelGGL(gemm_bf16_kernel<64>, grid, dim3(256), 0, (hipStream_t)stream, A, sam, sak, B, sbk, sbn, M, N,
+                           K, bias, relu, pos, ldpos, c32, ldc32, beta32, c16, ldc16);
+    return launched(what);
+}
+
 extern "C" stl_status stl_bf16_gemm(const uint16_t* A, int64_t sam, int64_t sak, const uint16_t* B, int64_t sbk,
                                     int64_t sbn, int32_t M, int32_t N, int32_t K, const float* bias, int32_t relu,
                                     float* c32, int64_t ldc32, int32_t beta32, uint16_t* c16, int64_t ldc16,
@@ -261,11 +354,19 @@ extern "C" stl_status stl_bf16_gemm(const uint16_t* A, int64_t sam, int64_t sak,
     if (M < 0 || N < 0 || K < 0) return mfail(STL_E_ARG, "stl_bf16_gemm: negative size");
     if (M == 0 || N == 0) return STL_OK;
     if ((K > 0 && (!A || !B)) || (!c32 && !c16)) return mfail(STL_E_ARG, "stl_bf16_gemm: null pointer");
-    if ((int64_t)(M + TM - 1) / TM > 65535) return mfail(STL_E_UNSUPPORTED, "stl_bf16_gemm: M too large");
-    dim3 grid((N + TN - 1) / TN, (M + TM - 1) / TM);
-    hipLaunchKernelGGL(gemm_bf16_kernel, grid, dim3(256), 0, (hipStream_t)stream, A, sam, sak, B, sbk, sbn, M, N, K,
-                       bias, relu, c32, ldc32, beta32, c16, ldc16);
-    return launched("stl_bf16_gemm");
+    return gemm("stl_bf16_gemm", A, sam, sak, B, sbk, sbn, M, N, K, bias, relu, nullptr, 0, c32, ldc32, beta32, c16,
+                ldc16, stream);
+}
+
+extern "C" stl_status stl_bf16_gemm_relu_grad(const uint16_t* A, int64_t sam, int64_t sak, const uint16_t* B,
+                                              int64_t sbk, int64_t sbn, int32_t M, int32_t N, int32_t K,
+                                              const uint16_t* h, int64_t ldh, uint16_t* g16, int64_t ldg, void* stream)
+{
+    if (M < 0 || N < 0 || K < 0) return mfail(STL_E_ARG, "stl_bf16_gemm_relu_grad: negative size");
+    if (M == 0 || N == 0) return STL_OK;
+    if ((K > 0 && (!A || !B)) || !h || !g16) return mfail(STL_E_ARG, "stl_bf16_gemm_relu_grad: null pointer");
+    return gemm("stl_bf16_gemm_relu_grad", A, sam, sak, B, sbk, sbn, M, N, K, nullptr, 0, h, ldh, nullptr, 0, 0, g16, ldg,
+                stream);
 }
 
 extern "C" stl_status stl_cast_bf16(const float* x, uint16_t* y, int64_t n, void* stream)
@@ -288,32 +389,74 @@ extern "C" stl_status stl_colsum(const float* x, int32_t rows, int32_t cols, int
 {
     if (rows < 0 || cols < 0 || (cols > 0 && (!x || !out))) return mfail(STL_E_ARG, "stl_colsum: bad arguments");
     if (cols == 0) return STL_OK;
-    hipLaunchKernelGGL(colsum_kernel, dim3((cols + 255) / 256), dim3(256), 0, (hipStream_t)stream, x, rows, cols,
-                       ld, out);
+    hipLaunchKernelGGL(colsum_kernel<float>, dim3((cols + 15) / 16), dim3(1024), 0, (hipStream_t)stream, x, rows, cols, ld,
+                       out);
     return launched("stl_colsum");
+}
+
+extern "C" stl_status stl_colsum_bf16(const uint16_t* x, int32_t rows, int32_t cols, int64_t ld, float* out, void* stream)
+{
+    if (rows < 0 || cols < 0 || (cols > 0 && (!x || !out))) return mfail(STL_E_ARG, "stl_colsum_bf16: bad arguments");
+    if (cols == 0) return STL_OK;
+    hipLaunchKernelGGL(colsum_kernel<uint16_t>, dim3((cols + 15) / 16), dim3(1024), 0, (hipStream_t)stream, x, rows, cols,
+                       ld, out);
+    return launched("stl_colsum_bf16");
 }
 
 extern "C" stl_status stl_mse_grad(const float* y, const float* t, float* g, float* loss, int64_t n, void* stream)
 {
     if (n <= 0 || !y || !t || !g) return mfail(STL_E_ARG, "stl_mse_grad: bad arguments");
-    // partial sums live in the first blocks of `loss` (caller passes >= 1 float);
-    // the reduction uses a single block so that no scratch buffer is needed
-    hipLaunchKernelGGL(mse_grad_kernel, dim3(1), dim3(256), 0, (hipStream_t)stream, y, t, g, loss, n);
+    // g holds the partial sums between the two launches, so an in-place g keeps
+    // to one work-group, as small n does (two launches cost about 10 us)
+    auto apart = [&](const float* a) { return a + n <= g || g + n <= a; };
+    const int nb = n >= 16384 && (!loss || (apart(y) && apart(t))) ? (int)(n / 4096 < 256 ? n / 4096 : 256) : 1;
+    hipLaunchKernelGGL(mse_grad_kernel, dim3(nb), dim3(256), 0, (hipStream_t)stream, y, t, g, loss, n);
     stl_status s = launched("stl_mse_grad");
-    if (s != STL_OK || !loss) return s;
-    hipLaunchKernelGGL(finish_loss_kernel, dim3(1), dim3(64), 0, (hipStream_t)stream, loss, 1, n, loss);
+    if (s != STL_OK || !loss || nb == 1) return s;
+    hipLaunchKernelGGL(mse_finish_kernel, dim3(1), dim3(256), 0, (hipStream_t)stream, y, t, g, loss, nb, n);
     return launched("stl_mse_grad");
+}
+
+extern "C" stl_status stl_adam_step_multi(const stl_adam_tensor* tensors, int32_t n_tensors, float lr, float b1, float b2,
+                                          float eps, int32_t step, void* stream)
+{
+    if (n_tensors < 0 || step < 1 || (n_tensors > 0 && !tensors))
+        return mfail(STL_E_ARG, "stl_adam_step_multi: bad arguments");
+    for (int k = 0; k < n_tensors; ++k) {
+        const stl_adam_tensor& t = tensors[k];
+        if (t.n < 0 || (t.n > 0 && (!t.w || !t.g || !t.m || !t.v)))
+            return mfail(STL_E_ARG, "stl_adam_step_multi: bad tensor");
+    }
+    for (int k0 = 0; k0 < n_tensors; k0 += ADAM_MAX) {
+        AdamArgs A;
+        A.n = 0;
+        A.first[0] = 0;
+        for (int k = k0; k < n_tensors && k < k0 + ADAM_MAX; ++k) {
+            if (tensors[k].n == 0) continue;
+            A.t[A.n] = tensors[k];
+            A.first[A.n + 1] = A.first[A.n] + grid_for(tensors[k].n);
+            ++A.n;
+        }
+        if (A.n == 0) continue;
+        A.lr = lr;
+        A.b1 = b1;
+        A.b2 = b2;
+        A.eps = eps;
+        A.c1 = 1.f - powf(b1, (float)step);
+        A.c2 = 1.f - powf(b2, (float)step);
+        hipLaunchKernelGGL(adam_kernel, dim3(A.first[A.n]), dim3(256), 0, (hipStream_t)stream, A);
+        const stl_status s = launched("stl_adam_step_multi");
+        if (s != STL_OK) return s;
+    }
+    return STL_OK;
 }
 
 extern "C" stl_status stl_adam_step(float* w, const float* g, float* m, float* v, uint16_t* w16, int64_t n, float lr,
                                     float b1, float b2, float eps, int32_t step, void* stream)
 {
     if (n < 0 || step < 1 || (n > 0 && (!w || !g || !m || !v))) return mfail(STL_E_ARG, "stl_adam_step: bad arguments");
-    if (n == 0) return STL_OK;
-    const float c1 = 1.f - powf(b1, (float)step), c2 = 1.f - powf(b2, (float)step);
-    hipLaunchKernelGGL(adam_kernel, dim3(grid_for(n)), dim3(256), 0, (hipStream_t)stream, w, g, m, v, w16, n, lr, b1,
-                       b2, eps, c1, c2);
-    return launched("stl_adam_step");
+    const stl_adam_tensor t = {w, g, m, v, w16, n};
+    return stl_adam_step_multi(&t, 1, lr, b1, b2, eps, step, stream);
 }
 
 extern "C" stl_status stl_ascent_update(float* x, const float* dx, const int32_t* active, int64_t N, int32_t T,

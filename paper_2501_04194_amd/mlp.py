@@ -17,6 +17,10 @@ from . import stl
 _c = None
 
 
+class AdamTensor(ctypes.Structure):
+    _fields_ = [(f, ctypes.c_void_p) for f in ("w", "g", "m", "v", "w16")] + [("n", ctypes.c_int64)]
+
+
 def _lib():
     global _c
     if _c is not None:
@@ -24,13 +28,16 @@ def _lib():
     L = stl.lib()
     vp, i32, i64, f32 = ctypes.c_void_p, ctypes.c_int32, ctypes.c_int64, ctypes.c_float
     L.stl_bf16_gemm.argtypes = [vp, i64, i64, vp, i64, i64, i32, i32, i32, vp, i32, vp, i64, i32, vp, i64, vp]
+    L.stl_bf16_gemm_relu_grad.argtypes = [vp, i64, i64, vp, i64, i64, i32, i32, i32, vp, i64, vp, i64, vp]
+    L.stl_colsum_bf16.argtypes = [vp, i32, i32, i64, vp, vp]
+    L.stl_adam_step_multi.argtypes = [ctypes.POINTER(AdamTensor), i32, f32, f32, f32, f32, i32, vp]
     L.stl_cast_bf16.argtypes = [vp, vp, i64, vp]
     L.stl_relu_grad_bf16.argtypes = [vp, vp, vp, i64, vp]
     L.stl_colsum.argtypes = [vp, i32, i32, i64, vp, vp]
     L.stl_mse_grad.argtypes = [vp, vp, vp, vp, i64, vp]
     L.stl_adam_step.argtypes = [vp, vp, vp, vp, vp, i64, f32, f32, f32, f32, i32, vp]
     L.stl_ascent_update.argtypes = [vp, vp, vp, i64, i32, i32, i32, i32, f32, vp]
-    for f in ("stl_bf16_gemm", "stl_cast_bf16", "stl_relu_grad_bf16", "stl_colsum", "stl_mse_grad",
+    for f in ("stl_bf16_gemm", "stl_bf16_gemm_relu_grad", "stl_colsum_bf16", "stl_adam_step_multi", "stl_cast_bf16", "stl_relu_grad_bf16", "stl_colsum", "stl_mse_grad",
               "stl_adam_step", "stl_ascent_update"):
         getattr(L, f).restype = ctypes.c_int
     _c = L
@@ -52,6 +59,12 @@ def gemm(A, B, M, N, K, sam, sak, sbk, sbn, bias=None, relu=False, c32=None, ldc
                                     int(beta), _p(c16), ldc16, _s(torch, A.device)))
 
 
+def gemm_relu_grad(A, B, M, N, K, sam, sak, sbk, sbn, h, ldh, g16, ldg):
+    import torch
+    stl._check(_lib().stl_bf16_gemm_relu_grad(_p(A), sam, sak, _p(B), sbk, sbn, M, N, K, _p(h), ldh, _p(g16), ldg,
+                                              _s(torch, A.device)))
+
+
 def cast_bf16(x, y):
     import torch
     stl._check(_lib().stl_cast_bf16(_p(x), _p(y), x.numel(), _s(torch, x.device)))
@@ -67,6 +80,11 @@ def colsum(x, rows, cols, ld, out):
     stl._check(_lib().stl_colsum(_p(x), rows, cols, ld, _p(out), _s(torch, x.device)))
 
 
+def colsum_bf16(x, rows, cols, ld, out):
+    import torch
+    stl._check(_lib().stl_colsum_bf16(_p(x), rows, cols, ld, _p(out), _s(torch, x.device)))
+
+
 def mse_grad(y, t, g, loss):
     import torch
     stl._check(_lib().stl_mse_grad(_p(y), _p(t), _p(g), _p(loss), y.numel(), _s(torch, y.device)))
@@ -76,6 +94,14 @@ def adam_step(w, g, m, v, w16, lr, b1, b2, eps, step):
     import torch
     stl._check(_lib().stl_adam_step(_p(w), _p(g), _p(m), _p(v), _p(w16), w.numel(), lr, b1, b2, eps, step,
                                     _s(torch, w.device)))
+
+
+def adam_step_multi(tensors, lr, b1, b2, eps, step):
+    """tensors: (w, g, m, v, w16 or None) of one device."""
+    import torch
+    t = (AdamTensor * len(tensors))(*[AdamTensor(*[None if x is None else x.data_ptr() for x in q], q[0].numel())
+                                      for q in tensors])
+    stl._check(_lib().stl_adam_step_multi(t, len(tensors), lr, b1, b2, eps, step, _s(torch, tensors[0][0].device)))
 
 
 def ascent_update(x, dx, active, lr, t0=1, d_upd=2):
@@ -143,46 +169,36 @@ class BF16MLP:
 
         Per layer, from the last: the gradient with respect to the
         pre-activation is rounded to BF16 (after the ReLU mask of a hidden
-        layer); dW = g^T h_in and db = column sums of g (both FP32), and the
-        gradient passed down is g W (FP32)."""
+        layer); dW = g^T h_in and db = column sums of g (both FP32); the
+        gradient passed down, g W, is masked in FP32 in the product's epilogue."""
         import torch
         acts = self._acts
         N = dOut.shape[0]
         dW = [None] * self.n_layers
         db = [None] * self.n_layers
-        g32 = dOut.contiguous()
+        dOut = dOut.contiguous()
+        g16 = torch.empty((N, self.sizes[-1]), dtype=torch.int16, device=self.dev)
+        relu_grad_bf16(dOut, None, g16)
         for l in range(self.n_layers - 1, -1, -1):
             I, O = self.sizes[l], self.sizes[l + 1]
-            g16 = torch.empty((N, O), dtype=torch.int16, device=self.dev)
-            relu_grad_bf16(g32, None if l == self.n_layers - 1 else acts[l + 1], g16)
             dW[l] = torch.empty((O, I), dtype=torch.float32, device=self.dev)
             gemm(g16, acts[l], O, I, N, 1, O, I, 1, c32=dW[l], ldc32=I)          # g^T [O,N] h [N,I]
             db[l] = torch.empty(O, dtype=torch.float32, device=self.dev)
-            # widen the BF16 gradient exactly (product with the identity) and sum its rows
-            wide = torch.empty((N, O), dtype=torch.float32, device=self.dev)
-            gemm(g16, self._eye16(O), N, O, O, O, 1, O, 1, c32=wide, ldc32=O)
-            colsum(wide, N, O, O, db[l])
+            colsum_bf16(g16, N, O, O, db[l])
             if l > 0:
-                g32 = torch.empty((N, I), dtype=torch.float32, device=self.dev)
-                gemm(g16, self.W16[l], N, I, O, O, 1, I, 1, c32=g32, ldc32=I)   # g [N,O] W [O,I]
+                # g [N,O] W [O,I], masked by the activation it passes back through
+                gn = torch.empty((N, I), dtype=torch.int16, device=self.dev)
+                gemm_relu_grad(g16, self.W16[l], N, I, O, O, 1, I, 1, acts[l], I, gn, I)
+                g16 = gn
         return dW, db
-
-    def _eye16(self, n):
-        import torch
-        if not hasattr(self, "_eyes"):
-            self._eyes = {}
-        if n not in self._eyes:
-            e = torch.eye(n, dtype=torch.float32, device=self.dev)
-            e16 = torch.empty((n, n), dtype=torch.int16, device=self.dev)
-            cast_bf16(e, e16)
-            self._eyes[n] = e16
-        return self._eyes[n]
 
     def adam(self, dW, db, lr=1e-3, b1=0.9, b2=0.999, eps=1e-8):
         self.step_count += 1
+        t = []
         for l in range(self.n_layers):
-            adam_step(self.W[l], dW[l], self.mW[l], self.vW[l], self.W16[l], lr, b1, b2, eps, self.step_count)
-            adam_step(self.b[l], db[l], self.mb[l], self.vb[l], None, lr, b1, b2, eps, self.step_count)
+            t.append((self.W[l], dW[l], self.mW[l], self.vW[l], self.W16[l]))
+            t.append((self.b[l], db[l], self.mb[l], self.vb[l], None))
+        adam_step_multi(t, lr, b1, b2, eps, self.step_count)
 
     def numpy_weights(self):
         return [(w.cpu().numpy().astype(np.float64), b.cpu().numpy().astype(np.float64))
