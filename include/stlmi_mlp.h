@@ -45,16 +45,6 @@ stl_status stl_bf16_gemm(const uint16_t* A, int64_t sam, int64_t sak, const uint
                          int64_t sbn, int32_t M, int32_t N, int32_t K, const float* bias, int32_t relu,
                          float* c32, int64_t ldc32, int32_t beta32, uint16_t* c16, int64_t ldc16, void* stream);
 
-/*
- * The gradient of a hidden layer's pre-activation in one product: g16 =
- * bf16((A * B) * (h > 0)), h the BF16 post-activation (M x N, h[m*ldh + n]),
- * g16 M x N (g16[m*ldg + n]); A and B as in stl_bf16_gemm.  The same bits as
- * stl_bf16_gemm into FP32 followed by stl_relu_grad_bf16.
- */
-stl_status stl_bf16_gemm_relu_grad(const uint16_t* A, int64_t sam, int64_t sak, const uint16_t* B, int64_t sbk,
-                                   int64_t sbn, int32_t M, int32_t N, int32_t K, const uint16_t* h, int64_t ldh,
-                                   uint16_t* g16, int64_t ldg, void* stream);
-
 /* y[i] = bf16(x[i]) (round to nearest even), i < n. */
 stl_status stl_cast_bf16(const float* x, uint16_t* y, int64_t n, void* stream);
 
@@ -66,9 +56,6 @@ stl_status stl_relu_grad_bf16(const float* g, const uint16_t* h, uint16_t* g16, 
 
 /* out[j] = sum_i x[i*ld + j] for j < cols, i < rows (FP32, fixed order). */
 stl_status stl_colsum(const float* x, int32_t rows, int32_t cols, int64_t ld, float* out, void* stream);
-
-/* The same over BF16 x (widened exactly, FP32 sums). */
-stl_status stl_colsum_bf16(const uint16_t* x, int32_t rows, int32_t cols, int64_t ld, float* out, void* stream);
 
 /*
  * Mean-squared error: g[i] = 2 (y[i] - t[i]) / n and loss[0] = sum (y-t)^2 / n
@@ -84,18 +71,6 @@ stl_status stl_mse_grad(const float* y, const float* t, float* g, float* loss, i
  */
 stl_status stl_adam_step(float* w, const float* g, float* m, float* v, uint16_t* w16, int64_t n, float lr,
                          float b1, float b2, float eps, int32_t step, void* stream);
-
-/* The same for several tensors (host array; one launch per 16 of them). */
-typedef struct {
-    float* w;
-    const float* g;
-    float* m;
-    float* v;
-    uint16_t* w16;
-    int64_t n;
-} stl_adam_tensor;
-stl_status stl_adam_step_multi(const stl_adam_tensor* tensors, int32_t n_tensors, float lr, float b1, float b2,
-                               float eps, int32_t step, void* stream);
 
 /*
  * Gradient-ascent step on trajectories x [N, T, D]:

@@ -2,7 +2,7 @@
 // cores (v_mfma_f32_16x16x32_bf16, FP32 accumulation) with a fused
 // bias/ReLU epilogue, BF16 rounding, ReLU derivative mask, column sums, MSE
 // gradient, Adam and the trajectory gradient-ascent step.  C ABI in
-// include/stlmi_mlp.h.
+// include/stlmi_mlp.h and mlp_step.h.
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 #include <math.h>
@@ -11,7 +11,7 @@
 #include <cstdio>
 #include <string>
 
-#include "../../include/stlmi_mlp.h"
+#include "mlp_step.h"
 
 namespace stlmi_mlp {
 
