@@ -155,16 +155,18 @@ struct Env {
 
 // value of another lane by a DPP move (0x110 + k: row_shr:k within rows of 16
 // lanes, 0x142: lane 15 of the row below, 0x143: lane 31, 0x138: wave_shr:1;
-// lanes without a source read 0), for types of 8 bytes
+// 0xB1, 0x4E: lanes 1 and 2 apart in a quad, 0x141, 0x140: mirrored halves of a
+// row and rows; lanes without a source read 0), for types of 4 or 8 bytes
 template <int CTRL, class T>
 DEV T dpp8(T v)
 {
-    static_assert(sizeof(T) == 8, "two words");
-    int w[2];
-    __builtin_memcpy(w, &v, 8);
-    w[0] = __builtin_amdgcn_update_dpp(0, w[0], CTRL, 0xF, 0xF, true);
-    w[1] = __builtin_amdgcn_update_dpp(0, w[1], CTRL, 0xF, 0xF, true);
-    __builtin_memcpy(&v, w, 8);
+    constexpr int N = sizeof(T) / 4;
+    static_assert(sizeof(T) == 4 * N && N <= 2, "one or two words");
+    int w[N];
+    __builtin_memcpy(w, &v, sizeof(T));
+#pragma unroll
+    for (int i = 0; i < N; ++i) w[i] = __builtin_amdgcn_update_dpp(0, w[i], CTRL, 0xF, 0xF, true);
+    __builtin_memcpy(&v, w, sizeof(T));
     return v;
 }
 
