@@ -136,7 +136,15 @@ stl_status geometry(const stl_plan* plan, const stl_batch* bt, const stl_launch*
 {
     DevInfo& di = devinfo();
     const DevPlan& dp = trace ? plan->dev_trace : plan->dev;
-    int nt = cfg && cfg->threads ? cfg->threads : 256;
+    // Default work-group size (one work-group per trajectory).  With enough
+    // trajectories to fill the chip: 128 up to 128 samples (1,000 reach-avoid
+    // trajectories of 100 samples, forward / backward: 12.3 / 22.4 us against 14.1 /
+    // 26.3 with 256), 256 beyond (200 samples: 15.2 / 29.4 against 16.6 / 34.1), and
+    // 512 from 768 samples on for plans without a smooth Until, whose scans then
+    // have one tile per wave (1,000 samples: 36.5 / 84.1 against 42.7 / 104.6; the
+    // smooth Until's lanes want the registers: 88 / 350 against 70 / 249).
+    const int want0 = bt->T <= 128 ? 128 : bt->T < 768 || plan->until_b >= 0 || bt->offsets ? 256 : 512;
+    int nt = cfg && cfg->threads ? cfg->threads : want0;
     if (nt != 64 && nt != 128 && nt != 256 && nt != 512) return fail(STL_E_ARG, "threads must be 64, 128, 256 or 512");
     if (bt->T < 1 || bt->T > (1 << 24)) return fail(STL_E_SHAPE, "T must be in [1, 2^24]");
     int Lc = (int)((bt->T + 3) / 4 * 4);
@@ -153,6 +161,9 @@ stl_status geometry(const stl_plan* plan, const stl_batch* bt, const stl_launch*
     auto until_lds = [&](int threads, bool glob) {
         return until_lds_bytes(threads, ub, bwd, glob ? until_tile(threads) : 0, Lc);
     };
+    if (!(cfg && cfg->threads) && nt == 512 &&
+        ((size_t)nslots * Lc + scratch(nt)) * sizeof(float) + until_lds(nt, false) > di.lds_max)
+        nt = 256;
     size_t arena = (size_t)nslots * Lc + scratch(nt);
     size_t lds = arena * sizeof(float) + until_lds(nt, false);
     bool global = (cfg && cfg->global_slots) || lds > di.lds_max;
@@ -472,10 +483,11 @@ static stl_status run(const stl_plan* plan, const stl_batch* bt, const float* pa
         e = launch_exec(bwd, dp, b, kf, g.grid, g.nt, g.lds_bytes, st);
     } else {
         if (bwd && dp.n_masks == 0) ka.gp_zero = gparams;
+        else if (bwd && bt->B == 1 && !bt->offsets) ka.gp_one = gparams;
         e = launch_exec(bwd, dp, b, ka, g.grid, g.nt, g.lds_bytes, st);
     }
     if (e != hipSuccess) return fail(STL_E_HIP, "kernel launch failed: %s", hipGetErrorString(e));
-    if (bwd && gparams && !ka.gp_zero) {
+    if (bwd && gparams && !ka.gp_zero && !ka.gp_one) {
         e = launch_reduce_params(ka.mask_part, bt->B, dp, gparams, st);
         if (e != hipSuccess) return fail(STL_E_HIP, "launch failed: %s", hipGetErrorString(e));
     }

@@ -2516,6 +2516,18 @@ DEV bool next_item(const KArgs& ka, Shared& sh, int64_t& item, bool first, int64
     return true;
 }
 
+// the only trajectory's mask partials (written by this thread) are the
+// parameter gradients: no reduction launch
+DEV void gp_from_partials(const DevPlan& P, const float* mp, float* gp)
+{
+    for (int p = 0; p < P.n_params; ++p) {
+        float s = 0.f;
+        for (int q = 0; q < 2 * P.n_masks; ++q)
+            if (P.mask_param[q >> 1] + (q & 1) == p) s += mp[q];
+        gp[p] = s;
+    }
+}
+
 // One word of every line of the plan that the program uses, requested at
 // once: the argument segment lies in host memory, and a line fetched when an
 // instruction is reached costs the program 0.5 to 1 us each time.
@@ -2652,6 +2664,7 @@ __global__ void __launch_bounds__(MAX_NT) stl_exec_kernel(DevPlan plan, Batch bt
             }
             e.tid = exec_tid();
             op_dx(e, ka.dx + off * bt.D);
+            if (FULL && ka.gp_one && e.tid == 0) gp_from_partials(*P, mp, ka.gp_one);
             __syncthreads();
         }
     }

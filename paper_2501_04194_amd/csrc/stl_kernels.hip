@@ -8,16 +8,27 @@ namespace stlmi {
 // rows and in a fixed order, of every (mask, bound) column of the partials
 // whose parameter index is p (two mask nodes may share a, b); parameters no
 // mask bound names get 0.  The kernels overwrite gp, they never accumulate.
-__global__ void __launch_bounds__(1024) stl_reduce_params(const float* part, int64_t rows, int n_masks, DevPlan plan,
-                                                          float* gp)
+struct ReduceArgs {              // (not the whole plan: the argument segment is copied for every launch)
+    const float* part;
+    float* gp;
+    int64_t rows;
+    int n_masks;
+    int mask_param[MAX_MASKS];
+};
+
+__global__ void __launch_bounds__(1024) stl_reduce_params(ReduceArgs A)
 {
+    const float* part = A.part;
+    float* gp = A.gp;
+    const int64_t rows = A.rows;
+    const int n_masks = A.n_masks;
     __shared__ float red[1024];
     const int tid = threadIdx.x;
     const int p = blockIdx.x;
     int cols[2 * MAX_MASKS];
     int nc = 0;
     for (int q = 0; q < 2 * n_masks; ++q)
-        if (plan.mask_param[q >> 1] + (q & 1) == p) cols[nc++] = q;
+        if (A.mask_param[q >> 1] + (q & 1) == p) cols[nc++] = q;
     if (nc == 0) {
         if (tid == 0) gp[p] = 0.f;
         return;
@@ -206,7 +217,13 @@ hipError_t launch_fill_int(int* p, int64_t n, int v, hipStream_t s)
 hipError_t launch_reduce_params(const float* part, int64_t B, const DevPlan& plan, float* gp, hipStream_t s)
 {
     if (plan.n_params < 1) return hipSuccess;
-    hipLaunchKernelGGL(stl_reduce_params, dim3(plan.n_params), dim3(1024), 0, s, part, B, plan.n_masks, plan, gp);
+    ReduceArgs A;
+    A.part = part;
+    A.gp = gp;
+    A.rows = B;
+    A.n_masks = plan.n_masks;
+    for (int m = 0; m < MAX_MASKS; ++m) A.mask_param[m] = plan.mask_param[m];
+    hipLaunchKernelGGL(stl_reduce_params, dim3(plan.n_params), dim3(1024), 0, s, A);
     return hipGetLastError();
 }
 

@@ -134,6 +134,7 @@ struct KArgs {
     const int* scan;       // [B] or NULL: the generic executor takes the trajectories whose flag is set
     int* saved_none;       // [B] or NULL: the generic executor marks its trajectories' saved traces unusable
     float* gp_zero;        // backward of a plan without masks: parameter gradients to clear, or NULL
+    float* gp_one;         // backward of one trajectory: parameter gradients from its partials, or NULL
     int nt;                // work-group size of the generic executor
     int tile;              // generic executor, slots in the workspace: positions of the smooth Until's LDS tile
     int part_stride;       // rows of mask_part per trajectory (1; a caller with more rows per
