@@ -2564,7 +2564,23 @@ __global__ void __launch_bounds__(MAX_NT) stl_exec_kernel(DevPlan plan, Batch bt
     // does once the kernel body grows past some size.)
     const DevPlan* P = (const DevPlan*)__builtin_amdgcn_kernarg_segment_ptr();
     (void)plan;
-    if (!ka.scan) plan_touch(P);         // (a fix-up launch usually finds no flag set)
+    // A fix-up launch usually finds no flag set: every wave reads this
+    // work-group's flags by itself and leaves without a barrier (no thread of
+    // the launch writes them).  Up to 256 rows of a work-group, whose loads are
+    // in flight together; beyond, next_item's reads of ka.nt rows at a time
+    // take fewer turns.
+    if (ka.scan) {
+        const int64_t nrow = bt.B > (int64_t)blockIdx.x ? (bt.B - 1 - (int64_t)blockIdx.x) / gridDim.x + 1 : 0;
+        if (nrow <= 256 && !(BWD && ka.gp_zero)) {
+            int f = 0;
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+                const int i = (int)(threadIdx.x & 63) + 64 * q;
+                if (i < nrow) f |= ka.scan[blockIdx.x + (int64_t)i * gridDim.x];
+            }
+            if (__ballot(f != 0) == 0) return;
+        }
+    } else plan_touch(P);
     float* arena = GLOBAL ? ka.garena + (size_t)blockIdx.x * ka.arena_floats : smem;
     const int nslots = BWD ? P->n_slots_bwd : P->n_slots_fwd;
     const int Lc = bt.Lcap;
