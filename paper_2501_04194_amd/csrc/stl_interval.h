@@ -310,6 +310,7 @@ __global__ void __launch_bounds__(IV_NT) stl_interval_split_kernel(IntervalArgs 
 constexpr int IVM_MAXT = 64;
 
 typedef float iv_f4 __attribute__((ext_vector_type(4)));
+typedef float iv_f4u __attribute__((ext_vector_type(4), aligned(4)));
 
 template <int KS, int NT, bool GRAD>
 __global__ void __launch_bounds__(IV_NT, 2) stl_interval_mfma_kernel(IntervalArgs A)
@@ -357,7 +358,6 @@ __global__ void __launch_bounds__(IV_NT, 2) stl_interval_mfma_kernel(IntervalArg
     }
     float* Uw = Ush[wv];
     const float ib = sg / A.beta;
-    const bool vec = A.N % 4 == 0 && (((uintptr_t)A.rho | (uintptr_t)A.ga | (uintptr_t)A.gb) & 15) == 0;
     for (int64_t b0 = (int64_t)blockIdx.y * 16; b0 < A.B; b0 += (int64_t)gridDim.y * 16) {
         const int64_t b = b0 + col;                   // this lane's trajectory
         const bool bok = b < A.B;
@@ -416,11 +416,12 @@ __global__ void __launch_bounds__(IV_NT, 2) stl_interval_mfma_kernel(IntervalArg
                 }
             }
             if (!bok) continue;
-            if (vec && n < A.N) {
-                *(iv_f4*)(A.rho + o) = s0[j];
+            if (n + 4 <= A.N) {
+                // (16-byte stores need the alignment of a float only: odd N, any buffers)
+                *(iv_f4u*)(A.rho + o) = s0[j];
                 if (GRAD) {
-                    *(iv_f4*)(A.ga + o) = sa[j];
-                    *(iv_f4*)(A.gb + o) = sb[j];
+                    *(iv_f4u*)(A.ga + o) = sa[j];
+                    *(iv_f4u*)(A.gb + o) = sb[j];
                 }
             } else {
                 for (int q = 0; q < 4; ++q)
@@ -457,9 +458,15 @@ __global__ void __launch_bounds__(IV_NT, 2) stl_interval_mfma_kernel(IntervalArg
 template <int KS, int NT>
 static void launch_interval_mfma(const IntervalArgs& A, hipStream_t s)
 {
-    // 64 NT intervals per work-group; enough trajectory-tile groups for about 8192 work-groups
+    // 64 NT intervals per work-group; enough trajectory-tile groups for about 8192
+    // work-groups, of the same number of tiles, and four tiles each while two work-groups
+    // per compute unit remain: the weights are evaluated once per work-group, which
+    // one or two tiles do not pay for (90,000 intervals x 250 signals, T = 20:
+    // 145 us with one tile each, 80 now)
     const int64_t nx = (A.N + 64 * NT - 1) / (64 * NT), tiles = (A.B + 15) / 16;
-    const int64_t ny = std::max<int64_t>(1, std::min<int64_t>(tiles, std::min<int64_t>(65535, (8192 + nx - 1) / nx)));
+    int64_t ny = std::max<int64_t>(1, std::min<int64_t>(tiles, std::min<int64_t>(65535, (8192 + nx - 1) / nx)));
+    const int64_t per = std::max<int64_t>((tiles + ny - 1) / ny, std::min<int64_t>(4, nx * tiles / 512));
+    ny = (tiles + per - 1) / per;
     const dim3 g((unsigned)nx, (unsigned)ny), blk(IV_NT);
     if (A.ga) hipLaunchKernelGGL((stl_interval_mfma_kernel<KS, NT, true>), g, blk, 0, s, A);
     else hipLaunchKernelGGL((stl_interval_mfma_kernel<KS, NT, false>), g, blk, 0, s, A);
@@ -748,7 +755,11 @@ hipError_t launch_interval_sweep(int op_sg, int smooth, float beta, float mc, fl
     if (smooth && T <= IVM_MAXT && B >= 16) {
         // batched smooth sweep: matrix cores
         // (interval tiles per wave: as many as 256 registers hold)
-        if (T <= 20) launch_interval_mfma<5, 4>(A, s);
+        // four tiles of intervals per wave once their weights serve about eight
+        // tiles of signals (T = 20, 90,000 intervals: 4,096 signals 1,150 us against 1,233
+        // with two; 1,000 signals 312 against 275)
+        if (T <= 20 && (N + 255) / 256 * ((B + 15) / 16) >= 65536) launch_interval_mfma<5, 4>(A, s);
+        else if (T <= 20) launch_interval_mfma<5, 2>(A, s);
         else if (T <= 32) launch_interval_mfma<8, 2>(A, s);
         else launch_interval_mfma<16, 2>(A, s);
         return hipGetLastError();
