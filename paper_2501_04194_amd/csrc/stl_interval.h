@@ -305,14 +305,20 @@ __global__ void __launch_bounds__(IV_NT) stl_interval_split_kernel(IntervalArgs 
 // beside it: one log, one reciprocal with a correction step and two
 // multiplications per output (through the library's general routines the
 // epilogue took as long as the writes), without branches.  4,096 signals x
-// 90,000 intervals of 20 samples: 1,259 -> 1,150 us with gradients (3.8 TB/s), 982
-// -> 448 us without.
+// 90,000 intervals of 20 samples without gradients: 982 -> 448 us.
+// SW: the operands the other way round (register q: trajectory b0 + 4(l/16) + q,
+// interval n0 + 16j + l%16): four 4-byte stores that cover 4 rows of 64 bytes
+// each, instead of one that covers 16.  With three outputs of 1.5 GB each the
+// rows in flight count for more than the stores.  With gradients, one set of
+// outputs written again and again: 1,137 us before, 1,131 with SW, 1,170
+// without; two sets in turn: 1,262, 1,197 and 1,160.  With two interval tiles
+// (below about 3,000 signals) SW loses 2 to 6%.
 constexpr int IVM_MAXT = 64;
 
 typedef float iv_f4 __attribute__((ext_vector_type(4)));
 typedef float iv_f4u __attribute__((ext_vector_type(4), aligned(4)));
 
-template <int KS, int NT, bool GRAD>
+template <int KS, int NT, bool GRAD, bool SW>
 __global__ void __launch_bounds__(IV_NT, 2) stl_interval_mfma_kernel(IntervalArgs A)
 {
     __shared__ float Ush[IV_NT / 64][16 * 4 * KS];     // per wave: 16 predicate traces
@@ -354,7 +360,7 @@ __global__ void __launch_bounds__(IV_NT, 2) stl_interval_mfma_kernel(IntervalArg
         // an interval whose support misses [0, T) has the empty-window value on
         // every trajectory: no sum and no fallback for it
         const unsigned long long m = __ballot(p != 0);
-        pos[j] = (int)((m | m >> 16 | m >> 32 | m >> 48) & 0xffff) >> (4 * row4);
+        pos[j] = (int)((m | m >> 16 | m >> 32 | m >> 48) & 0xffff) >> (SW ? col : 4 * row4);
     }
     float* Uw = Ush[wv];
     const float ib = sg / A.beta;
@@ -387,26 +393,28 @@ __global__ void __launch_bounds__(IV_NT, 2) stl_interval_mfma_kernel(IntervalArg
             const float e = (bok && k < T) ? exp2f(z[s] - (float)zm) : 0.f;
 #pragma unroll
             for (int j = 0; j < NT; ++j) {
-                s0[j] = __builtin_amdgcn_mfma_f32_16x16x4f32(W[j][s], e, s0[j], 0, 0, 0);
+                s0[j] = __builtin_amdgcn_mfma_f32_16x16x4f32(SW ? e : W[j][s], SW ? W[j][s] : e, s0[j], 0, 0, 0);
                 if (GRAD) {
-                    sa[j] = __builtin_amdgcn_mfma_f32_16x16x4f32(Wa[j][s], e, sa[j], 0, 0, 0);
-                    sb[j] = __builtin_amdgcn_mfma_f32_16x16x4f32(Wb[j][s], e, sb[j], 0, 0, 0);
+                    sa[j] = __builtin_amdgcn_mfma_f32_16x16x4f32(SW ? e : Wa[j][s], SW ? Wa[j][s] : e, sa[j], 0, 0, 0);
+                    sb[j] = __builtin_amdgcn_mfma_f32_16x16x4f32(SW ? e : Wb[j][s], SW ? Wb[j][s] : e, sb[j], 0, 0, 0);
                 }
             }
         }
         unsigned redo = 0;                 // outputs 4 j + q that need their own reference
-        const float fz = (float)zm;
+        float fz[4];
+#pragma unroll
+        for (int q = 0; q < 4; ++q) fz[q] = SW ? (float)__shfl(zm, 4 * row4 + q) : (float)zm;
 #pragma unroll
         for (int j = 0; j < NT; ++j) {
-            const int64_t n = n0 + 16 * j + 4 * row4, o = b * A.N + n;
+            const int64_t n = n0 + 16 * j + (SW ? col : 4 * row4), o = (SW ? b0 + 4 * row4 : b) * A.N + n;
 #pragma unroll
             for (int q = 0; q < 4; ++q) {
                 // (branch-free: a wave holds outputs with and without a support)
                 const float S = s0[j][q];
                 const bool ok = S >= 0x1p-100f;
-                redo |= !ok && (pos[j] >> q & 1) ? 1u << (4 * j + q) : 0u;
+                redo |= !ok && (pos[j] >> (SW ? 0 : q) & 1) ? 1u << (4 * j + q) : 0u;
                 // quotients as estimate and one correction step: S, bl and the results are normal
-                const float v = fz + lg2(S), r = v * ibl;
+                const float v = fz[q] + lg2(S), r = v * ibl;
                 s0[j][q] = ok ? fmaf(fmaf(-r, sbl, v), ibl, r) : empty;
                 if (GRAD) {
                     float iS = __builtin_amdgcn_rcpf(S);
@@ -414,6 +422,20 @@ __global__ void __launch_bounds__(IV_NT, 2) stl_interval_mfma_kernel(IntervalArg
                     sa[j][q] = ok ? sa[j][q] * iS : 0.f;
                     sb[j][q] = ok ? sb[j][q] * iS : 0.f;
                 }
+            }
+            if (SW) {
+                if (n < A.N) {
+#pragma unroll
+                    for (int q = 0; q < 4; ++q)
+                        if (b0 + 4 * row4 + q < A.B) {
+                            A.rho[o + q * A.N] = s0[j][q];
+                            if (GRAD) {
+                                A.ga[o + q * A.N] = sa[j][q];
+                                A.gb[o + q * A.N] = sb[j][q];
+                            }
+                        }
+                }
+                continue;
             }
             if (!bok) continue;
             if (n + 4 <= A.N) {
@@ -434,28 +456,29 @@ __global__ void __launch_bounds__(IV_NT, 2) stl_interval_mfma_kernel(IntervalArg
                     }
             }
         }
-        if (!bok) redo = 0;
+        if (!SW && !bok) redo = 0;
 #pragma unroll 1
         while (redo) {
             const int i = __builtin_ctz(redo);
             redo &= redo - 1;
-            const int64_t n = n0 + 16 * (i >> 2) + 4 * row4 + (i & 3);
-            if (n >= A.N) continue;
+            const int64_t n = n0 + 16 * (i >> 2) + (SW ? col : 4 * row4 + (i & 3));
+            const int bi = SW ? 4 * row4 + (i & 3) : col;
+            if (n >= A.N || b0 + bi >= A.B) continue;
             const MaskP mp = params(n);
             int lo, hi;
             iv_range(mp.a, mp.b, mp.c, mp.eps, T, lo, hi);
             float rho = -sg * A.rho_pad, ga = 0.f, gb = 0.f;
-            iv_own_ref(mp, Uw + col * (4 * KS), lo, hi, sg, bl, A.beta, rho, ga, gb);
-            A.rho[b * A.N + n] = rho;
+            iv_own_ref(mp, Uw + bi * (4 * KS), lo, hi, sg, bl, A.beta, rho, ga, gb);
+            A.rho[(b0 + bi) * A.N + n] = rho;
             if (GRAD) {
-                A.ga[b * A.N + n] = ga;
-                A.gb[b * A.N + n] = gb;
+                A.ga[(b0 + bi) * A.N + n] = ga;
+                A.gb[(b0 + bi) * A.N + n] = gb;
             }
         }
     }
 }
 
-template <int KS, int NT>
+template <int KS, int NT, bool SW = false>
 static void launch_interval_mfma(const IntervalArgs& A, hipStream_t s)
 {
     // 64 NT intervals per work-group; enough trajectory-tile groups for about 8192
@@ -468,8 +491,8 @@ static void launch_interval_mfma(const IntervalArgs& A, hipStream_t s)
     const int64_t per = std::max<int64_t>((tiles + ny - 1) / ny, std::min<int64_t>(4, nx * tiles / 512));
     ny = (tiles + per - 1) / per;
     const dim3 g((unsigned)nx, (unsigned)ny), blk(IV_NT);
-    if (A.ga) hipLaunchKernelGGL((stl_interval_mfma_kernel<KS, NT, true>), g, blk, 0, s, A);
-    else hipLaunchKernelGGL((stl_interval_mfma_kernel<KS, NT, false>), g, blk, 0, s, A);
+    if (A.ga) hipLaunchKernelGGL((stl_interval_mfma_kernel<KS, NT, true, SW>), g, blk, 0, s, A);
+    else hipLaunchKernelGGL((stl_interval_mfma_kernel<KS, NT, false, false>), g, blk, 0, s, A);
 }
 
 // ------------------------------------------------------------------ pSTL descent
@@ -755,10 +778,10 @@ hipError_t launch_interval_sweep(int op_sg, int smooth, float beta, float mc, fl
     if (smooth && T <= IVM_MAXT && B >= 16) {
         // batched smooth sweep: matrix cores
         // (interval tiles per wave: as many as 256 registers hold)
-        // four tiles of intervals per wave once their weights serve about eight
-        // tiles of signals (T = 20, 90,000 intervals: 4,096 signals 1,150 us against 1,233
-        // with two; 1,000 signals 312 against 275)
-        if (T <= 20 && (N + 255) / 256 * ((B + 15) / 16) >= 65536) launch_interval_mfma<5, 4>(A, s);
+        // four tiles of intervals per wave, and with gradients SW, once their
+        // weights serve about eight tiles of signals (T = 20, 90,000 intervals: 4,096
+        // signals 1,150 us against 1,233 with two; 1,000 signals 312 against 275)
+        if (T <= 20 && (N + 255) / 256 * ((B + 15) / 16) >= 65536) launch_interval_mfma<5, 4, true>(A, s);
         else if (T <= 20) launch_interval_mfma<5, 2>(A, s);
         else if (T <= 32) launch_interval_mfma<8, 2>(A, s);
         else launch_interval_mfma<16, 2>(A, s);
