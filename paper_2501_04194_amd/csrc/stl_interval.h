@@ -560,6 +560,23 @@ DEV T lps_reduce(T v, int lps, Op op)
     return v;
 }
 
+struct OpMax {
+    __device__ __forceinline__ float operator()(float a, float b) const { return fmaxf(a, b); }
+};
+
+// A step takes a signal's terms in FP32 where none of them can leave the normal
+// range: beta log2(e) times the trace's extent (and 2^-22 of its magnitude, so
+// that every exponent is below 1e9) is at most PD_SPAN.  A wave with any other
+// signal, non-finite samples included, takes FP64 terms with an exponent split.
+constexpr float PD_SPAN = 120.f;
+
+DEV void spread(float u, float& lo, float& hi, float& far)
+{
+    lo = fminf(lo, u);
+    hi = fmaxf(hi, u);
+    far = fmaxf(far, fabsf(u) < INFINITY ? fabsf(u) * 0x1p-22f : INFINITY);
+}
+
 template <int NR, bool REG>
 __global__ void __launch_bounds__(PD_NT) stl_pstl_descent_kernel(DescentArgs A, int lps)
 {
@@ -579,13 +596,19 @@ __global__ void __launch_bounds__(PD_NT) stl_pstl_descent_kernel(DescentArgs A, 
         for (int d = 0; d < D; ++d) u = fmaf(A.w[d], x[d], u);
         return u - A.c;
     };
-    float ur[NR];
+    float ur[NR], far = 0.f;
 #pragma unroll
     for (int k = 0; k < NR; ++k) ur[k] = 0.f;
     if (REG) {
+        float lo = INFINITY, hi = -INFINITY;
 #pragma unroll
         for (int k = 0; k < NR; ++k)
-            if (sig0 < B && r + lps * k < T) ur[k] = sg * trace(sig0, r + lps * k);
+            if (sig0 < B && r + lps * k < T) {
+                ur[k] = sg * trace(sig0, r + lps * k);
+                spread(ur[k], lo, hi, far);
+            }
+        far = lps_reduce(far, lps, OpMax());
+        far = fmaxf(far, lps_reduce(hi, lps, OpMax()) + lps_reduce(-lo, lps, OpMax()));
     } else {
         for (int i = threadIdx.x; i < B * T; i += PD_NT) U[i] = sg * trace(i / T, i % T);
     }
@@ -596,6 +619,12 @@ __global__ void __launch_bounds__(PD_NT) stl_pstl_descent_kernel(DescentArgs A, 
     };
     if (wv == PD_NT / 64 - 1) schedule(0);
     __syncthreads();
+    if (!REG)
+        for (int i = sig0; i < B; i += nsig) {             // (the farthest of this thread's signals)
+            float lo = INFINITY, hi = -INFINITY;
+            for (int j = 0; j < T; ++j) spread(U[i * T + j], lo, hi, far);
+            far = fmaxf(far, hi - lo);
+        }
     for (int k = 0; k < A.steps; ++k) {
         float af = 0.f, bf = 0.f;
         if (wv == 0) {
@@ -622,53 +651,61 @@ __global__ void __launch_bounds__(PD_NT) stl_pstl_descent_kernel(DescentArgs A, 
         const float beta = cb[k & 1][1], bl = beta * LOG2E;
         if (wv == PD_NT / 64 - 1) schedule(k + 1);     // (a wave with few signals)
         double ha = 0.0, hb = 0.0, hl = 0.0;      // this thread's hinge sums
-        for (int i = sig0; i < B; i += nsig) {
-            float u[NR], zm = -INFINITY;
+        auto signals = [&](auto wide) {
+            constexpr bool WIDE = decltype(wide)::value;
+            for (int i = sig0; i < B; i += nsig) {
+                float u[NR], zm = -INFINITY;
 #pragma unroll
-            for (int q = 0; q < NR; ++q) {
-                u[q] = REG ? ur[q] : (q < T ? U[i * T + q] : 0.f);
-                zm = fmaxf(zm, fmaf(bl, u[q], Wm[q][r]));
-            }
-            zm = lps_reduce(zm, lps, [](float a, float b) { return fmaxf(a, b); });
-            bool any = zm > -INFINITY;
-            if (!any) {                          // no support, or only terms of exponent -inf in it
-                float wm = -INFINITY;
-                for (int q = 0; q < NR; ++q) wm = fmaxf(wm, Wm[q][r]);
-                wm = lps_reduce(wm, lps, [](float a, float b) { return fmaxf(a, b); });
-                any = wm == 0.f;
-            }
-            // reference: the largest exponent of the support; terms are 2^{z - R} (their exponents
-            // outside the support do not matter, their weights are 0)
-            const float R = ceilf(fminf(fmaxf(zm, -1e9f), 1e9f));
-            float e[NR];
-            double S = 0.0;
-#pragma unroll
-            for (int q = 0; q < NR; ++q) {
-                e[q] = ex2(fminf(fmaf(bl, u[q], -R), 0.f));
-                S = fma(Wt[0][q][r], (double)e[q], S);
-            }
-            S = lps_reduce(S, lps, OpD());
-            const float rho = any ? sg * (R + log2d(S)) / bl : -sg * 1e6f;
-            const bool hinge = rho < 0.f;
-            if (__ballot(hinge) == 0) continue;  // the gradients are those of the violated signals only
-            double Sa = 0.0, Sb = 0.0;
-#pragma unroll
-            for (int q = 0; q < NR; ++q) {
-                Sa = fma(Wt[1][q][r], (double)e[q], Sa);
-                Sb = fma(Wt[2][q][r], (double)e[q], Sb);
-            }
-            Sa = lps_reduce(Sa, lps, OpD());
-            Sb = lps_reduce(Sb, lps, OpD());
-            if (hinge && r == 0) {
-                if (any) {
-                    double iS = __builtin_amdgcn_rcp(S);         // 1 / S to fp64 rounding: estimate and one step
-                    iS = fma(fma(-S, iS, 1.0), iS, iS) * (double)(sg / beta);
-                    ha -= (float)(iS * Sa);
-                    hb -= (float)(iS * Sb);
+                for (int q = 0; q < NR; ++q) {
+                    u[q] = REG ? ur[q] : (q < T ? U[i * T + q] : 0.f);
+                    if (!WIDE) zm = fmaxf(zm, fmaf(bl, u[q], Wm[q][r]));
+                    else if (Wm[q][r] == 0.f) zm = fmaxf(zm, fminf(fmaxf(bl * u[q], -1e9f), 1e9f));
                 }
-                hl -= rho;
+                zm = lps_reduce(zm, lps, OpMax());
+                const bool any = zm > -INFINITY;
+                // reference: the largest exponent of the support; terms are 2^{z - R} (FP32: their exponents
+                // outside the support do not matter, their weights are 0)
+                const float R = ceilf(fmaxf(zm, -1e9f));
+                float e[NR];
+                double S = 0.0, Sa = 0.0, Sb = 0.0;
+#pragma unroll
+                for (int q = 0; q < NR; ++q) {
+                    if (!WIDE) {
+                        e[q] = ex2(fminf(fmaf(bl, u[q], -R), 0.f));
+                        S = fma(Wt[0][q][r], (double)e[q], S);
+                    } else if (Wm[q][r] == 0.f) {
+                        const double t = exp2d_neg(bl * u[q] - R);
+                        S = fma(Wt[0][q][r], t, S);
+                        Sa = fma(Wt[1][q][r], t, Sa);
+                        Sb = fma(Wt[2][q][r], t, Sb);
+                    }
+                }
+                S = lps_reduce(S, lps, OpD());
+                const float rho = any ? sg * (R + log2d(S)) / bl : -sg * 1e6f;
+                const bool hinge = rho < 0.f;
+                if (__ballot(hinge) == 0) continue;  // the gradients are those of the violated signals only
+                if (!WIDE) {
+#pragma unroll
+                    for (int q = 0; q < NR; ++q) {
+                        Sa = fma(Wt[1][q][r], (double)e[q], Sa);
+                        Sb = fma(Wt[2][q][r], (double)e[q], Sb);
+                    }
+                }
+                Sa = lps_reduce(Sa, lps, OpD());
+                Sb = lps_reduce(Sb, lps, OpD());
+                if (hinge && r == 0) {
+                    if (any) {
+                        double iS = __builtin_amdgcn_rcp(S);         // 1 / S to fp64 rounding: estimate and one step
+                        iS = fma(fma(-S, iS, 1.0), iS, iS) * (double)(sg / beta);
+                        ha -= (float)(iS * Sa);
+                        hb -= (float)(iS * Sb);
+                    }
+                    hl -= rho;
+                }
             }
-        }
+        };
+        if (__ballot(!(bl * far <= PD_SPAN)) == 0) signals(std::false_type());
+        else signals(std::true_type());
         if (__ballot(hl != 0.0) != 0) {
             ha = wave_add63(ha);
             hb = wave_add63(hb);
