@@ -695,8 +695,7 @@ __global__ void __launch_bounds__(PD_NT) stl_pstl_descent_kernel(DescentArgs A, 
                 Sb = lps_reduce(Sb, lps, OpD());
                 if (hinge && r == 0) {
                     if (any) {
-                        double iS = __builtin_amdgcn_rcp(S);         // 1 / S to fp64 rounding: estimate and one step
-                        iS = fma(fma(-S, iS, 1.0), iS, iS) * (double)(sg / beta);
+                        const double iS = (double)(sg / beta) / S;   // one division for both ratios
                         ha -= (float)(iS * Sa);
                         hb -= (float)(iS * Sb);
                     }
