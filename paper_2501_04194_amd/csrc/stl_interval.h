@@ -10,6 +10,7 @@
 // E_j = 2^{z_j - R} (FP64, R the trajectory's largest exponent, as in the
 // fused kernels) sit in LDS.
 #pragma once
+#include <float.h>
 
 namespace stlmi {
 
@@ -413,8 +414,9 @@ __global__ void __launch_bounds__(IV_NT, 2) stl_interval_mfma_kernel(IntervalArg
                 const float S = s0[j][q];
                 const bool ok = S >= 0x1p-100f;
                 redo |= !ok && (pos[j] >> (SW ? 0 : q) & 1) ? 1u << (4 * j + q) : 0u;
-                // quotients as estimate and one correction step: S, bl and the results are normal
-                const float v = fz[q] + lg2(S), r = v * ibl;
+                // quotients as estimate and one correction step: S and bl are normal; the estimate is kept
+                // finite, since S is infinite where a sample is and inf - inf would be the correction
+                const float v = fz[q] + lg2(S), r = __builtin_amdgcn_fmed3f(v * ibl, -FLT_MAX, FLT_MAX);
                 s0[j][q] = ok ? fmaf(fmaf(-r, sbl, v), ibl, r) : empty;
                 if (GRAD) {
                     float iS = __builtin_amdgcn_rcpf(S);
