@@ -1404,11 +1404,14 @@ DEV void until_smooth_adj(const Env& e, int a, int b, const float* w, const floa
 
 // Smooth Until in fp64 against one reference exponent per trajectory.  The
 // leaf terms 2^u, u = -beta log2(e) (phi or psi), are kept as the doubles
-// 2^{u - M} with M = ceil(max u) over both inputs: every term is <= 1, so the
-// running sums, their reciprocals and the outer sums stay inside the fp64
-// range while the exponent range max u - min u is below UF_RANGE.  Beyond it
-// (or with a non-finite value) the scaled-pair routines above take over.
-constexpr int UF_RANGE = 1000;
+// 2^{u - M}, M = ceil(max u) - UF_TOP over both inputs.  While the exponent
+// range max u - min u is at most UF_RANGE, they lie in [2^-600, 2^400], a sum of
+// 2^25 of them below 2^425, the reciprocals and their sums in 2^-425 .. 2^624,
+// and the adjoint's sums over outputs, at most 2^24 |G| / D with |G| < 2^128,
+// below 2^752: nothing leaves the fp64 range.  (With M = ceil(max u) a sum
+// over the outputs that share a position reached 2^1024 at |G| = 2^24.)  Beyond
+// UF_RANGE (or with a non-finite value) the scaled-pair routines above take over.
+constexpr int UF_RANGE = 1000, UF_TOP = 400;
 
 // 2^{u - M} with exact exponent bookkeeping (u - ceil(u) is exact)
 DEV double uterm(float u, int M)
@@ -1461,8 +1464,8 @@ DEV bool until_ref(const float* phi, const float* psi, int L, float bl, const En
     atomicMin(&sh.ints[3], lo);
     if (bad) atomicOr(&sh.ints[4], 1);
     __syncthreads();
-    M = sh.ints[2];
-    const bool ok = sh.ints[4] == 0 && (long long)M - (long long)sh.ints[3] <= UF_RANGE;
+    M = sh.ints[2] - UF_TOP;
+    const bool ok = sh.ints[4] == 0 && (long long)sh.ints[2] - (long long)sh.ints[3] <= UF_RANGE;
     __syncthreads();
     return ok;
 }
