@@ -98,6 +98,7 @@ struct Geom {
     int persistent;
     int Lc;
     bool global;
+    bool lean;              // forward with each predicate in its place (plan->dev_lean)
     size_t arena_floats;
     size_t lds_bytes;
     int tile;               // positions of the smooth Until's LDS tile (slots in the workspace)
@@ -148,11 +149,18 @@ stl_status geometry(const stl_plan* plan, const stl_batch* bt, const stl_launch*
     if (nt != 64 && nt != 128 && nt != 256 && nt != 512) return fail(STL_E_ARG, "threads must be 64, 128, 256 or 512");
     if (bt->T < 1 || bt->T > (1 << 24)) return fail(STL_E_SHAPE, "T must be in [1, 2^24]");
     int Lc = (int)((bt->T + 3) / 4 * 4);
-    const int nslots = bwd ? dp.n_slots_bwd : dp.n_slots_fwd;
     const int ub = plan->until_b >= 0 ? (int)std::min<int64_t>(plan->until_b, bt->T) : -1;
     auto scratch = [&](int threads) {
         return scratch_floats(Lc, threads, plan->scr_units[bwd], bwd ? ub : -1, plan->until_masked);
     };
+    // All predicates at once where their traces fit on chip (twice as fast: one
+    // pass over x); else, for plans of many, the order that needs fewer slots: 32
+    // predicates under And / Or take 9 instead of 33, so that 1,300 samples stay
+    // on chip and the workspace stays small.
+    g->lean = !bwd && !trace && plan->has_lean &&
+              ((cfg && cfg->global_slots) ||
+               ((size_t)dp.n_slots_fwd * Lc + scratch(nt)) * sizeof(float) > di.lds_max);
+    const int nslots = bwd ? dp.n_slots_bwd : g->lean ? plan->dev_lean.n_slots_fwd : dp.n_slots_fwd;
     // (a tile whose checkpoints do not fit beside it is not used)
     auto until_tile = [&](int threads) {
         const int t = until_tile_len(threads, ub, plan->until_masked);
@@ -358,7 +366,7 @@ static stl_status run(const stl_plan* plan, const stl_batch* bt, const float* pa
     if (!ws || ws_bytes < g.ws_bytes)
         return fail(STL_E_WORKSPACE, "workspace too small: need %zu bytes, got %zu", g.ws_bytes, ws_bytes);
     hipStream_t st = (hipStream_t)stream;
-    const DevPlan& dp = trace ? plan->dev_trace : plan->dev;
+    const DevPlan& dp = trace ? plan->dev_trace : g.lean ? plan->dev_lean : plan->dev;
     if (bt->B == 0) {
         if (bwd && gparams) {
             if (launch_reduce_params(nullptr, 0, dp, gparams, st) != hipSuccess)

@@ -340,6 +340,12 @@ extern "C" stl_status stl_compile(const stl_node* nodes, int32_t n_nodes, const 
         return fail(STL_E_UNSUPPORTED, "predicate and pad coefficients need %d floats (max %d)", (int)B.coef.size(),
                     MAX_COEF);
 
+    // the formula's own order, for the forward in as few slots as possible: a
+    // predicate's slot is free again once its parent has read it
+    const std::vector<Instr> own_ins = B.ins;
+    const std::vector<std::vector<int>> own_kids = B.kids;
+    const int own_root = rootk;
+
     // the predicates first (in their order), then the other instructions
     {
         std::vector<int> at(n);
@@ -357,9 +363,13 @@ extern "C" stl_status stl_compile(const stl_node* nodes, int32_t n_nodes, const 
     }
 
     // consumers
-    std::vector<int> parent(n, -1);
-    for (int k = 0; k < n; ++k)
-        for (int c : B.kids[k]) parent[c] = k;
+    auto parents_of = [n](const std::vector<std::vector<int>>& kids) {
+        std::vector<int> par(n, -1);
+        for (int k = 0; k < n; ++k)
+            for (int c : kids[k]) par[c] = k;
+        return par;
+    };
+    const std::vector<int> parent = parents_of(B.kids);
 
     // forward slot map: value of k lives from k to its parent's step
     SlotAlloc fa;
@@ -481,14 +491,42 @@ extern "C" stl_status stl_compile(const stl_node* nodes, int32_t n_nodes, const 
         for (int j = 0; j < MAX_NCH; ++j) I.f_ch[j] = I.b_ch[j];
     }
     pred_refs(tp);
+    p->scr_units[0] = p->scr_units[1] = 0;
+    for (const Instr& I : B.ins)
+        for (int bwd = 0; bwd < 2; ++bwd) p->scr_units[bwd] = std::max(p->scr_units[bwd], scratch_units(I, bwd != 0));
+    // lean variant, for plans whose predicates' slots outweigh what the
+    // operators leave of the 16 scratch units (that many floats per timestep
+    // and the lean slots are what a forward may take of LDS and workspace);
+    // the fused shapes have at most four predicates
+    if (dp.fused.n == 0) {
+        const std::vector<int> par = parents_of(own_kids);
+        SlotAlloc la;
+        std::vector<int> slot(n);
+        for (int k = 0; k < n; ++k) slot[k] = la.get(k, par[k] < 0 ? n : par[k]);
+        p->has_lean = dp.n_slots_fwd + p->scr_units[0] > (int)la.free_at.size() + 16;
+        DevPlan& lp = p->dev_lean;
+        lp = dp;
+        lp.n_pred = 0;
+        lp.root = own_root;
+        lp.n_slots_fwd = (int)la.free_at.size();
+        for (int k = 0; k < n; ++k) {
+            Instr& I = lp.ins[k];
+            I = own_ins[k];
+            const auto& ch = own_kids[k];
+            I.f_out = (int8_t)slot[k];
+            if (I.kind == K_NARY) {
+                for (int j = 0; j < (int)ch.size(); ++j) I.f_ch[j] = (int8_t)slot[ch[j]];
+            } else {
+                if (ch.size() > 0) I.f_in0 = (int8_t)slot[ch[0]];
+                if (ch.size() > 1) I.f_in1 = (int8_t)slot[ch[1]];
+            }
+        }
+    }
     p->n_nodes = n_nodes;
     p->n_params = n_params;
     p->D = D;
     p->until_b = B.until_b;
     p->until_masked = B.until_masked;
-    p->scr_units[0] = p->scr_units[1] = 0;
-    for (const Instr& I : B.ins)
-        for (int bwd = 0; bwd < 2; ++bwd) p->scr_units[bwd] = std::max(p->scr_units[bwd], scratch_units(I, bwd != 0));
     *out = p;
     return STL_OK;
 }

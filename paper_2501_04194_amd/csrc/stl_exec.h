@@ -541,6 +541,36 @@ DEV void op_preds(const Env& e, bool bwdmap)
     }
 }
 
+// one predicate where the formula names it (plans whose predicates are not
+// evaluated together: their traces would take more slots than they may)
+template <int D>
+DEV void pred_one(const Env& e, const Instr& I, float* out)
+{
+    const float* cf = e.P->coef + I.coef;
+    const bool vec = vec_rows<D>(e.x);
+    for (int t0 = e.tid; t0 < e.L; t0 += PRED_TB * e.nt) {
+        float x[PRED_TB][D];
+#pragma unroll
+        for (int j = 0; j < PRED_TB; ++j)
+            if (t0 + j * e.nt < e.L) load_row<D>(e.x + (size_t)(t0 + j * e.nt) * D, vec, x[j]);
+#pragma unroll
+        for (int j = 0; j < PRED_TB; ++j)
+            if (t0 + j * e.nt < e.L) out[t0 + j * e.nt] = pred_value(I.kind, cf, D, x[j]);
+    }
+}
+
+DEV void op_pred(const Env& e, const Instr& I, float* out)
+{
+    switch (e.D) {
+    case 1: pred_one<1>(e, I, out); return;
+    case 2: pred_one<2>(e, I, out); return;
+    case 3: pred_one<3>(e, I, out); return;
+    case 4: pred_one<4>(e, I, out); return;
+    }
+    const float* cf = e.P->coef + I.coef;
+    for (int t = e.tid; t < e.L; t += e.nt) out[t] = pred_value(I.kind, cf, e.D, e.x + (size_t)t * e.D);
+}
+
 // d/dx of the predicates: dx[t, d] = sum_p dmu_p/dx_d * g_p[t]; one predicate's part
 template <class Row, class Acc>
 DEV void pred_dx(int kind, const float* cf, int D, float g, Row x, Acc& acc)
@@ -2034,8 +2064,9 @@ DEV void exec_fwd(const Env& e, const Instr& I, bool bwdmap)
         for (int t = e.tid; t < L; t += e.nt) out[t] = e.P->rho_max;
         break;
     case K_LIN:
-    case K_NORM:
-        break;          // op_preds, before the first instruction
+    case K_NORM:        // (evaluated by op_preds, before the first instruction, unless the plan has n_pred = 0)
+        if (!bwdmap) op_pred(e, I, out);
+        break;
     case K_NOT: {
         const float* u = slot(e, i0);
         for (int t = e.tid; t < L; t += e.nt) out[t] = -u[t];

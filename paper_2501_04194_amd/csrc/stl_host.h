@@ -11,6 +11,8 @@
 struct stl_plan {
     stlmi::DevPlan dev;          // liveness-optimised forward slot map
     stlmi::DevPlan dev_trace;    // forward map with one slot per instruction (node trace output)
+    stlmi::DevPlan dev_lean;     // forward with each predicate where the formula names it, in fewer slots
+    bool has_lean = false;       // dev_lean is there, and to be used where dev does not fit on chip
     int32_t n_nodes = 0;  // caller's nodes
     int32_t n_params = 0;
     int32_t D = 0;

@@ -84,7 +84,8 @@ struct DevPlan {
     int32_t D;
     int32_t n_masks;
     int32_t n_params;
-    int32_t n_pred;                         // predicates are instructions 0 .. n_pred-1
+    int32_t n_pred;                         // predicates evaluated together: instructions 0 .. n_pred-1 (all of
+                                            // them, or none: each is then evaluated in its place)
     int32_t root;                           // instruction index of the root
     float rho_max;
     float rho_pad;

@@ -1,0 +1,54 @@
+"""Formulas of many predicates through stl_forward_static, whose workspace is
+fixed: where all their traces at once would not fit on chip, a predicate's trace
+takes a slot only until its parent has read it."""
+import ctypes
+
+import numpy as np
+import pytest
+import torch
+
+from paper_2501_04194_amd import stl
+
+E_WORKSPACE = -5
+
+
+def tree(n, smooth=False):
+    s = {"smooth": True, "beta": 8.0} if smooth else {}
+    level = [{"op": "linear", "w": [np.cos(k), np.sin(k)], "c": 0.1 * k / n} for k in range(n)]
+    op = "and"
+    while len(level) > 1:
+        level = [dict(op=op, children=level[i:i + 4], **s) for i in range(0, len(level), 4)]
+        op = "or" if op == "and" else "and"
+    return level[0]
+
+
+# (formula, B, T, slots in the workspace): 25 floats a timestep and trajectory fit, 33 do not
+CASES = [(tree(32), 60, 2700, 0), (tree(32, True), 60, 2700, 0), (tree(32), 1000, 160, 1)]
+
+
+@pytest.mark.parametrize("case", range(len(CASES)))
+def test_accepted(case):
+    """The workspace is checked before the missing output: with it too small the status would say so."""
+    spec, B, T, slots = CASES[case]
+    plan = stl.Plan(spec, 2)
+    bt = stl.Batch()
+    bt.x, bt.B, bt.T, bt.D = 256, B, T, 2            # (never read: no output, so nothing is launched)
+    pv = ctypes.c_void_p(256)
+    launch = stl.Launch(0, 0, slots, 0)
+    st = stl.lib().stl_forward_static(plan.handle, ctypes.byref(bt), pv, None, None, ctypes.byref(launch), None)
+    msg = stl.lib().stl_last_error().decode()
+    assert st < 0 and "workspace" not in msg, (st, msg)
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("n,smooth,B,T", [(32, False, 300, 1300), (32, True, 300, 1300), (32, False, 60, 2700),
+                                          (20, True, 17, 2500), (32, True, 3, 6001)])
+def test_values(n, smooth, B, T):
+    from gpu_util import check_formula
+    spec = tree(n, smooth)
+    x = np.cumsum(0.05 * np.random.default_rng(T).normal(size=(B, T, 2)), axis=1).astype(np.float32)
+    g = check_formula(spec, x, grads=B <= 17, what="%d predicates T=%d" % (n, T))
+    xd = torch.from_numpy(x).cuda()
+    ref, nodes = g.plan.forward(xd, g.pv, node_traces=True)
+    assert torch.equal(ref, g.plan.forward(xd, g.pv))
+    assert torch.equal(ref, g.plan.forward_static(xd, g.pv))
