@@ -25,6 +25,7 @@ size_t until_lds_bytes(int nt, int until_b, bool bwd, int tile, int Lc);
 hipError_t launch_exec(bool bwd, const DevPlan& plan, const struct Batch& bt, const struct KArgs& ka, int grid,
                        int nt, size_t lds_bytes, hipStream_t s);
 hipError_t set_max_lds(size_t bytes);
+bool plan_is_plain(const DevPlan& plan);
 hipError_t launch_zero_counter(int* c, hipStream_t s);
 hipError_t launch_fill_int(int* p, int64_t n, int v, hipStream_t s);
 hipError_t launch_reduce_params(const float* part, int64_t B, const DevPlan& plan, float* gp, hipStream_t s);
@@ -132,6 +133,12 @@ static bool mx_applies(const DevPlan& dp, const stl_batch* bt, const stl_launch*
     return true;
 }
 
+// The fp64 fused kernels: dense batches of the fused shape they are long enough for.
+static bool fused_applies(const DevPlan& dp, const stl_batch* bt, const stl_launch* cfg, bool trace)
+{
+    return dp.fused.n > 0 && !trace && bt->offsets == nullptr && bt->T <= fused_max_T() && !(cfg && (cfg->flags & 1));
+}
+
 stl_status geometry(const stl_plan* plan, const stl_batch* bt, const stl_launch* cfg, bool bwd, bool trace,
                     Geom* g)
 {
@@ -141,9 +148,9 @@ stl_status geometry(const stl_plan* plan, const stl_batch* bt, const stl_launch*
     // trajectories to fill the chip: 128 up to 128 samples (1,000 reach-avoid
     // trajectories of 100 samples, forward / backward: 12.3 / 22.4 us against 14.1 /
     // 26.3 with 256), 256 beyond (200 samples: 15.2 / 29.4 against 16.6 / 34.1), and
-    // 512 from 768 samples on for plans without a smooth Until, whose scans then
-    // have one tile per wave (1,000 samples: 36.5 / 84.1 against 42.7 / 104.6; the
-    // smooth Until's lanes want the registers: 88 / 350 against 70 / 249).
+    // 512 from 768 samples on where as many of them are resident (below), for plans
+    // without a smooth Until, whose lanes want the registers (1,000 samples: 88 / 350
+    // with 512 against 70 / 249).
     const int want0 = bt->T <= 128 ? 128 : bt->T < 768 || plan->until_b >= 0 || bt->offsets ? 256 : 512;
     int nt = cfg && cfg->threads ? cfg->threads : want0;
     if (nt != 64 && nt != 128 && nt != 256 && nt != 512) return fail(STL_E_ARG, "threads must be 64, 128, 256 or 512");
@@ -169,9 +176,25 @@ stl_status geometry(const stl_plan* plan, const stl_batch* bt, const stl_launch*
     auto until_lds = [&](int threads, bool glob) {
         return until_lds_bytes(threads, ub, bwd, glob ? until_tile(threads) : 0, Lc);
     };
-    if (!(cfg && cfg->threads) && nt == 512 &&
-        ((size_t)nslots * Lc + scratch(nt)) * sizeof(float) + until_lds(nt, false) > di.lds_max)
-        nt = 256;
+    if (!(cfg && cfg->threads) && nt == 512) {
+        // 512 threads unless a compute unit, by its LDS and the kernels' registers, then holds
+        // so many fewer work-groups that its share of the trajectories takes more turns (a
+        // fix-up launch has at most one work-group per unit): 1,000 trajectories of 1,600
+        // samples, a hard Always and Eventually, backward, two resident of either size, 198 ->
+        // 139 us; 500 of 1,024 under a smooth mask, one of either, 226 -> 156; but 500 of 900,
+        // two of 256 or one of 512, 124 -> 155, and 1,000 of 900, two unbounded windows,
+        // forward, four of 256 or three of 512, 13.9 -> 19.4.
+        const int regs = plan_is_plain(dp) ? (bwd ? 16 : 24) : (bwd ? 8 : 16);      // waves the registers hold
+        const bool fixup = mx_applies(dp, bt, cfg, trace) || fused_applies(dp, bt, cfg, trace);
+        const int64_t share = fixup ? 1 : (bt->B + di.cus - 1) / di.cus;
+        auto turns = [&](int threads) {
+            const size_t a = (size_t)nslots * Lc + scratch(threads);
+            const size_t wg = (a * sizeof(float) + until_lds(threads, false) + 240 + 1279) / 1280 * 1280;
+            const int64_t fit = std::min<int64_t>((di.lds_max + 2048) / wg, regs / (threads / 64));
+            return fit > 0 ? (share + fit - 1) / fit : INT64_MAX;
+        };
+        if (turns(512) == INT64_MAX || turns(512) > turns(256)) nt = 256;
+    }
     size_t arena = (size_t)nslots * Lc + scratch(nt);
     size_t lds = arena * sizeof(float) + until_lds(nt, false);
     bool global = (cfg && cfg->global_slots) || lds > di.lds_max;
@@ -258,8 +281,7 @@ stl_status geometry(const stl_plan* plan, const stl_batch* bt, const stl_launch*
         }
         g->off_arena = off;
     }
-    const bool want_fused = !g->mx && dp.fused.n > 0 && !trace && bt->offsets == nullptr &&
-                            bt->T <= fused_max_T() && !(cfg && (cfg->flags & 1));
+    const bool want_fused = !g->mx && fused_applies(dp, bt, cfg, trace);
     if (want_fused) {
         const size_t fl = fused_lds((int)((bt->T + 3) / 4 * 4), dp.fused.n, bt->D, bwd);
         if (fl <= di.lds_max) {

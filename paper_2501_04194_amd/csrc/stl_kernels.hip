@@ -114,7 +114,7 @@ hipError_t set_max_lds_exec_bwd(int bytes);
 hipError_t set_max_lds_exec_bwd_ws(int bytes);
 
 // no smooth mask, no smooth Until, no softmax-weighted window: the small kernels
-static bool plan_is_plain(const DevPlan& plan)
+bool plan_is_plain(const DevPlan& plan)
 {
     for (int k = plan.n_pred; k < plan.n_ins; ++k) {
         const Instr& I = plan.ins[k];
