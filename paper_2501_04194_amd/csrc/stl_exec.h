@@ -1521,9 +1521,11 @@ DEV void until_terms(const float* phi, const float* psi, int L, float bl, int M,
 // terms (nothing cancels, whatever the range).  The walk is bound by vector
 // issue: per term an add, a reciprocal (4 issue slots) and the sum, against
 // two 8-byte LDS reads per term and a chain of dependent adds with one output
-// per thread.  R = 4 where the trajectory has enough outputs to give every
-// lane of the work-group four, else 2 or 1 (the lanes are worth more than the
-// shared reads).
+// per thread.  R = 1 or 2 while one pass over the work-group, and a second for at
+// most an eighth of it, takes the trajectory (a lane is worth more than the
+// shared reads: 300 trajectories of 513 samples, interval [20, 200], 256 threads,
+// forward / backward 21.8 / 66.0 us with R = 2 in two passes, 30.4 / 89.2 with
+// R = 4 in one), else R = 4.
 // n consecutive terms from p: 16-byte reads where the lanes are 2 or 4 outputs
 // apart (p is then 16-byte aligned; the 8-byte reads of lanes 32 bytes apart
 // fall on each LDS bank four times, and bound the walk)
@@ -1543,7 +1545,11 @@ DEV void load_terms(const double* p, double (&v)[N])
     }
 }
 
-DEV int until_outputs(int L, int nt) { return L <= nt ? 1 : (L <= 2 * nt ? 2 : 4); }
+DEV int until_outputs(int L, int nt)
+{
+    const int pass = nt + (nt >> 3);
+    return L <= pass ? 1 : (L <= 2 * pass ? 2 : 4);
+}
 
 // One pass: the outputs base .. base + nt R - 1; Ep, Eq hold the terms from
 // position j0 on.
