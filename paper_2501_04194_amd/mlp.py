@@ -37,8 +37,8 @@ def _lib():
     L.stl_mse_grad.argtypes = [vp, vp, vp, vp, i64, vp]
     L.stl_adam_step.argtypes = [vp, vp, vp, vp, vp, i64, f32, f32, f32, f32, i32, vp]
     L.stl_ascent_update.argtypes = [vp, vp, vp, i64, i32, i32, i32, i32, f32, vp]
-    for f in ("stl_bf16_gemm", "stl_bf16_gemm_relu_grad", "stl_colsum_bf16", "stl_adam_step_multi", "stl_cast_bf16", "stl_relu_grad_bf16", "stl_colsum", "stl_mse_grad",
-              "stl_adam_step", "stl_ascent_update"):
+    for f in ("stl_bf16_gemm", "stl_bf16_gemm_relu_grad", "stl_colsum_bf16", "stl_adam_step_multi", "stl_cast_bf16",
+              "stl_relu_grad_bf16", "stl_colsum", "stl_mse_grad", "stl_adam_step", "stl_ascent_update"):
         getattr(L, f).restype = ctypes.c_int
     _c = L
     return L
@@ -97,8 +97,10 @@ def adam_step(w, g, m, v, w16, lr, b1, b2, eps, step):
 
 
 def adam_step_multi(tensors, lr, b1, b2, eps, step):
-    """tensors: (w, g, m, v, w16 or None) of one device."""
+    """tensors: (w, g, m, v, w16 or None) of one device; none at all is fine."""
     import torch
+    if not tensors:
+        return
     t = (AdamTensor * len(tensors))(*[AdamTensor(*[None if x is None else x.data_ptr() for x in q], q[0].numel())
                                       for q in tensors])
     stl._check(_lib().stl_adam_step_multi(t, len(tensors), lr, b1, b2, eps, step, _s(torch, tensors[0][0].device)))
