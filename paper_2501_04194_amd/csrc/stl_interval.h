@@ -319,6 +319,14 @@ constexpr int IVM_MAXT = 64;
 typedef float iv_f4 __attribute__((ext_vector_type(4)));
 typedef float iv_f4u __attribute__((ext_vector_type(4), aligned(4)));
 
+// orders the LDS accesses of a wave's lanes on either side of it (a wave's LDS
+// instructions execute in order: the compiler has to keep theirs)
+DEV void wave_sync()
+{
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+}
+
 template <int KS, int NT, bool GRAD, bool SW>
 __global__ void __launch_bounds__(IV_NT, 2) stl_interval_mfma_kernel(IntervalArgs A)
 {
@@ -371,6 +379,7 @@ __global__ void __launch_bounds__(IV_NT, 2) stl_interval_mfma_kernel(IntervalArg
         const float* xb = A.x + (bok ? b : 0) * (int64_t)T * D;
         float z[KS];
         int zm = INT_MIN;
+        wave_sync();                                  // the previous tile's traces are no longer read
 #pragma unroll
         for (int s = 0; s < KS; ++s) {
             const int k = 4 * s + row4;
@@ -459,6 +468,7 @@ __global__ void __launch_bounds__(IV_NT, 2) stl_interval_mfma_kernel(IntervalArg
             }
         }
         if (!SW && !bok) redo = 0;
+        wave_sync();                                  // traces visible to every lane of the wave
 #pragma unroll 1
         while (redo) {
             const int i = __builtin_ctz(redo);
