@@ -145,7 +145,6 @@ struct Env {
     float* lds;        // LDS beside the slots (smooth Until): export buffers, with slots in the workspace
                        // also the term tile and the checkpoints
     int tile;          // positions of the smooth Until's term tile in lds (0: terms in the scratch)
-    bool global;       // slots in the workspace
     Shared* sh;
     int tid;           // threadIdx.x, opaque per instruction: what is derived from it is not kept in registers
                        // across the program (hoisted, it spilled)
@@ -410,7 +409,6 @@ DEV T wg_sum(T v, const Env& e)
 }
 
 // ------------------------------------------------------------------ context
-
 
 // scratch layout (floats): what an operator needs, in units of Lc (at most
 // 16; the plan compiler finds each plan's need)
@@ -2504,7 +2502,6 @@ DEV void exec_adj(const Env& e, const Instr& I, float* mask_part)
             const float sb = wg_sum(pb * ib, e);
             if (e.tid == 0) { mask_part[2 * I.mslot] = sa; mask_part[2 * I.mslot + 1] = sb; }
         }
-        // d phi / d psi are sums of scaled terms: convert the scaled psi/phi sums in place
         break;
     }
     default:
@@ -2520,7 +2517,6 @@ DEV bool crosses_threads(const Instr& I) { return I.kind == K_WIN || I.kind == K
 // ------------------------------------------------------------------ kernels
 
 struct MaskTab;
-
 
 DEV bool next_item(const KArgs& ka, Shared& sh, int64_t& item, bool first, int64_t B)
 {
@@ -2667,7 +2663,6 @@ __global__ void __launch_bounds__(MAX_NT) stl_exec_kernel(DevPlan plan, Batch bt
         e.D = bt.D;
         e.arena = arena;
         e.scr = arena + (size_t)nslots * Lc;
-        e.global = GLOBAL;
         e.tile = GLOBAL ? ka.tile : 0;
         e.lds = GLOBAL ? smem : smem + ka.arena_floats;
         e.sh = &sh;

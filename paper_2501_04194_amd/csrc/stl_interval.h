@@ -780,7 +780,9 @@ hipError_t launch_pstl_descent(const float* x, int B, int T, int D, const float*
     A.c = c;
     for (int d = 0; d < 16; ++d) A.w[d] = d < D ? w[d] : 0.f;
     // as many lanes per signal (a power of two) as the work-group has for all of
-    // them; then each lane holds at most 24 of B T <= 12288 values
+    // them; then each lane holds at most 24 of B T <= 12288 values, and a step
+    // takes all of the kernel's NR (500 signals of 20 samples, 10 values each, 200
+    // steps: 590 us with NR = 10, 656 with 12)
     int lps = 1;
     while (lps < 64 && 2 * lps * B <= PD_NT && lps < T) lps *= 2;
     const int nr = (T + lps - 1) / lps;

@@ -67,10 +67,6 @@ __global__ void stl_fill_int(int* p, int64_t n, int v)
 #include "stl_interval.h"
 #include "stl_mx.h"
 
-namespace stlmi {
-
-}  // namespace stlmi
-
 // ------------------------------------------------------------------ launch helpers (host)
 
 namespace stlmi {
