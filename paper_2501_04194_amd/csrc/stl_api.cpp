@@ -1,6 +1,7 @@
-// C ABI of the STL robustness library: plan compiler, validation, launch
-// configuration, persistent scheduling order, autotuner and HIP-graph
-// capture.  Kernels live in stl_kernels.hip.
+// C ABI of the STL robustness library: validation, launch configuration,
+// persistent scheduling order, autotuner and HIP-graph capture.  The plan
+// compiler is stl_compile.cpp; the kernels are in stl_exec_*.hip and
+// stl_kernels.hip.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>

@@ -1,5 +1,5 @@
 // Internal execution-plan layout shared by the host plan compiler
-// (stl_api.cpp) and the device executor (stl_kernels.hip).  Not part of the
+// (stl_compile.cpp) and the device executor (stl_exec.h).  Not part of the
 // public ABI.
 //
 // A plan is a straight-line program over on-chip "slots" (one float per
