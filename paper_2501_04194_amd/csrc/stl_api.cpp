@@ -149,9 +149,10 @@ stl_status geometry(const stl_plan* plan, const stl_batch* bt, const stl_launch*
     // trajectories to fill the chip: 128 up to 128 samples (1,000 reach-avoid
     // trajectories of 100 samples, forward / backward: 12.3 / 22.4 us against 14.1 /
     // 26.3 with 256), 256 beyond (200 samples: 15.2 / 29.4 against 16.6 / 34.1), and
-    // 512 from 768 samples on where as many of them are resident (below), for plans
-    // without a smooth Until, whose lanes want the registers (1,000 samples: 88 / 350
-    // with 512 against 70 / 249).
+    // 512 from 768 samples on where as many of them are resident (below; at 600, 500
+    // trajectories take 0.72 to 1.16 of the time of 256, by formula), for plans without a
+    // smooth Until, whose lanes want the registers (1,000 samples: 88 / 350 with 512
+    // against 70 / 249).
     const int want0 = bt->T <= 128 ? 128 : bt->T < 768 || plan->until_b >= 0 || bt->offsets ? 256 : 512;
     int nt = cfg && cfg->threads ? cfg->threads : want0;
     if (nt != 64 && nt != 128 && nt != 256 && nt != 512) return fail(STL_E_ARG, "threads must be 64, 128, 256 or 512");

@@ -52,3 +52,28 @@ def test_values(n, smooth, B, T):
     ref, nodes = g.plan.forward(xd, g.pv, node_traces=True)
     assert torch.equal(ref, g.plan.forward(xd, g.pv))
     assert torch.equal(ref, g.plan.forward_static(xd, g.pv))
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("D,n", [(1, 32), (2, 32), (3, 32), (4, 32), (5, 26)])
+@pytest.mark.parametrize("T", [1, 70, 700])
+def test_predicates_in_their_place(D, n, T):
+    """Every state width's predicate code, slots in the workspace, dense and ragged, norm predicates among
+    them where the coefficients allow it."""
+    from gpu_util import check_formula
+    rng = np.random.default_rng(D * T)
+
+    def pred(k):
+        if D <= 2 and k % 4 == 3:
+            return {"op": "norm", "A": [[1.0] * D], "p": [0.1], "r": 0.2 + 0.01 * k, "sign": 1.0 if k % 8 == 3 else -1.0}
+        return {"op": "linear", "w": [float(v) for v in rng.normal(size=D)], "c": 0.1 * k / n}
+
+    level, op = [pred(k) for k in range(n)], "or"
+    while len(level) > 1:
+        level = [dict(op=op, children=level[i:i + 4], smooth=True, beta=8.0) for i in range(0, len(level), 4)]
+        op = "and" if op == "or" else "or"
+    launch = stl.Launch(0, 0, 1, 0)
+    x = np.cumsum(0.1 * rng.normal(size=(3, T, D)), axis=1).astype(np.float32)
+    check_formula(level[0], x, launch=launch, what="D=%d T=%d" % (D, T))
+    off = np.array([0, T, T, T + (T + 1) // 2], dtype=np.int64)
+    check_formula(level[0], x.reshape(-1, D)[:off[-1]].copy(), launch=launch, offsets=off, T=T, what="ragged D=%d" % D)
