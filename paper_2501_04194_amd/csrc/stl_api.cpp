@@ -178,17 +178,17 @@ stl_status geometry(const stl_plan* plan, const stl_batch* bt, const stl_launch*
     auto until_lds = [&](int threads, bool glob) {
         return until_lds_bytes(threads, ub, bwd, glob ? until_tile(threads) : 0, Lc);
     };
-    if (!(cfg && cfg->threads) && nt == 512) {
+    // (a fix-up launch behind the matrix-core or fused kernels has at most one work-group per four units)
+    const bool few = bt->B < di.cus || mx_applies(dp, bt, cfg, trace) || fused_applies(dp, bt, cfg, trace);
+    if (!(cfg && cfg->threads) && nt == 512 && !few) {
         // 512 threads unless a compute unit, by its LDS and the kernels' registers, then holds
-        // so many fewer work-groups that its share of the trajectories takes more turns (a
-        // fix-up launch has at most one work-group per unit): 1,000 trajectories of 1,600
-        // samples, a hard Always and Eventually, backward, two resident of either size, 198 ->
-        // 139 us; 500 of 1,024 under a smooth mask, one of either, 226 -> 156; but 500 of 900,
-        // two of 256 or one of 512, 124 -> 155, and 1,000 of 900, two unbounded windows,
-        // forward, four of 256 or three of 512, 13.9 -> 19.4.
+        // so many fewer work-groups that its share of the trajectories takes more turns:
+        // 1,000 trajectories of 1,600 samples, a hard Always and Eventually, backward, two
+        // resident of either size, 198 -> 139 us; 500 of 1,024 under a smooth mask, one of
+        // either, 226 -> 156; but 500 of 900, two of 256 or one of 512, 124 -> 155, and 1,000
+        // of 900, two unbounded windows, forward, four of 256 or three of 512, 13.9 -> 19.4.
         const int regs = plan_is_plain(dp) ? (bwd ? 16 : 24) : (bwd ? 8 : 16);      // waves the registers hold
-        const bool fixup = mx_applies(dp, bt, cfg, trace) || fused_applies(dp, bt, cfg, trace);
-        const int64_t share = fixup ? 1 : (bt->B + di.cus - 1) / di.cus;
+        const int64_t share = (bt->B + di.cus - 1) / di.cus;
         auto turns = [&](int threads) {
             const size_t a = (size_t)nslots * Lc + scratch(threads);
             const size_t wg = (a * sizeof(float) + until_lds(threads, false) + 240 + 1279) / 1280 * 1280;
@@ -196,14 +196,18 @@ stl_status geometry(const stl_plan* plan, const stl_batch* bt, const stl_launch*
             return fit > 0 ? (share + fit - 1) / fit : INT64_MAX;
         };
         if (turns(512) == INT64_MAX || turns(512) > turns(256)) nt = 256;
+    } else if (!(cfg && cfg->threads) && nt == 512) {
+        nt = 256;       // (sized below)
     }
     size_t arena = (size_t)nslots * Lc + scratch(nt);
     size_t lds = arena * sizeof(float) + until_lds(nt, false);
     bool global = (cfg && cfg->global_slots) || lds > di.lds_max;
-    if (!(cfg && cfg->threads) && bt->B < di.cus) {
-        // fewer trajectories than compute units (one work-group each): size
-        // the work-group to the trajectory (measured on MI355X: 64 threads
-        // for T <= 64, 128 up to 128, 256 up to 256, 512 beyond), but keep
+    if (!(cfg && cfg->threads) && few) {
+        // fewer work-groups than compute units: size the work-group to the
+        // trajectory (measured on MI355X: 64 threads for T <= 64, 128 up to 128,
+        // 256 up to 256, 512 beyond; a fix-up launch that takes 100 of 500 trajectories
+        // of 1,021 samples, forward / backward: 212 / 574 us with 512 threads, 318 / 907
+        // with 256, and the same 4 us of either with none to take), but keep
         // 256 where the larger Until checkpoint area of 512 threads would
         // push the arena out of LDS
         const int want = bt->T <= 64 ? 64 : bt->T <= 128 ? 128 : bt->T <= 256 ? 256 : 512;

@@ -2615,6 +2615,7 @@ __global__ void __launch_bounds__(MAX_NT) stl_exec_kernel(DevPlan plan, Batch bt
                 if (i < nrow) f |= ka.scan[blockIdx.x + (int64_t)i * gridDim.x];
             }
             if (__ballot(f != 0) == 0) return;
+            plan_touch(P);
         }
     } else plan_touch(P);
     float* arena = GLOBAL ? ka.garena + (size_t)blockIdx.x * ka.arena_floats : smem;
