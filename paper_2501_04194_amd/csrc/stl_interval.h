@@ -306,7 +306,7 @@ __global__ void __launch_bounds__(IV_NT) stl_interval_split_kernel(IntervalArgs 
 // beside it: one log, one reciprocal with a correction step and two
 // multiplications per output (through the library's general routines the
 // epilogue took as long as the writes), without branches.  4,096 signals x
-// 90,000 intervals of 20 samples without gradients: 982 -> 448 us.
+// 90,000 intervals of 20 samples without gradients: 982 -> 443 us.
 // SW: the operands the other way round (register q: trajectory b0 + 4(l/16) + q,
 // interval n0 + 16j + l%16): four 4-byte stores that cover 4 rows of 64 bytes
 // each, instead of one that covers 16.  With three outputs of 1.5 GB each the
